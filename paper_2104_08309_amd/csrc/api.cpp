@@ -787,7 +787,7 @@ pft_status forward3d_core(Arena& ar, const void* verts, int vdtype, int64_t nv, 
   hipError_t e = launch_mesh_info_single(verts, vdtype, 3, nv, info, s);
   if (e == hipSuccess)
     e = launch_face64(verts, vdtype, nv, tris, nf, info, c128 ? kTauF64 : kTauF32, f64, s, order, meta);
-  if (e == hipSuccess && !c128) e = launch_face32(f64, nf, kTauF32, kTauRel32, f32, s);
+  if (e == hipSuccess && !c128) e = launch_face32(f64, nf, f32, s);
   if (e != hipSuccess) return hip_fail(e, "3D prologue");
   uint32_t* perm = nullptr;
   if (q_order)
@@ -938,6 +938,10 @@ pft_status set_error(pft_status st, const char* msg) { return fail(st, msg); }
 // keeps): the Q are visited in the list order (no sort), the face splits are capped so that the
 // partial sums fit, and the PFT_VALIDATE check (synchronous) and timing events are not used.
 // `scratch_fn` supplies the buffer once the arguments have been checked.
+// Bytes per face that the size limit counts for an FP32C record (Face32 is smaller; the limit is part of the
+// entry point's contract).
+constexpr size_t kNoallocFace32Bytes = 96;
+static_assert(sizeof(Face32) <= kNoallocFace32Bytes, "the no-allocation limit covers the records");
 pft_status forward3d_noalloc(pft_status (*scratch_fn)(void**), size_t cap, const void* verts, int vdtype,
                              int64_t nv, const int32_t* tris, int64_t nf, const void* q, int qdtype, int64_t nq,
                              int mode, void* out, void* intensity, void* stream) {
@@ -949,8 +953,8 @@ pft_status forward3d_noalloc(pft_status (*scratch_fn)(void**), size_t cap, const
   if (intensity && !aligned(intensity, c128 ? 8 : 4)) return fail(PFT_EINVAL, "intensity misaligned");
   if (nq == 0) return PFT_OK;
   const size_t fixed = Arena::take<MeshInfo>(1) + Arena::take<Face64>(std::max<int64_t>(nf, 1)) +
-                       (c128 ? 0 : Arena::take<Face32>(std::max<int64_t>(nf, 1)));
-  const size_t per_face = sizeof(Face64) + (c128 ? 0 : sizeof(Face32));
+                       (c128 ? 0 : (std::max<size_t>((size_t)nf * kNoallocFace32Bytes, 256) + 255) / 256 * 256);
+  const size_t per_face = sizeof(Face64) + (c128 ? 0 : kNoallocFace32Bytes);
   if (fixed + Arena::take<double2>((size_t)nq) > cap) {
     if (fixed + Arena::take<double2>(1) > cap)
       return fail(PFT_EINVAL, "mesh too large for the no-allocation scratch: " + std::to_string(nf) +
@@ -1357,7 +1361,7 @@ pft_status pft_intensity_loss_3d(const void* verts, pft_dtype vdtype, int64_t nv
   if (e == hipSuccess) e = launch_face64(verts, vdtype, nv, tris, nf, info, kTauF64, f64, s);
   if (e == hipSuccess && ordered)
     e = launch_face64(verts, vdtype, nv, tris, nf, info, kTauF64, f64o, s, face_order, face_meta);
-  if (e == hipSuccess && !c128) e = launch_face32(f64o, nf, kTauF32, kTauRel32, f32, s);
+  if (e == hipSuccess && !c128) e = launch_face32(f64o, nf, f32, s);
   if (e != hipSuccess) return hip_fail(e, "loss prologue");
   uint32_t* perm = nullptr;
   if ((st = build_qorder(ar, q, qdtype, nq, nullptr, 1, &perm, s)) != PFT_OK) return st;
@@ -1455,7 +1459,7 @@ pft_status pft_forward_3d_regions(const void* verts, pft_dtype vdtype, int64_t n
   if (e == hipSuccess)
     e = launch_face64(verts, vdtype, nv, tris, nf, info, c128 ? kTauF64 : kTauF32, f64, s,
                       ordered ? face_order : nullptr, ordered ? face_meta : nullptr);
-  if (e == hipSuccess && !c128) e = launch_face32(f64, nf, kTauF32, kTauRel32, f32, s);
+  if (e == hipSuccess && !c128) e = launch_face32(f64, nf, f32, s);
   if (e != hipSuccess) return hip_fail(e, "3D prologue");
   double* region_R = nullptr;
   double4* split_geo = nullptr;
@@ -1647,7 +1651,7 @@ pft_status pft_backward_3d_regions(const void* verts, pft_dtype vdtype, int64_t 
     double2* partial = ar.get<double2>((size_t)std::max(plan.splits, 1) * nq);
     if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
     if (!c128) {
-      e = launch_face32(f64, nf, kTauF32, kTauRel32, f32, s);
+      e = launch_face32(f64, nf, f32, s);
       if (e != hipSuccess) return hip_fail(e, "regions prologue");
     }
     FwdArgs a;
@@ -1778,7 +1782,7 @@ static pft_status batch_forward_impl(const pft_mesh_batch* b, pft_mode mode, voi
   if (!c128) {
     f32 = ar.get<Face32>(std::max<int64_t>(p.nf, 1));
     if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-    hipError_t e = launch_face32(p.f64, p.nf, kTauF32, kTauRel32, f32, s);
+    hipError_t e = launch_face32(p.f64, p.nf, f32, s);
     if (e != hipSuccess) return hip_fail(e, "batch prologue");
   }
   // work items: (mesh, Q-tile, face chunk), longest first, for given tile sizes; returns the number of

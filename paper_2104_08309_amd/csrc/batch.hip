@@ -148,7 +148,7 @@ __global__ __launch_bounds__(kBlock, QPT >= 3 ? kBatchFwdWaves : kBatchFwdWaves 
     float qmax = 0.0f;
 #pragma unroll
     for (int k = 0; k < QPT; ++k) qmax = fmaxf(qmax, sqrtf(Q2[k]));
-    const bool check = __builtin_amdgcn_readfirstlane((int)sinc_range_test_needed(wave_max(qmax), mi.rho)) != 0;
+    const bool check = __builtin_amdgcn_readfirstlane((int)fit_range_test_needed(wave_max(qmax), mi.rho)) != 0;
     float sr[QPT], si[QPT], cr[QPT], ci[QPT];
 #pragma unroll
     for (int k = 0; k < QPT; ++k) sr[k] = si[k] = cr[k] = ci[k] = 0.0f;
@@ -163,12 +163,10 @@ __global__ __launch_bounds__(kBlock, QPT >= 3 ? kBatchFwdWaves : kBatchFwdWaves 
       float tr[QPT], ti[QPT];
 #pragma unroll
       for (int k = 0; k < QPT; ++k) tr[k] = ti[k] = 0.0f;
-      // transcendentals in one run per face at 2 Q per thread (measured neutral at 1; at 3 the run
-      // would add register pressure to a variant that already spills)
       if (check)
-        fwd_tile_fp32c<QPT, SHARE, true, (QPT == 2)>(tile, nt, qx, qy, qz, ql, small, tr, ti, carry);
+        fwd_tile_fp32c<QPT, SHARE, true>(tile, nt, qx, qy, qz, ql, tr, ti, carry);
       else
-        fwd_tile_fp32c<QPT, SHARE, false, (QPT == 2)>(tile, nt, qx, qy, qz, ql, small, tr, ti, carry);
+        fwd_tile_fp32c<QPT, SHARE, false>(tile, nt, qx, qy, qz, ql, tr, ti, carry);
 #pragma unroll
       for (int k = 0; k < QPT; ++k) {
         kahan_add(sr[k], cr[k], tr[k]);
@@ -192,8 +190,8 @@ __global__ __launch_bounds__(kBlock, QPT >= 3 ? kBatchFwdWaves : kBatchFwdWaves 
     for (int k = 0; k < QPT; ++k) {
       if (l + k * 64 < it.nq) {
         const double2 v = small[k] ? make_double2(xr[k], xi[k])
-                                   : make_double2(((double)sr[k] - (double)cr[k]) * kInvSumScale32,
-                                                  ((double)si[k] - (double)ci[k]) * kInvSumScale32);
+                                   : make_double2((double)sr[k] - (double)cr[k],
+                                                  (double)si[k] - (double)ci[k]);
         store_stream(partial + it.part + l + k * 64, v);
       }
     }

@@ -11,12 +11,11 @@
 //
 // Two arithmetic forms:
 //  * fwd3d_fp64_kernel  -- IEEE binary64 throughout.
-//  * fwd3d_fp32c_kernel -- edge arithmetic in binary32 on face-local
-//    coordinates, the face origin phase Q.g reduced in binary64 and
-//    evaluated in turns, the near-degenerate series branch in binary64, the
-//    sum over faces blocked per LDS tile and compensated (Kahan) across tiles.
-//    With the records in an edge-sharing order (Face32::flags) a face takes
-//    the term of the edge it shares with its predecessor from registers.
+//  * fwd3d_fp32c_kernel -- the face integral in binary32 from its centred
+//    vertex phases (fwd_terms.h), the face origin phase Q.g reduced in
+//    binary64 and evaluated in turns, the sum over faces blocked per LDS tile
+//    and compensated (Kahan) across tiles. With the records in an edge-sharing
+//    order (Face32::flags) the origin phase follows the shared edges.
 #include "fwd_terms.h"
 
 namespace pft {
@@ -95,8 +94,8 @@ __global__ __launch_bounds__(kBlock) void fwd3d_fp64_kernel(FwdArgs a) {
 // A wavefront that is done leaves its binary64 partials in its own tile and counts itself done; the
 // last of the block's wavefronts adds their partials of each Q in wavefront order and writes them (one
 // partial per Q and block), and the others exit at once. SHARE: the records are in an
-// edge-sharing order and each face takes one edge term from its predecessor in the wavefront's range
-// (two edge terms per face instead of three). Small-|Q| lanes (|Q| R < tau0, R the split's radius) take
+// edge-sharing order and each face takes its origin phase from its predecessor in the wavefront's range
+// (binary32 instead of the binary64 dot product). Small-|Q| lanes (|Q| R < tau0, R the split's radius) take
 // the binary64 tetrahedron fan about the split's apex.
 template <bool SHARE, int QPT>
 __global__ __launch_bounds__(kFwdBlock, fwd_waves(QPT)) void fwd3d_fp32c_kernel(FwdArgs a) {
@@ -152,11 +151,11 @@ __global__ __launch_bounds__(kFwdBlock, fwd_waves(QPT)) void fwd3d_fp32c_kernel(
   float qmax = 0.0f;
 #pragma unroll
   for (int k = 0; k < QPT; ++k) qmax = fmaxf(qmax, sqrtf(Q2[k]));
-  const bool check = __builtin_amdgcn_readfirstlane((int)sinc_range_test_needed(wave_max(qmax), a.info[0].rho)) != 0;
+  const bool check = __builtin_amdgcn_readfirstlane((int)fit_range_test_needed(wave_max(qmax), a.info[0].rho)) != 0;
   float sr[QPT], si[QPT], cr[QPT], ci[QPT];
 #pragma unroll
   for (int k = 0; k < QPT; ++k) sr[k] = si[k] = cr[k] = ci[k] = 0.0f;
-  FwdCarry<QPT> carry;  // shared edge term from the previous face (SHARE)
+  FwdCarry<QPT> carry;  // shared edge's phase from the previous face (SHARE)
   carry.reset();         // no previous face at the start of the range
   for (int64_t t0 = f_begin; t0 < f_end; t0 += kTileF32) {
     const int nt = (int)min((int64_t)kTileF32, f_end - t0);
@@ -173,9 +172,9 @@ __global__ __launch_bounds__(kFwdBlock, fwd_waves(QPT)) void fwd3d_fp32c_kernel(
 #pragma unroll
     for (int k = 0; k < QPT; ++k) tr[k] = ti[k] = 0.0f;
     if (check)
-      fwd_tile_fp32c<QPT, SHARE, true, SHARE>(tile, nt, qx, qy, qz, ql, small, tr, ti, carry);
+      fwd_tile_fp32c<QPT, SHARE, true>(tile, nt, qx, qy, qz, ql, tr, ti, carry);
     else
-      fwd_tile_fp32c<QPT, SHARE, false, SHARE>(tile, nt, qx, qy, qz, ql, small, tr, ti, carry);
+      fwd_tile_fp32c<QPT, SHARE, false>(tile, nt, qx, qy, qz, ql, tr, ti, carry);
 #pragma unroll
     for (int k = 0; k < QPT; ++k) {
       kahan_add(sr[k], cr[k], tr[k]);
@@ -202,8 +201,8 @@ __global__ __launch_bounds__(kFwdBlock, fwd_waves(QPT)) void fwd3d_fp32c_kernel(
 #pragma unroll
   for (int k = 0; k < QPT; ++k)
     red[k * 64 + lane] = small[k] ? make_double2(xr[k], xi[k])
-                                  : make_double2(((double)sr[k] - (double)cr[k]) * kInvSumScale32,
-                                                 ((double)si[k] - (double)ci[k]) * kInvSumScale32);
+                                  : make_double2((double)sr[k] - (double)cr[k],
+                                                 (double)si[k] - (double)ci[k]);
   // count this wavefront done once its partials are visible to the block; the last one adds them all
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
   int last = 0;

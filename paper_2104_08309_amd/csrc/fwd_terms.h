@@ -2,6 +2,7 @@
 // forms, shared by the single-mesh and batched kernels (formulas in pft_device.h).
 #pragma once
 
+#include "face_poly.h"
 #include "moment_poly.h"
 #include "pft_device.h"
 
@@ -66,49 +67,62 @@ PFT_HD __forceinline__ void face_term_f64(const Face64& f, const double* Q, doub
 // ---------------------------------------------------------------------------
 // FP32-compensated per-(Q, face) term
 // ---------------------------------------------------------------------------
-// Per (Q, face), in binary32 on the record's face-local quantities (Face32):
-//   QN = Q.N' = Q.n/2, s_j = Q.e_j/2, |P'|^2 = s1^2 + s2^2 = |P|^2 / (4|N|^2),
-//   w_l = s2 al_l + s1 be_l = P.d_l / (4 pi |N|) (w_2 = -w_0 - w_1),
-//   edge half-phases eta_l = Q.d_l / (4 pi) = s1 al_l - s2 be_l in turns,
-//   half-vertex phases p_k = Q.u_k / (4 pi) (p_2 = -p_0 - p_1, eta_l = p_{l+1} - p_l),
-//   edge midpoint phase t_l = r - p_{l+2} with r = Q.g / (2 pi),
-//   E_l = 2 pi sinc(2 pi eta_l) exp(2 pi i t_l),  T = (QN / |P'|^2) sum_l w_l E_l,
-// the face term (Q.N)/|P|^2 exp(iQ.g) S of the 3D section written in turns. The
-// 2 pi sinc comes from sinc2pi_poly (no transcendental instruction) and the
-// midpoint exponentials from the hardware sine and cosine of turns.
+// T = -i (Q.N) exp(iQ.g) J, J the face integral normalised by twice the area, a symmetric function of the
+// centred vertex phases d_k = Q.u_k (d_0 + d_1 + d_2 = 0) alone. In binary32 on the record's face-local
+// quantities (Face32), with the phases as p_k = d_k / (4 pi) (half-phases in turns, p_2 = -s, s = p_0 + p_1):
 //
-// Where the midpoint phases come from. In an edge-sharing order (Face32::flags)
-// edge 0 of a linked face is the previous record's edge 1: the same segment, so
-// the same midpoint. Its phase t_0 = r + p_0 + p_1 is carried in registers
-// (reduced to [-1/2, 1/2] turn), and the two new midpoint phases follow from it
-// and the face's own half-vertex phases without the origin phase:
-//   t_1 = t_0 - (2 p_0 + p_1) = t_0 - eta_2,   t_2 = t_0 + (-p_0 - 2 p_1) = t_0 + eta_1.
-// Each carried step rounds once in binary32 (at most 2^-25 turn for a phase in
-// [-1/2, 1/2]), so the chain is re-anchored every kAnchor faces: there, and at
-// every face that does not follow its predecessor across an edge, the origin
-// phase r = Q.g / (2 pi) is formed in binary64 and reduced to [-1/2, 1/2]
-// before it is rounded to binary32. The edge term sinc(eta) exp(i Q.m) of the
-// carried edge is carried too (its sinc and the cosine and sine of its
-// midpoint phase): it depends only on the edge, since the sinc is even.
-// Near-degenerate pairs (Q nearly along the face normal, and empty faces) are
-// replaced by the face's simplex series (binary32 through a fitted polynomial at
-// small phases, binary64 beyond).
-
-// The FP32C forward sums tau_rel times each face term (Face32::N); partial sums are divided by it once.
-constexpr double kInvSumScale32 = 1.0 / kTauRel32;
-
+// * largest |d_k| <= FaceFit32::M: J = A(P, w) + i E B(P, w), two fitted polynomials in P = p_0^2 + p_0 p_1 +
+//   p_1^2 and w = E^2, E = p_0 p_1 s (face_poly.h; fit error 2.3e-8 of J(0) = 1/2). No quotient, so nothing
+//   cancels and Q along the face normal is an ordinary point; one sine and one cosine (of the face origin
+//   phase) are the only transcendental instructions.
+// * beyond: the divided differences of exp over the pairs of vertices, each an edge term sinc exp(i midpoint
+//   phase). -i (d_j - d_k) J is the difference of the two other edges' terms; weighting the three relations
+//   by the differences themselves gives the symmetric form
+//     J = i / (2 p) sum_k d_k E_k,   E_k the term of the edge opposite vertex k (midpoint phase -d_k / 2,
+//                                    half-difference (d_{k+1} - d_{k+2}) / 2),  p = d_0^2 + d_0 d_1 + d_1^2
+//   (the 3D section's edge sum with the weights expressed in the phases). p >= 3/4 max d_k^2, so |d_k| / (2 p)
+//   stays below 1 / M here: nothing is divided by a small number.
+//
+// The choice is per lane, on the pair's own phases, so a Q's value does not depend on the other Q of its
+// wavefront.
+//
+// The face origin phase r = Q.g / (2 pi) (turns). In an edge-sharing order (Face32::flags) a face's edge 0 is
+// its predecessor's edge 1, the same segment: its midpoint phase is t = r - p_2 = r + s. t is carried in a
+// register, reduced to [-1/2, 1/2] turn: r = t - s, and the phase passed on is that of the face's own edge 1,
+// r - p_0 = t - (s + p_0), formed from t so that each step adds one rounding of t (at most 2^-25 turn). The
+// chain is re-anchored every kAnchor faces: there, and at every face that does not follow its predecessor across
+// an edge, r is formed in binary64 and reduced to [-1/2, 1/2] before it is rounded to binary32.
+//
+// Cost and bound: FP32 vector issue (99 460 faces x 64 000 Q: 8.33 -> 5.54 ms a call against the form that summed
+// the three edge terms of every pair, with 5 transcendentals; 5 120 x 262 144: 1.65 -> 1.12 ms). Per pair 9 operations for Q.N, p_0, p_1, 6 for s, P, E, w, 14 for the
+// polynomials, 5 for the phase chain, 6 for the complex product and the sums, 2 transcendentals.
 #ifndef PFT_ANCHOR
 #define PFT_ANCHOR kTileF32
 #endif
 constexpr int kAnchor = PFT_ANCHOR;  // faces between binary64 origin phases in a chain (divides kTileF32)
-static_assert(kTileF32 % kAnchor == 0 && kAnchor % 2 == 0, "anchor interval: even, and divides the face tile");
+static_assert(kTileF32 % kAnchor == 0, "the anchor interval divides the face tile");
 
-// Inputs of the series fix-up for one pair.
-struct SeriesInputs {
-  float p0, p1;  // half-vertex phases psi_0, psi_1 in turns
-  float QN;      // Q . N, times whatever factor the caller's sums carry (the term is linear in it)
-  float r;       // face origin phase Q.g in turns (any integer offset)
-};
+// sum_a C::c[a] x^a in binary32 by fused multiply-adds whose addend is the instruction's literal. (Left to
+// itself the compiler keeps a loop's coefficients in scalar registers, and a scalar source halves the issue
+// rate of a vector instruction on this target: 99 460 faces x 64 000 Q, 5.80 ms against 5.66 ms.)
+template <class C, int A>
+__device__ __forceinline__ float horner_lit_from(float s, float x) {
+  if constexpr (A < 0) {
+    return s;
+  } else {
+    float r;
+    asm("v_fmaak_f32 %0, %1, %2, %3" : "=v"(r) : "v"(s), "v"(x), "n"(__builtin_bit_cast(int, C::c[A])));
+    return horner_lit_from<C, A - 1>(r, x);
+  }
+}
+template <class C>
+__device__ __forceinline__ float horner_lit(float x) {
+  constexpr int N = sizeof(C::c) / sizeof(C::c[0]);
+  return horner_lit_from<C, N - 2>(C::c[N - 1], x);
+}
+
+// Largest |p_k| in the range of FaceFit32.
+constexpr float kFitMax32 = (float)(FaceFit32::M / 12.566370614359172954);
 
 // The face integral J = sum_n i^n h_n(d) / (n+2)! (normalised by twice the area) in
 // binary32 from the polynomial P of exp(ix) fitted on [-P::M, P::M]: J = sum_n i^n
@@ -145,42 +159,11 @@ __device__ __forceinline__ void face_integral_poly(float d0, float d1, float& jr
   }
 }
 
-// Q nearly along the face normal: the face's simplex series,
-// T = -i (Q.N) exp(i Q.g) sum_n i^n h_n(delta) / (n+2)!, delta_k = 4 pi psi_k,
-// from the binary32 phases of the edge form (their rounding is that of the
-// edge form's own inputs). A lane whose largest |delta_k| is within the fitted
-// polynomial's range (always so for |Q_perp| L < 0.1, and for the relative test
-// while 0.02 |Q| rho stays below it) evaluates it in binary32, within 1e-7 of J;
-// a lane beyond it sums the series in binary64 to 1e-10 of the sum. The choice is
-// per lane, so a Q's value does not depend on the other lanes of its wavefront.
-__device__ __forceinline__ void face_series_fp32c(const SeriesInputs& sd, float& Tr, float& Ti) {
-  constexpr float kFourPiF = 12.566370614359172954f;
-  const float d0 = kFourPiF * sd.p0, d1 = kFourPiF * sd.p1;
-  const float m = fmaxf(fabsf(d0), fmaxf(fabsf(d1), fabsf(d0 + d1)));
-  if (m <= FacePoly::M) {
-    float sr, si;
-    face_integral_poly<FacePoly>(d0, d1, sr, si);
-    const float cf = cos_turns(sd.r), sf = sin_turns(sd.r);
-    Tr = sd.QN * (cf * si + sf * sr);
-    Ti = -sd.QN * (cf * sr - sf * si);
-    return;
-  }
-  constexpr double kFourPi = 12.566370614359172954;
-  const double q0 = kFourPi * (double)sd.p0, q1 = kFourPi * (double)sd.p1;
-  double sr, si;
-  face_series_f64(q0, q1, -q0 - q1, sr, si, 1e-10);
-  const double cf = (double)cos_turns(sd.r), sf = (double)sin_turns(sd.r);
-  const double QN = (double)sd.QN;
-  Tr = (float)(QN * (cf * si + sf * sr));
-  Ti = (float)(-QN * (cf * sr - sf * si));
-}
-
-// What one thread carries from face to face within a face range: the edge 1 of
-// the previous record, as its 2 pi sinc(2 pi eta), the cosine and sine of its
-// midpoint phase, and that phase in turns reduced to [-1/2, 1/2].
+// What one thread carries from face to face within a face range: the midpoint phase of the previous record's
+// edge 1, in turns reduced to [-1/2, 1/2].
 template <int NQ>
 struct FwdCarry {
-  float c[NQ], cs[NQ], sn[NQ], t[NQ];
+  float t[NQ];
   bool prev;             // there is a previous record in this range (uniform)
   __device__ __forceinline__ void reset() { prev = false; }
 };
@@ -241,191 +224,135 @@ __device__ __forceinline__ float wave_max(float v) {
   return v;
 }
 
-// Whether any edge half-phase |eta| = |Q.d| / (4 pi) of a wavefront can exceed
-// the polynomial sinc's range: |d| <= 2 rho for a face whose vertices lie within
-// rho of its centroid, so |eta| <= qmax rho / (2 pi). A wavefront that passes
-// this test never meets an argument beyond kSincPolyMax (1e-3 of margin for
-// rounding) and skips the per-lane range test; each lane's value is the same
-// either way.
-__device__ __forceinline__ bool sinc_range_test_needed(float qmax, double rho) {
-  return (double)qmax * rho * kInv2PiD > 0.999 * (double)kSincPolyMax;
+// Whether a centred vertex phase of a wavefront can exceed the fitted range: |d_k| <= |Q| rho for a face whose
+// vertices lie within rho of its centroid. A wavefront that passes this test never meets a phase beyond
+// FaceFit32::M (1e-3 of margin for rounding) and skips the per-lane test; each lane's value is the same either
+// way.
+__device__ __forceinline__ bool fit_range_test_needed(float qmax, double rho) {
+  return (double)qmax * rho > 0.999 * FaceFit32::M;
 }
 
-// S = sum_l w_l sinc_l e^{2 pi i t_l} of one face and Q from the carried edge 0 (its sinc c0 and
-// exponential e0) and the new edges 1 and 2, with w_2 = -(w_0 + w_1).
-__device__ __forceinline__ void edge_sum(float w0, float w1, float c0, float c1, float c2, float e0c, float e0s,
-                                         float e1c, float e1s, float e2c, float e2s, float& Sr, float& Si) {
-  const float a0 = w0 * c0, a1 = w1 * c1, a2 = (w0 + w1) * c2;
-  Sr = a0 * e0c + a1 * e1c - a2 * e2c;
-  Si = a0 * e0s + a1 * e1s - a2 * e2s;
+// The face term beyond the fitted range (edge terms, above): T / (Q.N) = 1 / (16 pi^2 P) sum_k p_k c_k exp(2 pi i t_k)
+// with t_k = r - p_k and c_k = 2 pi sinc of x_k = p_{k+1} - p_{k+2} (in turns, sin(2 pi x_k) from the exponentials
+// already formed: x_k = t_{k+2} - t_{k+1}).
+__device__ __forceinline__ void face_edge_term_fp32c(float r, float p0, float p1, float s, float P,
+                                                     float& Tr, float& Ti) {
+  constexpr float kInv16Pi2 = 0.0063325739776461107152f;
+  const float p[3] = {p0, p1, -s};
+  float c[3], cs[3], sn[3];
+  bool wide = false;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    const float t = r - p[k], x = p[(k + 1) % 3] - p[(k + 2) % 3];
+    cs[k] = cos_turns(t);
+    sn[k] = sin_turns(t);
+    c[k] = sinc2pi_poly(x);
+    wide |= fabsf(x) > kSincPolyMax;
+  }
+  if (wide) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const int i = (k + 1) % 3, j = (k + 2) % 3;
+      const float x = p[i] - p[j];
+      c[k] = fabsf(x) > kSincPolyMax ? (sn[j] * cs[i] - sn[i] * cs[j]) * rcp_f(x) : c[k];
+    }
+  }
+  const float a0 = p[0] * c[0], a1 = p[1] * c[1], a2 = p[2] * c[2];
+  const float co = kInv16Pi2 * rcp_f(P);
+  Tr = co * (a0 * cs[0] + a1 * cs[1] + a2 * cs[2]);
+  Ti = co * (a0 * sn[0] + a1 * sn[1] + a2 * sn[2]);
 }
 
-// One face record against a thread's NQ Q points: adds each term to tr[k], ti[k]
-// (lanes with small[k] set are left for the caller's small-|Q| path). CHECK:
-// test each edge half-phase against the polynomial sinc's range; anchor: form
-// the origin phase in binary64 even when the face is linked. `cin` holds the
-// previous record's edge 1 (edge 0 of a linked face); the face's own edge 1 goes
-// to `cout` (SHARE only; the two may be the same object).
-template <int NQ, bool SHARE, bool CHECK, bool TC, class QL>
+// One face record against a thread's NQ Q points: adds each term to tr[k], ti[k]. CHECK: test each pair's phases
+// against the fitted range; anchor: form the origin phase in binary64 even when the face is linked. `c` holds the
+// previous record's edge-1 midpoint phase and gets this one's (SHARE only).
+template <int NQ, bool SHARE, bool CHECK, class QL>
 __device__ __forceinline__ void fwd_face_fp32c(const Face32& f, const float* qx, const float* qy, const float* qz,
-                                               const QL& ql, const bool* small, float* tr,
-                                               float* ti, bool anchor, FwdCarry<NQ>& cin, FwdCarry<NQ>& cout) {
-  const uint32_t flags = __builtin_amdgcn_readfirstlane(f.flags);
-  const bool linked = SHARE && cin.prev && (flags & kFaceLinked) != 0u;
-  float QN[NQ], P2[NQ], w0[NQ], w1[NQ], x1[NQ], x2[NQ], c1[NQ], c2[NQ];
-  float m = 0.0f;
+                                               const QL& ql, float* tr, float* ti, bool anchor, FwdCarry<NQ>& c) {
+  float QN[NQ], p0[NQ], p1[NQ], s[NQ], P[NQ], r[NQ], Tr[NQ], Ti[NQ];
+  bool far[NQ];
+  bool any = false, all = true;
 #pragma unroll
   for (int k = 0; k < NQ; ++k) {
     QN[k] = qx[k] * f.N[0] + qy[k] * f.N[1] + qz[k] * f.N[2];
-    const float s1 = qx[k] * f.E1[0] + qy[k] * f.E1[1] + qz[k] * f.E1[2];
-    const float s2 = qx[k] * f.E2[0] + qy[k] * f.E2[1] + qz[k] * f.E2[2];
-    P2[k] = s1 * s1 + s2 * s2;
-    w0[k] = s2 * f.al[0] + s1 * f.be[0];
-    w1[k] = s2 * f.al[1] + s1 * f.be[1];
-    // edge half-phases eta_1, eta_2 (eta_0 = -eta_1 - eta_2)
-    x1[k] = s1 * f.al[1] - s2 * f.be[1];
-    x2[k] = s1 * f.al[2] - s2 * f.be[2];
-    c1[k] = sinc2pi_poly(x1[k]);
-    c2[k] = sinc2pi_poly(x2[k]);
-    if (CHECK) m = fmaxf(m, fmaxf(fabsf(x1[k]), fabsf(x2[k])));
-  }
-  if (CHECK && __builtin_expect(m > kSincPolyMax, 0)) {  // long edges at large |Q|: the sine quotient
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-      c1[k] = sinc2pi_wide(x1[k], c1[k]);
-      c2[k] = sinc2pi_wide(x2[k], c2[k]);
+    p0[k] = qx[k] * f.u0[0] + qy[k] * f.u0[1] + qz[k] * f.u0[2];
+    p1[k] = qx[k] * f.u1[0] + qy[k] * f.u1[1] + qz[k] * f.u1[2];
+    s[k] = p0[k] + p1[k];
+    P[k] = p0[k] * s[k] + p1[k] * p1[k];
+    if (CHECK) {
+      far[k] = fmaxf(fabsf(p0[k]), fmaxf(fabsf(p1[k]), fabsf(s[k]))) > kFitMax32;
+      any |= far[k];
+      all &= far[k];
     }
   }
-  // Edge 0 where it is not the carried edge: its midpoint phase t_0 = r + p_0 + p_1 = r + (eta_2 - eta_1)/3
-  // from the binary64 origin phase (also at an anchor, replacing the carried phase), and its term when
-  // unlinked.
-  if (!linked || anchor) {
+  const bool linked = SHARE && c.prev && (__builtin_amdgcn_readfirstlane(f.flags) & kFaceLinked) != 0u;
+  if (linked && !anchor) {
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
-      const double ph =
-          ql.qd_here(qx[k], k, 0) * f.gt[0] + ql.qd_here(qy[k], k, 1) * f.gt[1] + ql.qd_here(qz[k], k, 2) * f.gt[2];
-      const float r = (float)(ph - rint(ph));
-      cin.t[k] = r + (x2[k] - x1[k]) * (1.0f / 3.0f);
-    }
-    if (!linked) {  // first face of a chain, or the list order
-      float m0 = 0.0f;
-#pragma unroll
-      for (int k = 0; k < NQ; ++k) {
-        const float x0 = -(x1[k] + x2[k]);
-        cin.c[k] = sinc2pi_poly(x0);
-        if (CHECK) m0 = fmaxf(m0, fabsf(x0));
-        cin.cs[k] = cos_turns(cin.t[k]);
-        cin.sn[k] = sin_turns(cin.t[k]);
-      }
-      if (CHECK && __builtin_expect(m0 > kSincPolyMax, 0)) {
-#pragma unroll
-        for (int k = 0; k < NQ; ++k) cin.c[k] = sinc2pi_wide(-(x1[k] + x2[k]), cin.c[k]);
-      }
-    }
-  }
-  float Sr[NQ], Si[NQ], co[NQ], t1[NQ];
-  bool need[NQ];
-  bool any = false;
-  if constexpr (TC) {
-    // The face's transcendental instructions back to back. On this target every switch between
-    // transcendental and ordinary vector instructions costs issue cycles, so one run of 5 NQ is cheaper
-    // than the several shorter ones the compiler forms by itself; the scheduling barriers keep it from
-    // interleaving them (at the price of a few more live registers).
-    float t2[NQ], e1c[NQ], e1s[NQ], e2c[NQ], e2s[NQ], rp[NQ];
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-      // t_1 = t_0 - eta_2, t_2 = t_0 + eta_1
-      t1[k] = cin.t[k] - x2[k];
-      t2[k] = cin.t[k] + x1[k];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-      e1c[k] = cos_turns(t1[k]);
-      e1s[k] = sin_turns(t1[k]);
-      e2c[k] = cos_turns(t2[k]);
-      e2s[k] = sin_turns(t2[k]);
-      rp[k] = rcp_f(P2[k]);
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (int k = 0; k < NQ; ++k) {
-      edge_sum(w0[k], w1[k], cin.c[k], c1[k], c2[k], cin.cs[k], cin.sn[k], e1c[k], e1s[k], e2c[k], e2s[k], Sr[k], Si[k]);
-      co[k] = QN[k] * rp[k];
-      // |Q_perp| L < tau or |Q_perp| < tau_rel |Q| (and every pair of an empty face): the series
-      need[k] = P2[k] < fmaf(QN[k], QN[k], f.thr) && !small[k];
-      any |= need[k];
-      if (SHARE) {
-        cout.c[k] = c1[k];
-        cout.cs[k] = e1c[k];
-        cout.sn[k] = e1s[k];
-      }
+      r[k] = c.t[k] - s[k];
+      c.t[k] = c.t[k] - (s[k] + p0[k]);
     }
   } else {
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
-      t1[k] = cin.t[k] - x2[k];
-      const float t2 = cin.t[k] + x1[k];
-      const float e1c = cos_turns(t1[k]), e1s = sin_turns(t1[k]);
-      const float e2c = cos_turns(t2), e2s = sin_turns(t2);
-      edge_sum(w0[k], w1[k], cin.c[k], c1[k], c2[k], cin.cs[k], cin.sn[k], e1c, e1s, e2c, e2s, Sr[k], Si[k]);
-      co[k] = QN[k] * rcp_f(P2[k]);
-      need[k] = P2[k] < fmaf(QN[k], QN[k], f.thr) && !small[k];
-      any |= need[k];
-      if (SHARE) {
-        cout.c[k] = c1[k];
-        cout.cs[k] = e1c;
-        cout.sn[k] = e1s;
-      }
+      const double ph =
+          ql.qd_here(qx[k], k, 0) * f.gt[0] + ql.qd_here(qy[k], k, 1) * f.gt[1] + ql.qd_here(qz[k], k, 2) * f.gt[2];
+      r[k] = (float)(ph - rint(ph));
+      if (SHARE) c.t[k] = r[k] - p0[k];
     }
   }
-  // one branch per face for the rare lanes that need the series (of any of their NQ points)
-  if (__builtin_expect(any, 0)) {
+  if (!CHECK || !all) {  // some pair of this lane is in the fitted range
+    float jr[NQ], ji[NQ], cf[NQ], sf[NQ];
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
-      if (need[k]) {
-        // half-vertex phases from the edge half-phases: p_0 = (2 eta_2 + eta_1)/3, p_1 = -(2 eta_1 + eta_2)/3
-        SeriesInputs sd;
-        sd.p0 = (2.0f * x2[k] + x1[k]) * (1.0f / 3.0f);
-        sd.p1 = -(2.0f * x1[k] + x2[k]) * (1.0f / 3.0f);
-        sd.QN = QN[k] * f.nN;  // tau_rel Q.N through the record's own N', as in the edge form
-        sd.r = t1[k] + sd.p0;
-        face_series_fp32c(sd, Sr[k], Si[k]);  // tau_rel times the face term, like the edge form's
-        co[k] = 1.0f;
-      }
+      const float E = p0[k] * p1[k] * s[k];
+      const float w = E * E;
+      jr[k] = horner_lit<FaceFit32::A1>(P[k]) * w + horner_lit<FaceFit32::A0>(P[k]);
+      ji[k] = E * (horner_lit<FaceFit32::B1>(P[k]) * w + horner_lit<FaceFit32::B0>(P[k]));
+    }
+    // The face's transcendental instructions back to back: every switch between transcendental and ordinary
+    // vector instructions costs issue cycles on this target.
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+      cf[k] = cos_turns(r[k]);
+      sf[k] = sin_turns(r[k]);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+      Tr[k] = cf[k] * ji[k] + sf[k] * jr[k];
+      Ti[k] = sf[k] * ji[k] - cf[k] * jr[k];
+    }
+  }
+  if (CHECK && __builtin_expect(any, 0)) {  // one branch per face for the lanes with a pair beyond it
+#pragma unroll
+    for (int k = 0; k < NQ; ++k) {
+      float Xr, Xi;
+      face_edge_term_fp32c(r[k], p0[k], p1[k], s[k], P[k], Xr, Xi);
+      Tr[k] = far[k] ? Xr : Tr[k];
+      Ti[k] = far[k] ? Xi : Ti[k];
     }
   }
 #pragma unroll
   for (int k = 0; k < NQ; ++k) {
-    tr[k] = fmaf(co[k], Sr[k], tr[k]);
-    ti[k] = fmaf(co[k], Si[k], ti[k]);
-    if (SHARE) cout.t[k] = t1[k] - rintf(t1[k]);
+    tr[k] = fmaf(QN[k], Tr[k], tr[k]);
+    ti[k] = fmaf(QN[k], Ti[k], ti[k]);
+    if (SHARE) c.t[k] = c.t[k] - rintf(c.t[k]);
   }
-  cout.prev = true;
+  c.prev = true;
 }
 
-// One LDS tile of FP32C face records against the NQ Q points of a thread
-// (plain binary32 sums inside the tile). SHARE: the records are in an
-// edge-sharing order; `c` carries the shared edge's term and midpoint phase
-// across faces and tiles of one face range (reset it at the range's start).
-// The origin phase is formed in binary64 at every kAnchor-th face of a tile (of kTileF32 faces).
-// Faces go in pairs that pass the carry between two register sets, so no copy
-// of it is needed from one face to the next. TC: each face's transcendental
-// instructions in one run (fwd_face_fp32c).
-template <int NQ, bool SHARE, bool CHECK, bool TC, class QL>
+// One LDS tile of FP32C face records against the NQ Q points of a thread (plain binary32 sums inside the tile).
+// SHARE: the records are in an edge-sharing order; `c` carries the shared edge's midpoint phase across faces and
+// tiles of one face range (reset it at the range's start). The origin phase is formed in binary64 at every
+// kAnchor-th face of a tile (of kTileF32 faces).
+template <int NQ, bool SHARE, bool CHECK, class QL>
 __device__ __forceinline__ void fwd_tile_fp32c(const Face32* tile, int nt, const float* qx, const float* qy,
-                                               const float* qz, const QL& ql,
-                                               const bool* small, float* tr, float* ti, FwdCarry<NQ>& c) {
-  FwdCarry<NQ> d;
-  int j = 0;
-  for (; j + 2 <= nt; j += 2) {
-    fwd_face_fp32c<NQ, SHARE, CHECK, TC>(tile[j], qx, qy, qz, ql, small, tr, ti, (j % kAnchor) == 0, c, d);
-    fwd_face_fp32c<NQ, SHARE, CHECK, TC>(tile[j + 1], qx, qy, qz, ql, small, tr, ti, false, d, c);
-  }
-  if (j < nt) {
-    fwd_face_fp32c<NQ, SHARE, CHECK, TC>(tile[j], qx, qy, qz, ql, small, tr, ti, (j % kAnchor) == 0, c, d);
-    c = d;
-  }
+                                               const float* qz, const QL& ql, float* tr, float* ti,
+                                               FwdCarry<NQ>& c) {
+  for (int j = 0; j < nt; ++j)
+    fwd_face_fp32c<NQ, SHARE, CHECK>(tile[j], qx, qy, qz, ql, tr, ti, (j % kAnchor) == 0, c);
 }
 
 __device__ __forceinline__ void kahan_add(float& sum, float& comp, float x) {

@@ -22,7 +22,7 @@ constexpr int kTileF = PFT_TILEF;  // faces staged in LDS per tile (binary64 for
 #define PFT_TILEF32 64
 #endif
 // faces per LDS tile of an FP32C forward wavefront (also the binary64 re-anchoring interval of its carried
-// phases); 6 KiB of records plus 2.25 KiB of Q low parts per wavefront, so the LDS holds more wavefronts
+// phases); 4 KiB of records plus 768 B of Q low parts per Q and wavefront, so the LDS holds more wavefronts
 // than the 5 per SIMD the registers allow
 constexpr int kTileF32 = PFT_TILEF32;
 constexpr int kTileFB = 8;         // faces per block in the binary64 adjoint
@@ -42,7 +42,10 @@ constexpr int kQPT = PFT_QPT;
 constexpr int kQPTLarge = PFT_QPT_LARGE;
 constexpr int64_t kFwdLargeNq = PFT_FWD_LARGE_NQ;
 inline int fwd_qpt(int64_t nq) { return nq >= kFwdLargeNq ? kQPTLarge : kQPT; }
-__host__ __device__ constexpr int fwd_waves(int qpt) { return qpt >= 3 ? 4 : 5; }  // waves per SIMD
+#ifndef PFT_FWD_WAVES
+#define PFT_FWD_WAVES (qpt >= 3 ? 4 : 5)
+#endif
+__host__ __device__ constexpr int fwd_waves(int qpt) { return PFT_FWD_WAVES; }  // waves per SIMD
 #ifndef PFT_FWD_BLOCK_WAVES
 #define PFT_FWD_BLOCK_WAVES 4
 #endif
@@ -78,7 +81,7 @@ constexpr int kTileE = 64;         // 2D edges staged in LDS per tile
 // |Q_perp| < tau_rel |Q| (relative test, guards the rounding of Q x N in FP32).
 constexpr double kTauF64 = 0.05;     // forward and adjoint, FP64 mode
 constexpr double kTauF32 = 0.1;      // forward, FP32C mode (series in FP64)
-constexpr double kTauRel32 = 0.02;   // forward, FP32C mode, relative test
+constexpr double kTauRel32 = 0.02;   // polygon forward, FP32C mode, relative test
 constexpr double kTauB32 = 1.5;      // (record field of the FP32C adjoint; empty-face flag)
 // The adjoint evaluates each face's barycentric moments by their series (binary64)
 // or by a polynomial of exp(ix) fitted on [-3, 3] (binary32, moment_poly.h) when the
@@ -142,35 +145,19 @@ struct alignas(16) Face64 {
 };
 static_assert(sizeof(Face64) == 128, "Face64 layout");
 
-// FP32C forward face record (staged in LDS). The in-plane geometry is held in
-// an orthonormal basis e1, e2 of the face plane (e1 along b - a, e2 = n x e1,
-// with a, b, c the vertices in the record's traversal order and n that order's
-// unit normal). With the half components sigma_j = Q . e_j / 2 of the in-plane
-// part of Q, and the edge coefficients al_l = (e1 . d_l)/(2 pi), be_l = -(e2 . d_l)/(2 pi):
-//   eta_l = Q . d_l / (4 pi) = sigma1 al_l - sigma2 be_l      (edge half-phase, turns)
-//   w'_l = sigma2 al_l + sigma1 be_l = (P . d_l) / (4 pi |N|)  (P = Q x N; the edge weight)
-//   |P|^2 / (4 |N|^2) = sigma1^2 + sigma2^2,   tau_rel (Q . n) / 2 = Q . N'  (N' = tau_rel N / (2 |N|)),
-// so tau_rel times the face term (Q.N)/|P|^2 sum_l (P.d_l) E_l equals (Q.N')/(sigma1^2 + sigma2^2)
-// sum_l w'_l E_l: the kernels sum that and divide by tau_rel once per partial sum. The factor tau_rel
-// (the relative series threshold) lets one fused multiply-add form the series test
-// |P'|^2 < (Q.N')^2 + thr, i.e. |Q_perp| < tau_rel |Q.n| or |Q_perp| L < tau.
-// In an edge-sharing order the traversal may be the reverse of the outward
-// (counter-clockwise) one, so that the edge shared with the next face is edge
-// 1: the edge sum is the same for both traversals (each edge's P . d and
-// sinc are unchanged when both the normal and the edge flip), and N' below
-// stays the outward normal, so the face term is unchanged.
+// FP32C forward face record (staged in LDS): what T = -i (Q.N) exp(iQ.g) J needs, J a function of the two
+// vertex phases p_0 = Q.u0, p_1 = Q.u1 (half-phases in turns). u0 and u1 belong to the first and second vertex
+// of the record's traversal. In an edge-sharing order the traversal may be the reverse of the outward
+// (counter-clockwise) one, so that the edge shared with the next face is edge 1: J is symmetric in the
+// vertices and N stays the outward normal, so the face term is the same for both traversals.
 struct alignas(16) Face32 {
-  double gt[3];   // centroid / (2 pi), binary64: face origin phase in turns is Q . gt
-  float N[3];     // N' = tau_rel N / (2 |N|), N the outward (b - a) x (c - a) of the counter-clockwise traversal
-  float E1[3];    // e1 / 2
-  float E2[3];    // e2 / 2
-  float al[3];    // (e1 . d_l) / (2 pi), l = 0, 1, 2 (d_0 = b - a, d_1 = c - b, d_2 = a - c)
-  float be[3];    // -(e2 . d_l) / (2 pi)
-  float thr;      // tau^2 / (4 L^2) (1 for an empty face: its series term is Q.N = 0 times a sum)
-  float nN;       // 2 |N|: the series branch takes tau_rel Q . N as nN (Q . N'), scaled like the edge terms
+  float N[3];     // N, the outward (b - a) x (c - a) of the counter-clockwise traversal
   uint32_t flags; // kFaceLinked: edge 0 is the previous record's edge 1 (edge-sharing order)
+  float u0[3];    // (a - g) / (4 pi)
+  float u1[3];    // (b - g) / (4 pi)
+  double gt[3];   // centroid / (2 pi), binary64: face origin phase in turns is Q . gt
 };
-static_assert(sizeof(Face32) == 96, "Face32 layout");
+static_assert(sizeof(Face32) == 64, "Face32 layout");
 constexpr uint32_t kFaceLinked = 1u;
 // Edge-sharing order metadata (pft_strip_order, one byte per position): the face's
 // vertex list rotated by (meta & 3), edge 0 shared with the previous position's
@@ -229,7 +216,7 @@ hipError_t launch_mesh_info_single(const void* verts, int vdtype, int dim, int64
 hipError_t launch_face64(const void* verts, int vdtype, int64_t nv, const int32_t* tris, int64_t nf,
                          MeshInfo* info, double tau, Face64* out, hipStream_t s,
                          const int32_t* order = nullptr, const uint8_t* meta = nullptr);
-hipError_t launch_face32(const Face64* f64, int64_t nf, double tau, double tau_rel, Face32* out, hipStream_t s);
+hipError_t launch_face32(const Face64* f64, int64_t nf, Face32* out, hipStream_t s);
 hipError_t launch_face32b(const Face64* f64, int64_t nf, double tau, double tau_rel, Face32B* out, hipStream_t s);
 hipError_t launch_face64_batch(const void* verts, int vdtype, const int32_t* tris, const int64_t* d_vert_off,
                                const int64_t* d_tri_off, const int32_t* d_face_mesh, int64_t nf_total,
@@ -334,8 +321,8 @@ struct FwdArgs {
   void* out;
   void* intensity;
   double tau0;
-  int share_edges = 0;  // FP32C: records are in edge-sharing order (Face32::link), reuse the shared edge's term
-  int qpt = kQPT;       // FP32C: Q per thread (kQPT or kQPTLarge, fwd_qpt), set with the splits
+  int share_edges = 0;  // FP32C: records are in edge-sharing order (Face32::flags), phases follow the shared edges
+  int qpt = kQPT;       // FP32C: Q per thread (1, kQPT or kQPTLarge), set with the splits
   // [splits] (x, y, z) the centre of the split's region relative to t, w its radius: the small-|Q| test of
   // a split uses that radius and its tetrahedron fan that apex (NULL: the mesh's R, apex t)
   const double4* split_geo = nullptr;

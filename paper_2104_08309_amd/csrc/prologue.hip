@@ -406,61 +406,23 @@ __global__ __launch_bounds__(256) void iota_u32_kernel(uint32_t* p, int64_t n) {
   if (i < n) p[i] = (uint32_t)i;
 }
 
-__global__ __launch_bounds__(256) void face32_kernel(const Face64* in, int64_t nf, double tau, double tau_rel,
-                                                     Face32* out) {
+__global__ __launch_bounds__(256) void face32_kernel(const Face64* in, int64_t nf, Face32* out) {
   const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (m >= nf) return;
   const Face64 f = in[m];
   Face32 r;
-  const double L2 = f.pad[0], N2 = f.pad[1];
   const bool ok = f.thr >= 0.0;
   const int code = (int)f.pad[2];
-  // linked only to a non-empty predecessor (an empty record carries no edge term)
-  const bool link = ok && (code & 1) && m > 0 && in[m - 1].thr >= 0.0;
-  const bool refl = (code & 2) != 0;
-  // traversal order (a, b, c), or (b, a, c) reversed; the normal of the traversal
-  double u0[3], u1[3], Nt[3], d0[3], d1[3], e1[3], e2[3];
+  const bool refl = (code & 2) != 0;  // traversal (b, a, c) instead of (a, b, c)
   for (int k = 0; k < 3; ++k) {
-    u0[k] = refl ? f.u1[k] : f.u0[k];
-    u1[k] = refl ? f.u0[k] : f.u1[k];
-    Nt[k] = refl ? -f.N[k] : f.N[k];
-    d0[k] = u1[k] - u0[k];
-    d1[k] = -u0[k] - 2.0 * u1[k];
+    r.gt[k] = f.g[k] * kInv2Pi;
+    // an empty face has N = 0 and phases 0: its term is Q.N = 0 times a finite J
+    r.N[k] = ok ? (float)f.N[k] : 0.0f;
+    r.u0[k] = ok ? (float)((refl ? f.u1[k] : f.u0[k]) * kInv4Pi) : 0.0f;
+    r.u1[k] = ok ? (float)((refl ? f.u0[k] : f.u1[k]) * kInv4Pi) : 0.0f;
   }
-  for (int k = 0; k < 3; ++k) r.gt[k] = f.g[k] * kInv2Pi;
-  auto dot = [](const double* x, const double* y) { return x[0] * y[0] + x[1] * y[1] + x[2] * y[2]; };
-  const double nN = sqrt(N2), nd0 = sqrt(dot(d0, d0));
-  if (ok && nd0 > 0.0) {
-    double d2[3];
-    for (int k = 0; k < 3; ++k) {
-      e1[k] = d0[k] / nd0;
-      d2[k] = -d0[k] - d1[k];
-    }
-    // e2 = n x e1 = (N x d0) / (|N| |d0|), with the traversal's normal
-    e2[0] = (Nt[1] * d0[2] - Nt[2] * d0[1]) / (nN * nd0);
-    e2[1] = (Nt[2] * d0[0] - Nt[0] * d0[2]) / (nN * nd0);
-    e2[2] = (Nt[0] * d0[1] - Nt[1] * d0[0]) / (nN * nd0);
-    for (int k = 0; k < 3; ++k) {
-      r.N[k] = (float)(0.5 * tau_rel * f.N[k] / nN);
-      r.E1[k] = (float)(0.5 * e1[k]);
-      r.E2[k] = (float)(0.5 * e2[k]);
-    }
-    const double* d[3] = {d0, d1, d2};
-    for (int l = 0; l < 3; ++l) {
-      r.al[l] = (float)(dot(e1, d[l]) * kInv2Pi);
-      r.be[l] = (float)(-dot(e2, d[l]) * kInv2Pi);
-    }
-    r.thr = (float)(0.25 * tau * tau / L2);
-    r.nN = (float)(2.0 * nN);
-    r.flags = link ? kFaceLinked : 0u;
-  } else {
-    // empty face: every weight is zero; thr > 0 sends every pair to the series, whose term is
-    // Q.N = 0 times a finite sum, so its contribution is exactly zero (the edge form would be 0/0)
-    for (int k = 0; k < 3; ++k) r.N[k] = r.E1[k] = r.E2[k] = r.al[k] = r.be[k] = 0.0f;
-    r.thr = 1.0f;
-    r.nN = 0.0f;
-    r.flags = 0u;
-  }
+  // linked only to a non-empty predecessor (an empty record carries no edge)
+  r.flags = ok && (code & 1) && m > 0 && in[m - 1].thr >= 0.0 ? kFaceLinked : 0u;
   out[m] = r;
 }
 
@@ -577,9 +539,9 @@ hipError_t launch_poly_records32(const FaceP64* f64, const VtxP64* v64, int64_t 
   return hipGetLastError();
 }
 
-hipError_t launch_face32(const Face64* f64, int64_t nf, double tau, double tau_rel, Face32* out, hipStream_t s) {
+hipError_t launch_face32(const Face64* f64, int64_t nf, Face32* out, hipStream_t s) {
   if (nf <= 0) return hipSuccess;
-  face32_kernel<<<grid_for(nf), 256, 0, s>>>(f64, nf, tau, tau_rel, out);
+  face32_kernel<<<grid_for(nf), 256, 0, s>>>(f64, nf, out);
   return hipGetLastError();
 }
 
