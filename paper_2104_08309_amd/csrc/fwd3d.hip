@@ -264,22 +264,19 @@ hipError_t launch_fwd3d_fp64(const FwdArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_fwd3d_fp32c(const FwdArgs& a, hipStream_t s) {
-  if (a.qpt != kQPT && a.qpt != kQPTLarge) return hipErrorInvalidValue;
   const int64_t qtiles = (a.nq + fwd_qtile(a.qpt) - 1) / fwd_qtile(a.qpt);
   const int64_t blocks = (qtiles + kXcds - 1) / kXcds * kXcds * a.splits;
   if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-  const bool large = a.qpt == kQPTLarge && kQPTLarge != kQPT;
-  if (a.share_edges) {
-    if (large)
-      fwd3d_fp32c_kernel<true, kQPTLarge><<<(unsigned)blocks, kFwdBlock, 0, s>>>(a);
-    else
-      fwd3d_fp32c_kernel<true, kQPT><<<(unsigned)blocks, kFwdBlock, 0, s>>>(a);
-  } else {
-    if (large)
-      fwd3d_fp32c_kernel<false, kQPTLarge><<<(unsigned)blocks, kFwdBlock, 0, s>>>(a);
-    else
-      fwd3d_fp32c_kernel<false, kQPT><<<(unsigned)blocks, kFwdBlock, 0, s>>>(a);
-  }
+#define PFT_FWD3D(SH, QP) fwd3d_fp32c_kernel<SH, QP><<<(unsigned)blocks, kFwdBlock, 0, s>>>(a)
+  if (a.qpt == 1)
+    a.share_edges ? PFT_FWD3D(true, 1) : PFT_FWD3D(false, 1);
+  else if (a.qpt == kQPT)
+    a.share_edges ? PFT_FWD3D(true, kQPT) : PFT_FWD3D(false, kQPT);
+  else if (a.qpt == kQPTLarge)
+    a.share_edges ? PFT_FWD3D(true, kQPTLarge) : PFT_FWD3D(false, kQPTLarge);
+  else
+    return hipErrorInvalidValue;
+#undef PFT_FWD3D
   return hipGetLastError();
 }
 
