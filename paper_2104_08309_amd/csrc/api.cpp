@@ -298,7 +298,7 @@ void choose_face_splits(int64_t nq, int64_t nf, int64_t qtile, int64_t min_faces
   *splits = (int)cdiv(nf, p);
 }
 
-// How a forward of nq Q and nf faces is cut: Q per thread (FP32C), least faces per split and target blocks.
+// How a forward of nq Q and nf faces is cut: Q per thread, least faces per split and target blocks.
 // A call whose blocks of at least kMinFacesPerSplit faces per wavefront would leave most of the chip idle is
 // cut finer, down to one tile of kTileF faces per block and, if that does not give kSmallBlocks blocks either,
 // one Q per thread: such a call is bound by the latency of its longest wavefront, not by issue. 320 faces x
@@ -309,8 +309,7 @@ struct FwdPlan {
   int64_t qtile, min_faces, target;
 };
 FwdPlan fwd_plan(int64_t nq, int64_t nf, bool c128) {
-  if (c128) return {kQPT, kBlock, kMinFacesPerSplit, kTargetBlocks};
-  FwdPlan p{fwd_qpt(nq), 0, kMinFacesPerSplit * kFwdSplitWaves, kTargetBlocksF32};
+  FwdPlan p{c128 ? kQPT64 : fwd_qpt(nq), 0, kMinFacesPerSplit * kFwdSplitWaves, c128 ? kTargetBlocks : kTargetBlocksF32};
   if (cdiv(nq, fwd_qtile(p.qpt)) * cdiv(nf, p.min_faces) < kSmallBlocks) {
     p.min_faces = kTileF;
     p.target = kSmallBlocks;

@@ -70,6 +70,7 @@ __global__ __launch_bounds__(kBlock) void batch_fwd_fp64_kernel(const BatchGroup
     if (active) load_q3(q, qdtype, perm ? (int64_t)perm[it.q0 + lane] : it.q0 + lane, Qd);
     const double Q2d = Qd[0] * Qd[0] + Qd[1] * Qd[1] + Qd[2] * Qd[2];
     const bool small = sqrt(Q2d) * R < tau0;
+    const bool big = big_phases64(Q2d, R);
     double xr = 0.0, xi = 0.0;
     for (int64_t t0 = it.f0; t0 < f_end; t0 += kTileF) {
       const int nt = (int)min((int64_t)kTileF, f_end - t0);
@@ -78,12 +79,7 @@ __global__ __launch_bounds__(kBlock) void batch_fwd_fp64_kernel(const BatchGroup
         reinterpret_cast<uint4*>(tile)[i] = reinterpret_cast<const uint4*>(f64 + t0)[i];
       __syncthreads();
       if (!small) {
-        for (int j = 0; j < nt; ++j) {
-          double Tr, Ti;
-          face_term_f64(tile[j], Qd, Tr, Ti);
-          xr += Tr;
-          xi += Ti;
-        }
+        for (int j = 0; j < nt; ++j) fwd_face_f64<1>(tile[j], &Qd, big, &xr, &xi);
       } else {
         for (int j = 0; j < nt; ++j) tet_term_f64(tile[j], Qd, xr, xi, kZeroOrigin);
       }

@@ -1,0 +1,94 @@
+// Face integral and barycentric moments of a triangle from its centred vertex phases through the fitted
+// symmetric polynomials (face_poly.h), and the binary64 sine / cosine they are combined with.
+//
+// With d_0 + d_1 + d_2 = 0, p = d_0^2 + d_0 d_1 + d_1^2, E = d_0 d_1 (d_0 + d_1), w = E^2:
+//   J = A + i E B,   Y_k = alpha + beta d_k + gamma d_k^2,   beta = i bi + E br,   gamma = gr + i E gi,
+//   alpha = (J - 2 p gamma) / 3,
+// A, B, bi, br, gr, gi polynomials in (p, w). Valid for max |d_k| <= FaceFit64::M / FaceFit32::M.
+#pragma once
+
+#include "face_poly.h"
+#include "pft_device.h"
+
+namespace pft {
+
+// The binary64 coefficients in constant memory. A binary64 instruction takes no 64-bit literal, and the coefficients
+// of a face term (54 in the forward, 110 in the adjoint) fit neither register file, so each face reads them through
+// the scalar cache: fit64() once per face, whose empty asm keeps the loads inside the face loop (hoisted out of it
+// they spilled 86 vector registers). A scalar source costs a binary64 instruction nothing.
+__constant__ const double kFit64Row[] = {PFT_FIT64_ROW};
+using Fit64 = const __attribute__((address_space(4))) double*;
+__device__ __forceinline__ Fit64 fit64() {
+  Fit64 t = (Fit64)kFit64Row;
+  asm volatile("" : "+s"(t));
+  return t;
+}
+
+// a * b + c with c in scalar registers. (The compiler's own choice, v_fmac_f64, first copies the coefficient into the
+// destination with two v_mov_b32: 1.3 times the instructions of a Horner sum.)
+__device__ __forceinline__ double fma64s(double a, double b, double c) {
+  double r;
+  asm("v_fma_f64 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "s"(c));
+  return r;
+}
+
+// sum_a C::c[a] x^a, binary64.
+template <class C>
+__device__ __forceinline__ double horner64(Fit64 t, double x) {
+  constexpr int N = sizeof(C::c) / sizeof(C::c[0]);
+  double s = t[C::at + N - 1];
+#pragma unroll
+  for (int a = N - 2; a >= 0; --a) s = fma64s(s, x, t[C::at + a]);
+  return s;
+}
+
+// sin x and cos x for |x| <= kSinCosMax64: x reduced by the nearest multiple n of pi/2 (pi/2 as a double plus its
+// remainder, both products exact in the fused multiply-add: the reduced argument carries one rounding), polynomials
+// on [-pi/4, pi/4]. Beyond, n times pi/2's second remainder would be felt: the callers take the library function
+// there (sincos_any64), which costs twice the instructions everywhere.
+constexpr double kSinCosMax64 = 268435456.0;  // 2^28
+__device__ __forceinline__ void sincos64(Fit64 t, double x, double* s, double* c) {
+  const double n = rint(x * 0.63661977236758134308);
+  double r = fma(-n, 1.5707963267948965580, x);
+  r = fma(-n, 6.123233995736766036e-17, r);
+  const double z = r * r;
+  const double sr = r + r * z * horner64<SinCos64::S>(t, z);
+  const double cr = 1.0 + z * (z * horner64<SinCos64::C>(t, z) - 0.5);
+  const int q = (int)n;
+  const double a = (q & 1) ? cr : sr, b = (q & 1) ? sr : cr;
+  *s = (q & 2) ? -a : a;
+  *c = ((q + 1) & 2) ? -b : b;
+}
+__device__ __forceinline__ void sincos_any64(Fit64 t, double x, double* s, double* c) {
+  if (__builtin_expect(!(fabs(x) <= kSinCosMax64), 0))
+    sincos(x, s, c);
+  else
+    sincos64(t, x, s, c);
+}
+
+// 1 / x to about one unit in the last place (x finite, not 0): two Newton steps from the hardware estimate.
+__device__ __forceinline__ double recip64(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = r + r * (1.0 - x * r);
+  return r + r * (1.0 - x * r);
+}
+
+// J, binary64, max |d_k| <= FaceFit64::M.
+__device__ __forceinline__ void face_integral_fit64(Fit64 t, double d0, double d1, double& jr, double& ji) {
+  const double s = d0 + d1;
+  const double p = d0 * s + d1 * d1, E = d0 * d1 * s, w = E * E;
+  jr = ((horner64<FaceFit64::A3>(t, p) * w + horner64<FaceFit64::A2>(t, p)) * w + horner64<FaceFit64::A1>(t, p)) * w +
+       horner64<FaceFit64::A0>(t, p);
+  ji = E * ((horner64<FaceFit64::B2>(t, p) * w + horner64<FaceFit64::B1>(t, p)) * w + horner64<FaceFit64::B0>(t, p));
+}
+
+// beta and gamma's parts: beta = i bi + E br, gamma = gr + i E gi.
+__device__ __forceinline__ void face_beta_gamma64(Fit64 t, double p, double w, double& bi, double& br, double& gr, double& gi) {
+  bi = ((horner64<FaceFit64::bi3>(t, p) * w + horner64<FaceFit64::bi2>(t, p)) * w + horner64<FaceFit64::bi1>(t, p)) * w +
+       horner64<FaceFit64::bi0>(t, p);
+  br = (horner64<FaceFit64::br2>(t, p) * w + horner64<FaceFit64::br1>(t, p)) * w + horner64<FaceFit64::br0>(t, p);
+  gr = (horner64<FaceFit64::gr2>(t, p) * w + horner64<FaceFit64::gr1>(t, p)) * w + horner64<FaceFit64::gr0>(t, p);
+  gi = (horner64<FaceFit64::gi2>(t, p) * w + horner64<FaceFit64::gi1>(t, p)) * w + horner64<FaceFit64::gi0>(t, p);
+}
+
+}  // namespace pft

@@ -1,13 +1,11 @@
 // Forward 3D transform of a closed triangle mesh: F(Q) for a list of Q.
 //
-// Layout: Q-tiles of threads (binary64: one Q per thread; FP32C: QPT Q per
-// thread, each wavefront of a block on its own share of the faces), faces
-// streamed through LDS in tiles of kTileF records and broadcast to the
+// Layout: Q-tiles of QPT Q per thread, each wavefront of a block on its own
+// share of the faces, faces streamed through LDS tiles and broadcast to the
 // wavefront. Each block's sums over its face range are binary64 partials; the
 // finish kernel adds a Q's partials in a fixed order and applies
 // exp(i Q.t) / |Q|^2. The faces are split when there are too few Q to fill
-// the GPU (over blockIdx.y in binary64; in FP32C the split is part of the
-// one-dimensional block index).
+// the GPU (the split is part of the one-dimensional block index).
 //
 // Two arithmetic forms:
 //  * fwd3d_fp64_kernel  -- IEEE binary64 throughout.
@@ -43,52 +41,113 @@ __device__ __forceinline__ void split_faces(const FwdArgs& a, int64_t sp, int64_
   }
 }
 
-__global__ __launch_bounds__(kBlock) void fwd3d_fp64_kernel(FwdArgs a) {
-  __shared__ Face64 tile[kTileF];
-  const int64_t qi = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const bool active = qi < a.nq;
-  double Q[3] = {0.0, 0.0, 0.0};
-  if (active) load_q3(a.q, a.qdtype, a.perm ? (int64_t)a.perm[qi] : qi, Q);
-  const double Q2 = Q[0] * Q[0] + Q[1] * Q[1] + Q[2] * Q[2];
+// (Q-tile, split) of a forward block. The grid is one-dimensional and its blocks go to the dies in turn (block b
+// to die b mod kXcds), so the block index is read as (die, rank on the die) and the k-th group of `splits` blocks a
+// die receives holds every split of one Q-tile: a Q-tile's Q and permutation entries are fetched into that die's L2
+// once and served from there to its other splits (the Q-tile count is padded to a multiple of kXcds; the padding
+// blocks exit at once).
+__device__ __forceinline__ void fwd_block(const FwdArgs& a, uint32_t& qtile, uint32_t& sp) {
+  const uint32_t rank = blockIdx.x / kXcds;
+  qtile = blockIdx.x % kXcds + kXcds * (rank / (uint32_t)a.splits);
+  sp = rank % (uint32_t)a.splits;
+}
+
+// The last of a block's wavefronts to come here returns true, with the others' LDS writes visible.
+__device__ __forceinline__ bool last_wave(uint32_t* done) {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+  int last = 0;
+  if ((threadIdx.x & 63) == 0) last = atomicAdd(done, 1u) == (uint32_t)(kFwdSplitWaves - 1) ? 1 : 0;
+  if (__builtin_amdgcn_readfirstlane(last) == 0) return false;
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  return true;
+}
+
+// The binary64 forward, in the FP32C forward's layout (below): QPT Q per lane, each wavefront of a block on its own
+// quarter of the split's faces through its own LDS tile. Bound by binary64 issue: about 95 binary64 instructions
+// per pair (two Horner sums of 42 coefficients, one sine and cosine) against some 290 with the edge terms'
+// library sines and divisions (5 120 faces x 64 000 Q: kernel 3.3 -> 1.35 ms under the profiler). QPT = 2: a record
+// read from LDS (96 B) and a coefficient read through the scalar cache serve two pairs (1 and 4 Q per lane: 1 % and
+// -0.6 % on the fitting step; 3: 3 %).
+template <int QPT>
+__global__ __launch_bounds__(kFwdBlock, kFwdWaves64) void fwd3d_fp64_kernel(FwdArgs a) {
+  constexpr int kQT = fwd_qtile(QPT);
+  __shared__ Face64 tiles[kFwdSplitWaves][kTileF64];
+  __shared__ uint32_t done;
+  static_assert(sizeof(Face64) * kTileF64 >= sizeof(double2) * QPT * 64, "a wavefront's partials fit its tile");
+  uint32_t qtile, sp;
+  fwd_block(a, qtile, sp);
+  if ((int64_t)qtile * kQT >= a.nq) return;  // padding of the Q-tile count (whole block)
+  if (threadIdx.x == 0) done = 0u;
+  __syncthreads();
+  const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = (int)(threadIdx.x & 63);
+  Face64* tile = tiles[w];
   // the split's region (centre o relative to t, radius) when the splits follow regions, else the mesh
-  const double4 geo = a.split_geo ? a.split_geo[blockIdx.y] : make_double4(0.0, 0.0, 0.0, a.info[0].R);
-  const double o[3] = {geo.x, geo.y, geo.z};
-  const bool small = sqrt(Q2) * geo.w < a.tau0;
+  const double4 geo = a.split_geo ? a.split_geo[sp] : make_double4(0.0, 0.0, 0.0, a.info[0].R);
   int64_t f_begin, f_end;
-  split_faces(a, blockIdx.y, f_begin, f_end);
-  double xr = 0.0, xi = 0.0;
-  for (int64_t t0 = f_begin; t0 < f_end; t0 += kTileF) {
-    const int nt = (int)min((int64_t)kTileF, f_end - t0);
-    __syncthreads();
+  split_faces(a, sp, f_begin, f_end);
+  {  // this wavefront's share
+    const int64_t per = (f_end - f_begin + kFwdSplitWaves - 1) / kFwdSplitWaves;
+    const int64_t b = min(f_end, f_begin + w * per);
+    f_end = min(f_end, b + per);
+    f_begin = b;
+  }
+  double Q[QPT][3], xr[QPT], xi[QPT];
+  bool small[QPT];
+  bool any_small = false, big = false;
+#pragma unroll
+  for (int k = 0; k < QPT; ++k) {
+    const int64_t qi = (int64_t)qtile * kQT + k * 64 + lane;
+    Q[k][0] = Q[k][1] = Q[k][2] = 0.0;
+    if (qi < a.nq) load_q3(a.q, a.qdtype, a.perm ? (int64_t)a.perm[qi] : qi, Q[k]);
+    const double Q2 = Q[k][0] * Q[k][0] + Q[k][1] * Q[k][1] + Q[k][2] * Q[k][2];
+    small[k] = sqrt(Q2) * geo.w < a.tau0;
+    any_small |= small[k];
+    big |= big_phases64(Q2, a.info[0].R);
+    xr[k] = xi[k] = 0.0;
+  }
+  for (int64_t t0 = f_begin; t0 < f_end; t0 += kTileF64) {
+    const int nt = (int)min((int64_t)kTileF64, f_end - t0);
+    wave_lds_fence();
     {
       const uint4* src = reinterpret_cast<const uint4*>(a.f64 + t0);
       uint4* dst = reinterpret_cast<uint4*>(tile);
-      for (int i = threadIdx.x; i < nt * (int)(sizeof(Face64) / 16); i += kBlock) dst[i] = src[i];
+      for (int i = lane; i < nt * (int)(sizeof(Face64) / 16); i += 64) dst[i] = src[i];
     }
-    __syncthreads();
-    if (!small) {
-      for (int j = 0; j < nt; ++j) {
-        double Tr, Ti;
-        face_term_f64(tile[j], Q, Tr, Ti);
-        xr += Tr;
-        xi += Ti;
-      }
-    } else {
-      for (int j = 0; j < nt; ++j) tet_term_f64(tile[j], Q, xr, xi, o);
-    }
+    wave_lds_fence();
+    for (int j = 0; j < nt; ++j) fwd_face_f64<QPT>(tile[j], Q, big, xr, xi);
   }
-  if (small && a.split_geo) apex_phase(Q, o, xr, xi);
-  if (active) store_stream(a.partial + (int64_t)blockIdx.y * a.nq + qi, make_double2(xr, xi));
+  if (any_small) {  // small-|Q| lanes: the tetrahedron fan about the apex instead
+    const double o[3] = {geo.x, geo.y, geo.z};
+#pragma unroll
+    for (int k = 0; k < QPT; ++k)
+      if (small[k]) {
+        xr[k] = xi[k] = 0.0;
+        for (int64_t j = f_begin; j < f_end; ++j) tet_term_f64(a.f64[j], Q[k], xr[k], xi[k], o);
+        if (a.split_geo) apex_phase(Q[k], o, xr[k], xi[k]);
+      }
+  }
+  // this wavefront's partials into its own tile (it reads no more records)
+  wave_lds_fence();
+  double2* red = reinterpret_cast<double2*>(tiles[w]);
+#pragma unroll
+  for (int k = 0; k < QPT; ++k) red[k * 64 + lane] = make_double2(xr[k], xi[k]);
+  if (!last_wave(&done)) return;
+#pragma unroll
+  for (int k = 0; k < QPT; ++k) {
+    const int64_t qi = (int64_t)qtile * kQT + k * 64 + lane;
+    double2 v = reinterpret_cast<const double2*>(tiles[0])[k * 64 + lane];
+    for (int u = 1; u < kFwdSplitWaves; ++u) {
+      const double2 x = reinterpret_cast<const double2*>(tiles[u])[k * 64 + lane];
+      v.x += x.x;
+      v.y += x.y;
+    }
+    if (qi < a.nq) store_stream(a.partial + (int64_t)sp * a.nq + qi, v);
+  }
 }
 
 // The FP32C forward. A block holds one Q-tile of kQT = 64 QPT Q, the same in each of its
 // kFwdSplitWaves wavefronts (lane l holds the tile's Q l, l + 64, ...; QPT per thread, so each face
-// record read from LDS serves QPT independent instruction streams), and one face split. The grid is
-// one-dimensional and its blocks go to the dies in turn (block b to die b mod kXcds), so the block
-// index is read as (die, rank on the die) and the k-th group of `splits` blocks a die receives holds
-// every split of one Q-tile: a Q-tile's Q and permutation entries are fetched into that die's L2 once
-// and served from there to its other splits (the Q-tile count is padded to a multiple of kXcds; the
-// padding blocks exit at once).
+// record read from LDS serves QPT independent instruction streams), and one face split (fwd_block).
 // Each wavefront takes its own contiguous share of the split's faces and streams them through its own
 // LDS tile of kTileF32 records, with wavefront-local ordering only: no block barrier after the start.
 // A wavefront that is done leaves its binary64 partials in its own tile and counts itself done; the
@@ -104,10 +163,8 @@ __global__ __launch_bounds__(kFwdBlock, fwd_waves(QPT)) void fwd3d_fp32c_kernel(
   __shared__ float qlo[kFwdSplitWaves][3 * QPT * 64];
   __shared__ uint32_t done;  // wavefronts of the block that have left their partials
   static_assert(sizeof(Face32) * kTileF32 >= sizeof(double2) * QPT * 64, "a wavefront's partials fit its tile");
-  // (Q-tile, split) of this block from its die and rank on the die
-  const uint32_t rank = blockIdx.x / kXcds;
-  const uint32_t qtile = blockIdx.x % kXcds + kXcds * (rank / (uint32_t)a.splits);
-  const uint32_t sp = rank % (uint32_t)a.splits;
+  uint32_t qtile, sp;
+  fwd_block(a, qtile, sp);
   if ((int64_t)qtile * kQT >= a.nq) return;  // padding of the Q-tile count (whole block)
   if (threadIdx.x == 0) done = 0u;
   __syncthreads();
@@ -204,11 +261,7 @@ __global__ __launch_bounds__(kFwdBlock, fwd_waves(QPT)) void fwd3d_fp32c_kernel(
                                   : make_double2((double)sr[k] - (double)cr[k],
                                                  (double)si[k] - (double)ci[k]);
   // count this wavefront done once its partials are visible to the block; the last one adds them all
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-  int last = 0;
-  if (lane == 0) last = atomicAdd(&done, 1u) == (uint32_t)(kFwdSplitWaves - 1) ? 1 : 0;
-  if (__builtin_amdgcn_readfirstlane(last) == 0) return;
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+  if (!last_wave(&done)) return;
   // the lane index anew (from the lane mask, not threadIdx), so no Q index is kept live across the loop
   const int l = (int)__lane_id();
 #pragma unroll
@@ -257,17 +310,30 @@ __global__ __launch_bounds__(256) void fwd3d_finish_kernel(FwdArgs a, int out_c1
 
 }  // namespace
 
+static hipError_t fwd_grid(const FwdArgs& a, unsigned* blocks) {
+  const int64_t qtiles = (a.nq + fwd_qtile(a.qpt) - 1) / fwd_qtile(a.qpt);
+  const int64_t n = (qtiles + kXcds - 1) / kXcds * kXcds * a.splits;
+  if (n > 0x7fffffff) return hipErrorInvalidConfiguration;
+  *blocks = (unsigned)n;
+  return hipSuccess;
+}
+
 hipError_t launch_fwd3d_fp64(const FwdArgs& a, hipStream_t s) {
-  dim3 grid((unsigned)((a.nq + kBlock - 1) / kBlock), (unsigned)a.splits);
-  fwd3d_fp64_kernel<<<grid, kBlock, 0, s>>>(a);
+  unsigned blocks = 0;
+  if (hipError_t e = fwd_grid(a, &blocks)) return e;
+  if (a.qpt == 1)
+    fwd3d_fp64_kernel<1><<<blocks, kFwdBlock, 0, s>>>(a);
+  else if (a.qpt == kQPT64)
+    fwd3d_fp64_kernel<kQPT64><<<blocks, kFwdBlock, 0, s>>>(a);
+  else
+    return hipErrorInvalidValue;
   return hipGetLastError();
 }
 
 hipError_t launch_fwd3d_fp32c(const FwdArgs& a, hipStream_t s) {
-  const int64_t qtiles = (a.nq + fwd_qtile(a.qpt) - 1) / fwd_qtile(a.qpt);
-  const int64_t blocks = (qtiles + kXcds - 1) / kXcds * kXcds * a.splits;
-  if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-#define PFT_FWD3D(SH, QP) fwd3d_fp32c_kernel<SH, QP><<<(unsigned)blocks, kFwdBlock, 0, s>>>(a)
+  unsigned blocks = 0;
+  if (hipError_t e = fwd_grid(a, &blocks)) return e;
+#define PFT_FWD3D(SH, QP) fwd3d_fp32c_kernel<SH, QP><<<blocks, kFwdBlock, 0, s>>>(a)
   if (a.qpt == 1)
     a.share_edges ? PFT_FWD3D(true, 1) : PFT_FWD3D(false, 1);
   else if (a.qpt == kQPT)

@@ -2,7 +2,7 @@
 // forms, shared by the single-mesh and batched kernels (formulas in pft_device.h).
 #pragma once
 
-#include "face_poly.h"
+#include "face_moments.h"
 #include "moment_poly.h"
 #include "pft_device.h"
 
@@ -21,47 +21,68 @@ PFT_HD __forceinline__ double sinc_f64(double x, double sinx) {
   return sinx / x;
 }
 
-PFT_HD __forceinline__ void face_term_f64(const Face64& f, const double* Q, double& Tr, double& Ti) {
-  const double QN = Q[0] * f.N[0] + Q[1] * f.N[1] + Q[2] * f.N[2];
-  const double Px = Q[1] * f.N[2] - Q[2] * f.N[1];
-  const double Py = Q[2] * f.N[0] - Q[0] * f.N[2];
-  const double Pz = Q[0] * f.N[1] - Q[1] * f.N[0];
-  const double P2 = Px * Px + Py * Py + Pz * Pz;
-  const double phi = Q[0] * f.g[0] + Q[1] * f.g[1] + Q[2] * f.g[2];
-  double sf, cf;
-  sincos(phi, &sf, &cf);
-  const double q0 = Q[0] * f.u0[0] + Q[1] * f.u0[1] + Q[2] * f.u0[2];  // delta_0 = 2 psi_0
-  const double q1 = Q[0] * f.u1[0] + Q[1] * f.u1[1] + Q[2] * f.u1[2];
-  if (P2 < f.thr) {
-    double sr, si;
-    face_series_f64(q0, q1, -q0 - q1, sr, si, 1e-17);
-    // T = -i (Q.N) exp(i phi) s
-    Tr = QN * (cf * si + sf * sr);
-    Ti = -QN * (cf * sr - sf * si);
-    return;
-  }
-  const double p0 = 0.5 * q0, p1 = 0.5 * q1, p2 = -p0 - p1;
+// J beyond the fitted range by the edge terms (as the FP32C form below): J = i / (2 p) sum_k d_k
+// sinc((d_{k+1} - d_{k+2}) / 2) exp(-i d_k / 2).
+__device__ __forceinline__ void face_integral_far64(Fit64 t, double d0, double d1, double& jr, double& ji) {
+  const double s = d0 + d1;
   double s0, c0, s1, c1;
-  sincos(p0, &s0, &c0);
-  sincos(p1, &s1, &c1);
-  const double c2 = c0 * c1 - s0 * s1;      // exp(i psi_2) = conj(exp(i psi_0) exp(i psi_1))
-  const double s2 = -(s0 * c1 + c0 * s1);
-  // w_l = P.d_l = pi_{l+1} - pi_l with pi_k = P.u_k
-  const double pi0 = Px * f.u0[0] + Py * f.u0[1] + Pz * f.u0[2];
-  const double pi1 = Px * f.u1[0] + Py * f.u1[1] + Pz * f.u1[2];
-  const double pi2 = -pi0 - pi1;
-  const double w0 = pi1 - pi0, w1 = pi2 - pi1, w2 = pi0 - pi2;
-  // sinc(eta_l), eta_l = psi_{l+1} - psi_l, sin(eta_l) = Im(exp(i psi_{l+1}) exp(-i psi_l))
-  const double a0 = w0 * sinc_f64(p1 - p0, s1 * c0 - c1 * s0);
-  const double a1 = w1 * sinc_f64(p2 - p1, s2 * c1 - c2 * s1);
-  const double a2 = w2 * sinc_f64(p0 - p2, s0 * c2 - c0 * s2);
-  // edge l carries exp(-i psi_{l+2})
-  const double Sr = a0 * c2 + a1 * c0 + a2 * c1;
-  const double Si = -(a0 * s2 + a1 * s0 + a2 * s1);
-  const double co = QN / fmax(P2, 1e-300);
-  const double Ur = co * cf, Ui = co * sf;
-  Tr = Ur * Sr - Ui * Si;
-  Ti = Ur * Si + Ui * Sr;
+  sincos_any64(t, 0.5 * d0, &s0, &c0);
+  sincos_any64(t, 0.5 * d1, &s1, &c1);
+  // exp(i d_2 / 2) = conj(exp(i d_0 / 2) exp(i d_1 / 2))
+  const double c2 = c0 * c1 - s0 * s1, s2 = -(s0 * c1 + c0 * s1);
+  // d_k times the sinc of the edge opposite vertex k
+  const double a0 = d0 * sinc_f64(0.5 * (s + d1), s1 * c2 - c1 * s2);
+  const double a1 = d1 * sinc_f64(-0.5 * (s + d0), s2 * c0 - c2 * s0);
+  const double a2 = -s * sinc_f64(0.5 * (d0 - d1), s0 * c1 - c0 * s1);
+  const double h = 0.5 / (d0 * s + d1 * d1);
+  jr = h * (a0 * s0 + a1 * s1 + a2 * s2);
+  ji = h * (a0 * c0 + a1 * c1 + a2 * c2);
+}
+
+// One face against a thread's NQ Q points, binary64: adds T = -i (Q.N) exp(iQ.g) J to xr, xi. J by the fitted
+// polynomials where the largest centred vertex phase is at most FaceFit64::M (no quotient, nothing cancels near the
+// face normal), by the edge terms beyond; the choice is per lane. An empty record (N = 0, phases 0) gives 0. big
+// (wavefront-uniform): some origin phase may exceed kSinCosMax64.
+template <int NQ>
+__device__ __forceinline__ void fwd_face_f64(const Face64& f, const double (*Q)[3], bool big, double* xr, double* xi) {
+  const Fit64 t = fit64();
+  double d0[NQ], d1[NQ], jr[NQ], ji[NQ];
+  bool far[NQ];
+  bool any = false;
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    d0[k] = Q[k][0] * f.u0[0] + Q[k][1] * f.u0[1] + Q[k][2] * f.u0[2];
+    d1[k] = Q[k][0] * f.u1[0] + Q[k][1] * f.u1[1] + Q[k][2] * f.u1[2];
+    face_integral_fit64(t, d0[k], d1[k], jr[k], ji[k]);
+    far[k] = fmax(fabs(d0[k]), fmax(fabs(d1[k]), fabs(d0[k] + d1[k]))) > FaceFit64::M;
+    any |= far[k];
+  }
+  if (any) {
+#pragma unroll
+    for (int k = 0; k < NQ; ++k)
+      if (far[k]) face_integral_far64(t, d0[k], d1[k], jr[k], ji[k]);
+  }
+  double sf[NQ], cf[NQ];
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    const double phi = Q[k][0] * f.g[0] + Q[k][1] * f.g[1] + Q[k][2] * f.g[2];
+    if (__builtin_expect(big, 0))
+      sincos_any64(t, phi, &sf[k], &cf[k]);
+    else
+      sincos64(t, phi, &sf[k], &cf[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < NQ; ++k) {
+    const double QN = Q[k][0] * f.N[0] + Q[k][1] * f.N[1] + Q[k][2] * f.N[2];
+    xr[k] += QN * (cf[k] * ji[k] + sf[k] * jr[k]);
+    xi[k] += QN * (sf[k] * ji[k] - cf[k] * jr[k]);
+  }
+}
+
+// Whether an origin phase Q.g of a wavefront can exceed the range of sincos64: |g| <= R, the mesh's radius (qmax2
+// the lane's largest |Q|^2). NaN counts as beyond.
+__device__ __forceinline__ bool big_phases64(double qmax2, double R) {
+  return __any(!(sqrt(qmax2) * R <= 0.999 * kSinCosMax64));
 }
 
 // ---------------------------------------------------------------------------

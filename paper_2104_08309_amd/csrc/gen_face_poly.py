@@ -19,7 +19,9 @@ needed), the largest error (times |E| for B, br, gi) minimised by Lawson's rewei
 80-bit arithmetic. Symmetric functions in two variables need about half the operations of the
 one-variable recurrences in n.
 
-Two sets: binary32 in the scaled phases d / (4 pi) (half-phases in turns), binary64 in radians.
+Two sets: binary32 in the scaled phases d / (4 pi) (half-phases in turns), binary64 in radians. The binary64
+sine and cosine on [-pi/4, pi/4] (their arguments are reduced by multiples of pi/2) are fitted the same way:
+sin x = x + x^3 S(x^2), cos x = 1 - x^2 / 2 + x^4 C(x^2).
 Run from this directory (on a machine with an 80-bit long double): python gen_face_poly.py > face_poly.h
 """
 from fractions import Fraction
@@ -35,6 +37,7 @@ M32, M64 = 3.6, 3.0
 SHAPE32 = {"A": (6, 3), "B": (5, 2), "bi": (6, 3), "br": (4, 1), "gr": (5, 2), "gi": (4, 1)}
 SHAPE64 = {"A": (11, 8, 4, 1), "B": (9, 6, 3), "bi": (9, 7, 3, 1), "br": (8, 5, 2), "gr": (9, 6, 3), "gi": (8, 4, 1)}
 ODD = ("B", "br", "gi")  # multiplied by E
+ROW64 = []  # every binary64 coefficient, in the order of the "at" offsets
 
 
 def taylor():
@@ -180,8 +183,33 @@ def table(name, T, M, shape, odd, scale, kind):
             txt = ", ".join(f"{float(np.float32(x))!r}f" for x in v)
         else:
             txt = ", ".join(repr(float(x)) for x in v)
-        out.append(f"  struct {name}{k} {{ static constexpr {kind} c[{na}] = {{{txt}}}; }};")
+        at = ""
+        if kind == "double":
+            at = f" static constexpr int at = {len(ROW64)};"
+            ROW64.extend(repr(float(x)) for x in v)
+        out.append(f"  struct {name}{k} {{ static constexpr {kind} c[{na}] = {{{txt}}};{at} }};")
     return out
+
+
+def sincos_fit(first, terms, rounds=40):
+    """Coefficients of g(z), z = x^2, with first = 3: sin x = x + x^3 g, first = 4: cos x = 1 - x^2/2 + x^4 g,
+    on |x| <= pi/4 (error of the sine or cosine minimised)."""
+    n = 400
+    z = (LD(np.pi) / 4 * LD(1.0001)) ** 2 * (1 - np.cos(LD(np.pi) * (np.arange(n, dtype=LD) + LD(0.5)) / n)) / 2
+    y = np.zeros(n, LD)
+    for k in reversed(range(14)):
+        y = y * z + LD((-1) ** (k + (1 if first == 3 else 0))) / LD(factorial(first + 2 * k))
+    unit = z ** (LD(first) / 2)
+    A = np.stack([(z / z.max()) ** a for a in range(terms)], 1)
+    lw, best = np.ones(n, LD) / n, None
+    for _ in range(rounds):
+        sw = np.sqrt(lw) * unit
+        c = least_squares(A * sw[:, None], y * sw)
+        r = abs(A @ c - y) * unit
+        if best is None or r.max() < best[0]:
+            best = (r.max(), c)
+        lw = np.maximum(lw * r / (lw * r).sum(), LD(1e-25))
+    return [float(v / z.max() ** a) for a, v in enumerate(best[1])], float(best[0])
 
 
 def main():
@@ -192,18 +220,32 @@ def main():
     print("// for centred vertex phases max |d_k| <= M: each function is sum_k w^k sum_a f<k>::c[a] p^a with")
     print("// p = d_0^2 + d_0 d_1 + d_1^2, E = d_0 d_1 (d_0 + d_1), w = E^2. \"error\" is the fit's largest.")
     print("#pragma once\n\nnamespace pft {\n")
+    print("// sin x = x + x^3 S(x^2), cos x = 1 - x^2 / 2 + x^4 C(x^2) on [-pi/4, pi/4], binary64.")
+    print("struct SinCos64 {")
+    for name, first in (("S", 3), ("C", 4)):
+        c, err = sincos_fit(first, 6)
+        print(f"  // error {err:.1e}")
+        print(f"  struct {name} {{ static constexpr double c[{len(c)}] = {{{', '.join(repr(v) for v in c)}}};"
+              f" static constexpr int at = {len(ROW64)}; }};")
+        ROW64.extend(repr(v) for v in c)
+    print("};\n")
     for st, M, shapes, scale, kind, what in (
-            ("FaceFit32", M32, SHAPE32, 4 * np.pi, "float", "binary32; the variables are phases / (4 pi): p, E, w of d / (4 pi)"),
+            ("FaceFit32", M32, SHAPE32, LD(4) * LD("3.14159265358979323846264338"), "float",
+             "binary32; the variables are phases / (4 pi): p, E, w of d / (4 pi)"),
             ("FaceFit64", M64, SHAPE64, 1, "double", "binary64; phases in radians")):
         print(f"// {what}; M in radians.")
         print(f"struct {st} {{")
         print(f"  static constexpr double M = {M!r};")
         for name in shapes:
             # beta and gamma multiply d_k and d_k^2, which carry their own scale
-            for line in table(name, T[name], M, shapes[name], name in ODD, LD(4) * LD("3.14159265358979323846264338") if scale != 1 else 1, kind):
+            for line in table(name, T[name], M, shapes[name], name in ODD, scale, kind):
                 print(line)
         print("};\n")
-    print("}  // namespace pft")
+    print("// Every binary64 coefficient above in one row; a function's start at its \"at\".")
+    print("#define PFT_FIT64_ROW \\")
+    rows = [", ".join(ROW64[i:i + 5]) for i in range(0, len(ROW64), 5)]
+    print(", \\\n".join("  " + r for r in rows))
+    print("\n}  // namespace pft")
 
 
 if __name__ == "__main__":

@@ -52,6 +52,15 @@ __host__ __device__ constexpr int fwd_waves(int qpt) { return PFT_FWD_WAVES; }  
 constexpr int kFwdSplitWaves = PFT_FWD_BLOCK_WAVES;  // wavefronts of an FP32C forward block, each on its own faces
 constexpr int kFwdBlock = 64 * kFwdSplitWaves;       // threads of an FP32C forward block
 __host__ __device__ constexpr int fwd_qtile(int qpt) { return 64 * qpt; }  // Q of an FP32C forward block
+#ifndef PFT_QPT64
+#define PFT_QPT64 2
+#endif
+constexpr int kQPT64 = PFT_QPT64;    // Q per thread in the binary64 forward
+#ifndef PFT_FWD_WAVES64
+#define PFT_FWD_WAVES64 4
+#endif
+constexpr int kFwdWaves64 = PFT_FWD_WAVES64;  // its waves per SIMD
+constexpr int kTileF64 = 32;         // faces per LDS tile of one of its wavefronts (4 KiB)
 constexpr int kXcds = 8;                             // accelerator dies (each with its own L2) of the target
 #ifndef PFT_BATCH_FWD_WAVES
 #define PFT_BATCH_FWD_WAVES 4

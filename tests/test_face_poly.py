@@ -16,7 +16,7 @@ def _fits():
     out = {}
     for m in re.finditer(r"struct (FaceFit\d+) \{\n  static constexpr double M = ([0-9.]+);\n(.*?)\n\};", src, re.S):
         tab = {}
-        for t in re.finditer(r"struct ([A-Za-z]+)(\d) \{ static constexpr \w+ c\[(\d+)\] = \{([^}]*)\}; \};", m.group(3)):
+        for t in re.finditer(r"struct ([A-Za-z]+)(\d) \{ static constexpr \w+ c\[(\d+)\] = \{([^}]*)\};", m.group(3)):
             c = np.array([float(x.strip().rstrip("f")) for x in t.group(4).split(",")])
             assert len(c) == int(t.group(3))
             tab.setdefault(t.group(1), []).append(c)
