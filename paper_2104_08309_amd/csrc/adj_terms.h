@@ -3,6 +3,7 @@
 // kernels. The formulas are stated at the top of bwd3d.hip.
 #pragma once
 
+#include "face_moments.h"
 #include "moment_poly.h"
 #include "pft_device.h"
 
@@ -18,80 +19,10 @@ PFT_HD __forceinline__ double dsinc_series(double x) {
              x2 * (-1.0 / 3991680.0 + x2 * (1.0 / 518918400.0))))));
 }
 
-// Barycentric moments of a triangle from its centred vertex phases
-// d0 + d1 + d2 = 0 (d_k = Q.(v_k - g)):
+// Barycentric moments of a triangle from its centred vertex phases d0 + d1 + d2 = 0 (d_k = Q.(v_k - g)):
 //   Y_k = sum_n i^n h_n(d0, d1, d2, d_k) / (n+3)!   (k = 0, 1),
-//   J   = sum_n i^n h_n(d0, d1, d2) / (n+2)!         (so Y_2 = J - Y_0 - Y_1),
-// with H_n = h_n(d0, d1, d2) = -e2 H_{n-2} + e3 H_{n-3} and
-// h_n(d0, d1, d2, d_k) = H_n + d_k h_{n-1}(d0, d1, d2, d_k). Terms are added four
-// at a time until m^n / n! < tol (m = max |d_k|; the next term of Y is below
-// (1/6) m^n / n!, of J below (1/2) m^n / n!), or n reaches NMAX. The loop is
-// unrolled, so the factorial coefficients are compile-time constants folded into
-// the instructions rather than values held in registers.
-template <typename T>
-PFT_HD constexpr T inv_fact_c(int n) {
-  constexpr double t[kInvFactCount] = {PFT_INV_FACT_VALUES};
-  return T(t[n]);
-}
-
-template <typename T, int NMAX>
-PFT_HD __forceinline__ void bary_moments(T d0, T d1, T m, T tol, T* yr, T* yi, T& jr, T& ji) {
-  const T d2 = -d0 - d1;
-  const T e2 = d0 * d1 + d2 * (d0 + d1);
-  const T e3 = d0 * d1 * d2;
-  const T m2 = m * m, m4 = m2 * m2;
-  // n = 1..4 written out: H_1 = 0, H_2 = -e2, H_3 = e3, H_4 = e2^2
-  const T H2 = -e2, H3 = e3, H4 = e2 * e2;
-  T a0 = d0, a1 = d1;  // h_{n}(d0,d1,d2,d0), h_{n}(d0,d1,d2,d1) at n = 1
-  T y0i = inv_fact_c<T>(4) * a0, y1i = inv_fact_c<T>(4) * a1;
-  a0 = H2 + d0 * a0;
-  a1 = H2 + d1 * a1;
-  T y0r = T(1.0 / 6.0) - inv_fact_c<T>(5) * a0, y1r = T(1.0 / 6.0) - inv_fact_c<T>(5) * a1;
-  jr = T(0.5) - inv_fact_c<T>(4) * H2;
-  a0 = H3 + d0 * a0;
-  a1 = H3 + d1 * a1;
-  y0i -= inv_fact_c<T>(6) * a0;
-  y1i -= inv_fact_c<T>(6) * a1;
-  ji = -inv_fact_c<T>(5) * H3;
-  a0 = H4 + d0 * a0;
-  a1 = H4 + d1 * a1;
-  y0r += inv_fact_c<T>(7) * a0;
-  y1r += inv_fact_c<T>(7) * a1;
-  jr += inv_fact_c<T>(6) * H4;
-  T Hm3 = H2, Hm2 = H3, Hm1 = H4;  // H_{n-3}, H_{n-2}, H_{n-1} at n = 5
-  T mn = m * m4;                   // m^n at the start of each chunk
-  if (!(mn * inv_fact_c<T>(5) < tol)) {
-#pragma unroll
-    for (int n = 5; n < NMAX; n += 4) {
-      // i^n cycles (+i, -1, -i, +1) over n = 1, 2, 3, 4 (mod 4)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const T H = -e2 * Hm2 + e3 * Hm3;
-        a0 = H + d0 * a0;
-        a1 = H + d1 * a1;
-        const T c3 = inv_fact_c<T>(n + r + 3), c2 = inv_fact_c<T>(n + r + 2);
-        if (r == 0) {
-          y0i += c3 * a0; y1i += c3 * a1; ji += c2 * H;
-        } else if (r == 1) {
-          y0r -= c3 * a0; y1r -= c3 * a1; jr -= c2 * H;
-        } else if (r == 2) {
-          y0i -= c3 * a0; y1i -= c3 * a1; ji -= c2 * H;
-        } else {
-          y0r += c3 * a0; y1r += c3 * a1; jr += c2 * H;
-        }
-        Hm3 = Hm2;
-        Hm2 = Hm1;
-        Hm1 = H;
-      }
-      mn *= m4;
-      if (mn * inv_fact_c<T>(n + 4) < tol) break;
-    }
-  }
-  yr[0] = y0r; yi[0] = y0i;
-  yr[1] = y1r; yi[1] = y1i;
-}
-
-// The same moments in binary32 from a polynomial q(x) = sum_n i^n a_n x^n of exp(ix)
+//   J   = sum_n i^n h_n(d0, d1, d2) / (n+2)!         (so Y_2 = J - Y_0 - Y_1).
+// In binary32 from a polynomial q(x) = sum_n i^n a_n x^n of exp(ix)
 // fitted on [-M, M] (moment_poly.h): J = sum_n i^n a_n n! H_n / (n+2)! and
 // Y_k = sum_n i^n a_n n! h_n(d0, d1, d2, d_k) / (n+3)!, exact for q, so the error is
 // the simplex average of q - exp(ix) at phases within [-M, M] (J within err/2, Y_k
@@ -181,14 +112,14 @@ __device__ __forceinline__ void bary_moments_f32(float d0, float d1, float m, fl
 // X_k * inv with inv = 1/|P|^2 (P = Q x N), and S is the face's edge sum, so
 // that X_0 + X_1 + X_2 = i S and the normalised face integral is i S inv. The
 // moments come from the closed-form Q-derivative of the edge sum.
-PFT_HD __forceinline__ void edge_moments_f64(const Face64& f, const double* G, const double* Q, double Px, double Py,
-                                             double Pz, double q0, double q1, double inv, double* Xr, double* Xi,
-                                             double& Sr, double& Si) {
+__device__ __forceinline__ void edge_moments_f64(Fit64 t, const Face64& f, const double* G, double Px, double Py,
+                                                 double Pz, double q0, double q1, double inv, double* Xr, double* Xi,
+                                                 double& Sr, double& Si) {
   const double q2 = -q0 - q1;
   const double p0 = 0.5 * q0, p1 = 0.5 * q1, p2 = 0.5 * q2;
   double s0, c0, s1, c1;
-  sincos(p0, &s0, &c0);
-  sincos(p1, &s1, &c1);
+  sincos_any64(t, p0, &s0, &c0);
+  sincos_any64(t, p1, &s1, &c1);
   const double c2 = c0 * c1 - s0 * s1;
   const double s2 = -(s0 * c1 + c0 * s1);
   const double pi0 = Px * f.u0[0] + Py * f.u0[1] + Pz * f.u0[2];
@@ -245,40 +176,80 @@ PFT_HD __forceinline__ void edge_moments_f64(const Face64& f, const double* G, c
   }
 }
 
-PFT_HD __forceinline__ void adj_term_f64(const Face64& f, const double* G, const double* Q, double gr,
-                                             double gi, double* R) {
+// The edge form's moments of one pair: X_k / |P|^2 for k = 0, 1 and the face integral J = i S / |P|^2.
+__device__ __forceinline__ void far_moments_f64(Fit64 t, const Face64& f, const double* G, const double* Q, double d0,
+                                                double d1, double* yr, double* yi, double& jr, double& ji) {
   const double Px = Q[1] * f.N[2] - Q[2] * f.N[1];
   const double Py = Q[2] * f.N[0] - Q[0] * f.N[2];
   const double Pz = Q[0] * f.N[1] - Q[1] * f.N[0];
-  const double P2 = Px * Px + Py * Py + Pz * Pz;
-  const double phi = Q[0] * f.g[0] + Q[1] * f.g[1] + Q[2] * f.g[2];
-  double sf, cf;
-  sincos(phi, &sf, &cf);
-  // z = conj(g) exp(i Q.g)
-  const double zr = gr * cf + gi * sf;
-  const double zi = gr * sf - gi * cf;
-  const double q0 = Q[0] * f.u0[0] + Q[1] * f.u0[1] + Q[2] * f.u0[2];
-  const double q1 = Q[0] * f.u1[0] + Q[1] * f.u1[1] + Q[2] * f.u1[2];
-  const double q2 = -q0 - q1;
-  if (f.thr < 0.0) {  // empty face
-    R[0] = R[1] = R[2] = 0.0;
-    return;
-  }
-  const double m = fmax(fabs(q0), fmax(fabs(q1), fabs(q2)));
-  if (m <= kSeriesMaxPhase) {
-    // barycentric moments by their series (no cancellation for |delta| <= 3)
-    double yr[2], yi[2], jr, ji;
-    bary_moments<double, 33>(q0, q1, m, 1e-17, yr, yi, jr, ji);
-    R[0] = zr * yr[0] - zi * yi[0];
-    R[1] = zr * yr[1] - zi * yi[1];
-    R[2] = (zr * jr - zi * ji) - R[0] - R[1];
-    return;
-  }
-  const double inv = 1.0 / P2;
+  const double inv = 1.0 / (Px * Px + Py * Py + Pz * Pz);
   double Xr[3], Xi[3], Sr, Si;
-  edge_moments_f64(f, G, Q, Px, Py, Pz, q0, q1, inv, Xr, Xi, Sr, Si);
+  edge_moments_f64(t, f, G, Px, Py, Pz, d0, d1, inv, Xr, Xi, Sr, Si);
+  for (int k = 0; k < 2; ++k) yr[k] = Xr[k] * inv, yi[k] = Xi[k] * inv;
+  jr = -Si * inv;
+  ji = Sr * inv;
+}
+
+// One face against a thread's P Q points, binary64: with z = conj(g) exp(iQ.g), adds Re(z Y_0), Re(z Y_1) and
+// Re(z J) (Y_2 = J - Y_0 - Y_1 is taken once per face in adj_block_sum) to S. Y_k = alpha + beta d_k + gamma d_k^2
+// only enters through Re(z .), so three real combinations of the six fitted functions serve all corners. The edge
+// form beyond the fitted range; the choice is per lane. An empty record (N = 0, phases 0) gives finite weights that
+// the vertex gather multiplies by N = 0. Bound by binary64 issue, about 165 instructions per pair against some 300 of
+// the series in n (5 120 faces x 64 000 Q: kernel 3.41 -> 2.41 ms under the profiler); with P = 2 a coefficient is
+// read once for two pairs (3 and 4 points: 9 % and 0.5 % slower fitting step, fewer wavefronts in flight).
+template <int P>
+__device__ __forceinline__ void adj_face_f64(const Face64& f, const double* G, const double (*Q)[3], const double* gr,
+                                             const double* gi, bool big, double* S) {
+  const Fit64 t = fit64();
+  // the P points side by side: a coefficient is read once for all of them
+  double d0[P], d1[P], zr[P], zi[P], A[P], B[P], bi[P], br[P], cr[P], ci[P];
+  bool any = false;
 #pragma unroll
-  for (int k = 0; k < 3; ++k) R[k] = (zr * Xr[k] - zi * Xi[k]) * inv;
+  for (int k = 0; k < P; ++k) {
+    d0[k] = Q[k][0] * f.u0[0] + Q[k][1] * f.u0[1] + Q[k][2] * f.u0[2];
+    d1[k] = Q[k][0] * f.u1[0] + Q[k][1] * f.u1[1] + Q[k][2] * f.u1[2];
+    const double phi = Q[k][0] * f.g[0] + Q[k][1] * f.g[1] + Q[k][2] * f.g[2];
+    double sf, cf;
+    if (__builtin_expect(big, 0))
+      sincos_any64(t, phi, &sf, &cf);
+    else
+      sincos64(t, phi, &sf, &cf);
+    zr[k] = gr[k] * cf + gi[k] * sf;
+    zi[k] = gr[k] * sf - gi[k] * cf;
+  }
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    const double s = d0[k] + d1[k];
+    const double p = d0[k] * s + d1[k] * d1[k], E = d0[k] * d1[k] * s, w = E * E;
+    any |= fmax(fabs(d0[k]), fmax(fabs(d1[k]), fabs(s))) > FaceFit64::M;
+    face_ab64(t, p, w, A[k], B[k]);
+    face_beta_gamma64(t, p, w, bi[k], br[k], cr[k], ci[k]);
+    const double er = zr[k] * E, ei = zi[k] * E;
+    const double a = zr[k] * A[k] - ei * B[k];           // Re(z J)
+    const double b = er * br[k] - zi[k] * bi[k];         // Re(z beta)
+    const double c = zr[k] * cr[k] - ei * ci[k];         // Re(z gamma)
+    const double al = (a - 2.0 * p * c) * (1.0 / 3.0);
+    A[k] = a;
+    B[k] = al + d0[k] * (b + d0[k] * c);
+    bi[k] = al + d1[k] * (b + d1[k] * c);
+  }
+  if (any) {
+#pragma unroll
+    for (int k = 0; k < P; ++k)
+      if (fmax(fabs(d0[k]), fmax(fabs(d1[k]), fabs(d0[k] + d1[k]))) > FaceFit64::M) {
+        double yr[2], yi[2], jr, ji;
+        far_moments_f64(t, f, G, Q[k], d0[k], d1[k], yr, yi, jr, ji);
+        B[k] = zr[k] * yr[0] - zi[k] * yi[0];
+        bi[k] = zr[k] * yr[1] - zi[k] * yi[1];
+        A[k] = zr[k] * jr - zi[k] * ji;
+      }
+  }
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    S[0] += B[k];
+    S[1] += bi[k];
+    S[2] += A[k];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -424,12 +395,13 @@ __device__ __forceinline__ double block_total(double v, double* lds) {
 // reduces the slots once the range is done.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void adj_tile_f64(const Face64* tile, const double (*gtile)[8], int nt, int64_t qb,
-                                             int64_t qe, const QRec64* __restrict__ rec, double (*acc)[kBlock]) {
-  constexpr int P = kQPTB;
+                                             int64_t qe, const QRec64* __restrict__ rec, double R, double (*acc)[kBlock]) {
+  constexpr int P = kQPTB64;
   const int tid = threadIdx.x;
   for (int64_t q0 = qb; q0 < qe; q0 += (int64_t)kBlock * P) {
     double Qd[P][3];
     double hr[P], hi[P];
+    bool big = false;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int64_t qi = q0 + (int64_t)p * kBlock + tid;
@@ -443,18 +415,12 @@ __device__ __forceinline__ void adj_tile_f64(const Face64* tile, const double (*
         hr[p] = r.hr;
         hi[p] = r.hi;
       }
+      big |= big_phases64(Qd[p][0] * Qd[p][0] + Qd[p][1] * Qd[p][1] + Qd[p][2] * Qd[p][2], R);
     }
 #pragma unroll 1
     for (int j = 0; j < nt; ++j) {
       double S[3] = {0.0, 0.0, 0.0};
-#pragma unroll
-      for (int p = 0; p < P; ++p) {
-        double R[3];
-        adj_term_f64(tile[j], gtile[j], Qd[p], hr[p], hi[p], R);
-        S[0] += R[0];
-        S[1] += R[1];
-        S[2] += R[2];
-      }
+      adj_face_f64<P>(tile[j], gtile[j], Qd, hr, hi, big, S);
 #pragma unroll
       for (int k = 0; k < 3; ++k) acc[3 * j + k][tid] += S[k];
     }
@@ -511,18 +477,27 @@ __device__ __forceinline__ void adj_tile_fp32c(const Face32B* tile, int nt, int6
   }
 }
 
-// Sum of the per-thread slots of adj_tile_fp32c / adj_tile_f64 for each of the
-// nt * 3 weights, in binary64 and a fixed order; wave w handles weights w,
-// w + 4, ... and lane 0 writes out[v]. Call after a barrier.
-template <typename T>
+// Sum of the per-thread slots of adj_tile_fp32c / adj_tile_f64 for each of the nt faces, in binary64 and a fixed
+// order; wave w handles faces w, w + 4, ... and lane 0 writes the corner weights out[3 j + k]. kFaceSum: the third
+// slot holds the face integral's weight, corner 2 is that less the other two (binary64; in binary32 the subtraction
+// after the sum would leave corner 2 the rounding of a three times larger sum). Call after a barrier.
+template <bool kFaceSum, typename T>
 __device__ __forceinline__ void adj_block_sum(T (*acc)[kBlock], int nt, double* out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int v = wave; v < nt * 3; v += kBlock / 64) {
-    double x = 0.0;
+  for (int j = wave; j < nt; j += kBlock / 64) {
+    double x[3];
 #pragma unroll
-    for (int i = 0; i < kBlock / 64; ++i) x += (double)acc[v][lane + 64 * i];
-    x = wave_total(x);
-    if (lane == 0) out[v] = x;
+    for (int k = 0; k < 3; ++k) {
+      x[k] = 0.0;
+#pragma unroll
+      for (int i = 0; i < kBlock / 64; ++i) x[k] += (double)acc[3 * j + k][lane + 64 * i];
+      x[k] = wave_total(x[k]);
+    }
+    if (lane == 0) {
+      out[3 * j] = x[0];
+      out[3 * j + 1] = x[1];
+      out[3 * j + 2] = kFaceSum ? x[2] - x[0] - x[1] : x[2];
+    }
   }
 }
 

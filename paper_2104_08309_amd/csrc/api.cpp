@@ -2063,7 +2063,7 @@ pft_status pft_batch_backward(const pft_mesh_batch* b, pft_mode mode, const void
     const int grid = (int)std::min<int64_t>(std::max<int64_t>(n_items, 1),
                                             (int64_t)num_cus() * batch_bwd_blocks_per_cu(mode));
     if (profile) prof_begin("batch_bwd", s);
-    re = launch_batch_bwd(mode, d_items, n_items, counter, p.f64, gram, f32b, rec, rec64, partial, grid, s);
+    re = launch_batch_bwd(mode, d_items, n_items, counter, p.f64, gram, f32b, rec, rec64, p.info, partial, grid, s);
     if (profile) prof_end("batch_bwd", s);
     return re == hipSuccess ? PFT_OK : hip_fail(re, "batch adjoint");
   };

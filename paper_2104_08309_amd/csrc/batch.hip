@@ -246,7 +246,8 @@ __global__ __launch_bounds__(kBlock) void batch_bwd_fp64_kernel(const BatchItemB
                                                                int64_t n_items, uint32_t* counter,
                                                                const Face64* __restrict__ f64,
                                                                const double* __restrict__ gram,
-                                                               const QRec64* __restrict__ rec, double* partial) {
+                                                               const QRec64* __restrict__ rec, const MeshInfo* __restrict__ info,
+                                                               double* partial) {
   __shared__ Face64 tile[kTileFB];
   __shared__ double gtile[kTileFB][8];
   __shared__ double acc[kTileFB * 3][kBlock];
@@ -262,9 +263,9 @@ __global__ __launch_bounds__(kBlock) void batch_bwd_fp64_kernel(const BatchItemB
     for (int i = tid; i < nt * 8; i += kBlock) gtile[i / 8][i % 8] = gram[(it.f0 + i / 8) * 8 + i % 8];
     for (int v = 0; v < nt * 3; ++v) acc[v][tid] = 0.0;
     __syncthreads();
-    adj_tile_f64(tile, gtile, nt, it.q0, it.q0 + it.nq, rec, acc);
+    adj_tile_f64(tile, gtile, nt, it.q0, it.q0 + it.nq, rec, info[it.mesh].R, acc);
     __syncthreads();
-    adj_block_sum(acc, nt, partial + it.part * 3);
+    adj_block_sum<true>(acc, nt, partial + it.part * 3);
     __syncthreads();
   }
 }
@@ -288,7 +289,7 @@ __global__ __launch_bounds__(kBlock) void batch_bwd_fp32c_kernel(const BatchItem
     __syncthreads();
     adj_tile_fp32c(tile, nt, it.q0, it.q0 + it.nq, rec, acc);
     __syncthreads();
-    adj_block_sum(acc, nt, partial + it.part * 3);
+    adj_block_sum<false>(acc, nt, partial + it.part * 3);
     __syncthreads();
   }
 }
@@ -373,10 +374,10 @@ hipError_t launch_batch_fwd_finish(const double2* partial, const int64_t* d_q_of
 
 hipError_t launch_batch_bwd(int mode, const BatchItemBwd* items, int64_t n_items, uint32_t* counter,
                             const Face64* f64, const double* gram, const Face32B* f32b, const QRec32* rec,
-                            const QRec64* rec64, double* partial, int grid, hipStream_t s) {
+                            const QRec64* rec64, const MeshInfo* info, double* partial, int grid, hipStream_t s) {
   if (n_items <= 0) return hipSuccess;
   if (mode == PFT_FP64)
-    batch_bwd_fp64_kernel<<<grid, kBlock, 0, s>>>(items, n_items, counter, f64, gram, rec64, partial);
+    batch_bwd_fp64_kernel<<<grid, kBlock, 0, s>>>(items, n_items, counter, f64, gram, rec64, info, partial);
   else
     batch_bwd_fp32c_kernel<<<grid, kBlock, 0, s>>>(items, n_items, counter, f32b, rec, partial);
   return hipGetLastError();

@@ -67,9 +67,9 @@ __global__ __launch_bounds__(kBlock) void bwd3d_fp64_kernel(BwdArgs a, const dou
   __syncthreads();
   const int64_t qb = qs * a.q_per_split;
   const int64_t qe = min(a.nq, qb + a.q_per_split);
-  adj_tile_f64(tile, gtile, nt, qb, qe, a.rec64, acc);
+  adj_tile_f64(tile, gtile, nt, qb, qe, a.rec64, a.info[0].R, acc);
   __syncthreads();
-  adj_block_sum(acc, nt, a.partial + (qs * a.nf + f0) * 3);
+  adj_block_sum<true>(acc, nt, a.partial + (qs * a.nf + f0) * 3);
 }
 
 __global__ __launch_bounds__(kBlock) void bwd3d_fp32c_kernel(BwdArgs a) {
@@ -88,7 +88,7 @@ __global__ __launch_bounds__(kBlock) void bwd3d_fp32c_kernel(BwdArgs a) {
   const int64_t qe = min(a.nq, qb + a.q_per_split);
   adj_tile_fp32c(tile, nt, qb, qe, a.rec, acc);
   __syncthreads();
-  adj_block_sum(acc, nt, a.partial + (qs * a.nf + f0) * 3);
+  adj_block_sum<false>(acc, nt, a.partial + (qs * a.nf + f0) * 3);
 }
 
 __global__ __launch_bounds__(256) void gram64_kernel(const Face64* f64, int64_t nf, double* gram) {

@@ -46,7 +46,8 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp64_kernel(DqArgs a) {
   if (active) load_q3(a.q, a.qdtype, a.perm ? (int64_t)a.perm[qi] : qi, Q);
   const double4 geo = a.split_geo ? a.split_geo[blockIdx.y] : make_double4(0.0, 0.0, 0.0, a.info[0].R);
   const double o[3] = {geo.x, geo.y, geo.z};
-  const bool small = sqrt(Q[0] * Q[0] + Q[1] * Q[1] + Q[2] * Q[2]) * geo.w < a.tau;
+  const double Q2 = Q[0] * Q[0] + Q[1] * Q[1] + Q[2] * Q[2];
+  const bool small = sqrt(Q2) * geo.w < a.tau, big = big_phases64(Q2, a.info[0].R);
   int64_t f_begin, f_end;
   split_range(a, f_begin, f_end);
   double Ar[3] = {0.0, 0.0, 0.0}, Ai[3] = {0.0, 0.0, 0.0}, Br = 0.0, Bi = 0.0;
@@ -62,7 +63,7 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp64_kernel(DqArgs a) {
     }
     __syncthreads();
     if (!small) {
-      for (int j = 0; j < nt; ++j) dq_term_f64(tile[j], gtile[j], Q, Ar, Ai, Br, Bi);
+      for (int j = 0; j < nt; ++j) dq_term_f64(tile[j], gtile[j], Q, big, Ar, Ai, Br, Bi);
     } else {
       for (int j = 0; j < nt; ++j) dq_tet_f64(tile[j], Q, Ar, Ai, Br, Bi, o);
     }

@@ -110,34 +110,23 @@ PFT_HD __forceinline__ void dq_apex(const double* Q, const double* o, double* Gr
   Fr = fr;
 }
 
-// binary64 surface term of face f: A += c sum_k (v_k - t) Y_k, B += c J.
-PFT_HD __forceinline__ void dq_term_f64(const Face64& f, const double* G, const double* Q, double* Ar, double* Ai,
-                                        double& Br, double& Bi) {
-  if (f.thr < 0.0) return;  // empty face
-  const double Px = Q[1] * f.N[2] - Q[2] * f.N[1];
-  const double Py = Q[2] * f.N[0] - Q[0] * f.N[2];
-  const double Pz = Q[0] * f.N[1] - Q[1] * f.N[0];
-  const double P2 = Px * Px + Py * Py + Pz * Pz;
+// binary64 surface term of face f: A += c sum_k (v_k - t) Y_k, B += c J. (An empty record has N = 0 and phases 0: it
+// adds 0.)
+__device__ __forceinline__ void dq_term_f64(const Face64& f, const double* G, const double* Q, bool big, double* Ar,
+                                            double* Ai, double& Br, double& Bi) {
+  const Fit64 t = fit64();
   double sf, cf;
-  sincos(Q[0] * f.g[0] + Q[1] * f.g[1] + Q[2] * f.g[2], &sf, &cf);
+  const double phi = Q[0] * f.g[0] + Q[1] * f.g[1] + Q[2] * f.g[2];
+  if (__builtin_expect(big, 0))
+    sincos_any64(t, phi, &sf, &cf);
+  else
+    sincos64(t, phi, &sf, &cf);
   const double QN = Q[0] * f.N[0] + Q[1] * f.N[1] + Q[2] * f.N[2];
   const double q0 = Q[0] * f.u0[0] + Q[1] * f.u0[1] + Q[2] * f.u0[2];
   const double q1 = Q[0] * f.u1[0] + Q[1] * f.u1[1] + Q[2] * f.u1[2];
-  const double m = fmax(fabs(q0), fmax(fabs(q1), fabs(q0 + q1)));
   double yr[2], yi[2], jr, ji;
-  if (m <= kSeriesMaxPhase) {
-    bary_moments<double, 33>(q0, q1, m, 1e-17, yr, yi, jr, ji);
-  } else {
-    const double inv = 1.0 / P2;
-    double Xr[3], Xi[3], Sr, Si;
-    edge_moments_f64(f, G, Q, Px, Py, Pz, q0, q1, inv, Xr, Xi, Sr, Si);
-    yr[0] = Xr[0] * inv;
-    yi[0] = Xi[0] * inv;
-    yr[1] = Xr[1] * inv;
-    yi[1] = Xi[1] * inv;
-    jr = -Si * inv;
-    ji = Sr * inv;
-  }
+  bary_moments_fit64(t, q0, q1, yr, yi, jr, ji);
+  if (fmax(fabs(q0), fmax(fabs(q1), fabs(q0 + q1))) > FaceFit64::M) far_moments_f64(t, f, G, Q, q0, q1, yr, yi, jr, ji);
   const double cr = QN * cf, ci = QN * sf;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {

@@ -66,20 +66,18 @@ __device__ __forceinline__ void sincos_any64(Fit64 t, double x, double* s, doubl
     sincos64(t, x, s, c);
 }
 
-// 1 / x to about one unit in the last place (x finite, not 0): two Newton steps from the hardware estimate.
-__device__ __forceinline__ double recip64(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = r + r * (1.0 - x * r);
-  return r + r * (1.0 - x * r);
+// A and B of J = A + i E B, and J itself, binary64, max |d_k| <= FaceFit64::M.
+__device__ __forceinline__ void face_ab64(Fit64 t, double p, double w, double& A, double& B) {
+  A = ((horner64<FaceFit64::A3>(t, p) * w + horner64<FaceFit64::A2>(t, p)) * w + horner64<FaceFit64::A1>(t, p)) * w +
+      horner64<FaceFit64::A0>(t, p);
+  B = (horner64<FaceFit64::B2>(t, p) * w + horner64<FaceFit64::B1>(t, p)) * w + horner64<FaceFit64::B0>(t, p);
 }
-
-// J, binary64, max |d_k| <= FaceFit64::M.
 __device__ __forceinline__ void face_integral_fit64(Fit64 t, double d0, double d1, double& jr, double& ji) {
   const double s = d0 + d1;
-  const double p = d0 * s + d1 * d1, E = d0 * d1 * s, w = E * E;
-  jr = ((horner64<FaceFit64::A3>(t, p) * w + horner64<FaceFit64::A2>(t, p)) * w + horner64<FaceFit64::A1>(t, p)) * w +
-       horner64<FaceFit64::A0>(t, p);
-  ji = E * ((horner64<FaceFit64::B2>(t, p) * w + horner64<FaceFit64::B1>(t, p)) * w + horner64<FaceFit64::B0>(t, p));
+  const double E = d0 * d1 * s;
+  double B;
+  face_ab64(t, d0 * s + d1 * d1, E * E, jr, B);
+  ji = E * B;
 }
 
 // beta and gamma's parts: beta = i bi + E br, gamma = gr + i E gi.
@@ -89,6 +87,30 @@ __device__ __forceinline__ void face_beta_gamma64(Fit64 t, double p, double w, d
   br = (horner64<FaceFit64::br2>(t, p) * w + horner64<FaceFit64::br1>(t, p)) * w + horner64<FaceFit64::br0>(t, p);
   gr = (horner64<FaceFit64::gr2>(t, p) * w + horner64<FaceFit64::gr1>(t, p)) * w + horner64<FaceFit64::gr0>(t, p);
   gi = (horner64<FaceFit64::gi2>(t, p) * w + horner64<FaceFit64::gi1>(t, p)) * w + horner64<FaceFit64::gi0>(t, p);
+}
+
+// J and the complex moments Y_0, Y_1 (Y_2 = J - Y_0 - Y_1), binary64, max |d_k| <= FaceFit64::M.
+__device__ __forceinline__ void bary_moments_fit64(Fit64 t, double d0, double d1, double* yr, double* yi, double& jr,
+                                                   double& ji) {
+  const double s = d0 + d1;
+  const double p = d0 * s + d1 * d1, E = d0 * d1 * s, w = E * E;
+  double B, bi, br, gr, gi;
+  face_ab64(t, p, w, jr, B);
+  ji = E * B;
+  face_beta_gamma64(t, p, w, bi, br, gr, gi);
+  br *= E;
+  gi *= E;
+  const double ar = (jr - 2.0 * p * gr) * (1.0 / 3.0), ai = (ji - 2.0 * p * gi) * (1.0 / 3.0);
+  yr[0] = ar + d0 * (br + d0 * gr);
+  yi[0] = ai + d0 * (bi + d0 * gi);
+  yr[1] = ar + d1 * (br + d1 * gr);
+  yi[1] = ai + d1 * (bi + d1 * gi);
+}
+
+// Whether an origin phase Q.g of a wavefront can exceed the range of sincos64: |g| <= R, the mesh's radius (q2
+// the lane's |Q|^2). NaN counts as beyond.
+__device__ __forceinline__ bool big_phases64(double q2, double R) {
+  return __any(!(sqrt(q2) * R <= 0.999 * kSinCosMax64));
 }
 
 }  // namespace pft

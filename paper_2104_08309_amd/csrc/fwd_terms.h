@@ -79,12 +79,6 @@ __device__ __forceinline__ void fwd_face_f64(const Face64& f, const double (*Q)[
   }
 }
 
-// Whether an origin phase Q.g of a wavefront can exceed the range of sincos64: |g| <= R, the mesh's radius (qmax2
-// the lane's largest |Q|^2). NaN counts as beyond.
-__device__ __forceinline__ bool big_phases64(double qmax2, double R) {
-  return __any(!(sqrt(qmax2) * R <= 0.999 * kSinCosMax64));
-}
-
 // ---------------------------------------------------------------------------
 // FP32-compensated per-(Q, face) term
 // ---------------------------------------------------------------------------

@@ -74,7 +74,11 @@ constexpr int kQPTBatch = PFT_QPT_BATCH;  // Q per thread in the batched FP32C f
 #ifndef PFT_QPTB
 #define PFT_QPTB 3
 #endif
-constexpr int kQPTB = PFT_QPTB;    // Q per thread per pass in the adjoint
+constexpr int kQPTB = PFT_QPTB;    // Q per thread per pass in the FP32C adjoint
+#ifndef PFT_QPTB64
+#define PFT_QPTB64 2
+#endif
+constexpr int kQPTB64 = PFT_QPTB64;  // Q per thread per pass in the binary64 adjoint
 #ifndef PFT_TILEFB32
 #define PFT_TILEFB32 8
 #endif
@@ -513,7 +517,7 @@ hipError_t launch_batch_fwd_finish(const double2* partial, const int64_t* d_q_of
                                    int out_c128, void* out, void* intensity, hipStream_t s);
 hipError_t launch_batch_bwd(int mode, const BatchItemBwd* items, int64_t n_items, uint32_t* counter,
                             const Face64* f64, const double* gram, const Face32B* f32b, const QRec32* rec,
-                            const QRec64* rec64, double* partial, int grid, hipStream_t s);
+                            const QRec64* rec64, const MeshInfo* info, double* partial, int grid, hipStream_t s);
 hipError_t launch_batch_bwd_reduce(const double* partial, const int64_t* d_face_base, const int32_t* d_face_nchunks,
                                    const int64_t* d_tri_off, const int32_t* d_face_mesh, const Face64* f64,
                                    int64_t nf_total, double* contrib, hipStream_t s);
