@@ -4,7 +4,6 @@
 #pragma once
 
 #include "face_moments.h"
-#include "moment_poly.h"
 #include "pft_device.h"
 
 namespace pft {
@@ -22,90 +21,9 @@ PFT_HD __forceinline__ double dsinc_series(double x) {
 // Barycentric moments of a triangle from its centred vertex phases d0 + d1 + d2 = 0 (d_k = Q.(v_k - g)):
 //   Y_k = sum_n i^n h_n(d0, d1, d2, d_k) / (n+3)!   (k = 0, 1),
 //   J   = sum_n i^n h_n(d0, d1, d2) / (n+2)!         (so Y_2 = J - Y_0 - Y_1).
-// In binary32 from a polynomial q(x) = sum_n i^n a_n x^n of exp(ix)
-// fitted on [-M, M] (moment_poly.h): J = sum_n i^n a_n n! H_n / (n+2)! and
-// Y_k = sum_n i^n a_n n! h_n(d0, d1, d2, d_k) / (n+3)!, exact for q, so the error is
-// the simplex average of q - exp(ix) at phases within [-M, M] (J within err/2, Y_k
-// within err/6) for every lane with max |d_k| <= M. The degree is fixed by P.
-template <class P>
-__device__ __forceinline__ void bary_moments_poly(float d0, float d1, float* yr, float* yi, float& jr, float& ji) {
-  static_assert(P::N >= 5, "the first five terms are written out");
-  const float d2 = -d0 - d1;
-  const float e2 = d0 * d1 + d2 * (d0 + d1);
-  const float e3 = d0 * d1 * d2;
-  // n = 0..4 written out: H_0 = 1, H_1 = 0, H_2 = -e2, H_3 = e3, H_4 = e2^2
-  const float H2 = -e2, H3 = e3, H4 = e2 * e2;
-  float a0 = d0, a1 = d1;  // h_1(d0,d1,d2,d_k) = d_k (H_1 = 0)
-  float y0r = P::cy[0], y1r = P::cy[0];
-  jr = P::cj[0];
-  float y0i = P::cy[1] * a0, y1i = P::cy[1] * a1;
-  a0 = H2 + d0 * a0;
-  a1 = H2 + d1 * a1;
-  y0r -= P::cy[2] * a0;
-  y1r -= P::cy[2] * a1;
-  jr -= P::cj[2] * H2;
-  a0 = H3 + d0 * a0;
-  a1 = H3 + d1 * a1;
-  y0i -= P::cy[3] * a0;
-  y1i -= P::cy[3] * a1;
-  ji = -P::cj[3] * H3;
-  a0 = H4 + d0 * a0;
-  a1 = H4 + d1 * a1;
-  y0r += P::cy[4] * a0;
-  y1r += P::cy[4] * a1;
-  jr += P::cj[4] * H4;
-  float Hm3 = H2, Hm2 = H3, Hm1 = H4;  // H_{n-3}, H_{n-2}, H_{n-1} at n = 5
-#pragma unroll
-  for (int n = 5; n <= P::N; ++n) {
-    const float H = -e2 * Hm2 + e3 * Hm3;
-    a0 = H + d0 * a0;
-    a1 = H + d1 * a1;
-    const float c3 = P::cy[n], c2 = P::cj[n];
-    // i^n cycles (+i, -1, -i, +1) over n = 1, 2, 3, 0 (mod 4)
-    if ((n & 3) == 1) {
-      y0i += c3 * a0; y1i += c3 * a1; ji += c2 * H;
-    } else if ((n & 3) == 2) {
-      y0r -= c3 * a0; y1r -= c3 * a1; jr -= c2 * H;
-    } else if ((n & 3) == 3) {
-      y0i -= c3 * a0; y1i -= c3 * a1; ji -= c2 * H;
-    } else {
-      y0r += c3 * a0; y1r += c3 * a1; jr += c2 * H;
-    }
-    Hm3 = Hm2;
-    Hm2 = Hm1;
-    Hm1 = H;
-  }
-  yr[0] = y0r; yi[0] = y0i;
-  yr[1] = y1r; yi[1] = y1i;
-}
-
-// Binary32 moments for the lanes that take the series branch (max |d_k| = m <= 3):
-// the wavefront takes the lowest-degree polynomial whose range covers the largest m
-// among its active lanes (a wavefront-uniform choice, so no lane waits on another's
-// branch), after at most three comparisons.
-static_assert(kSeriesMaxPhase <= kMomentPolyMaxPhase, "the series branch must stay within the fitted range");
-__device__ __forceinline__ void bary_moments_f32(float d0, float d1, float m, float* yr, float* yi, float& jr,
-                                                 float& ji) {
-  static_assert(kMomentPolyBuckets == 7, "the dispatch below names seven polynomials");
-  if (__any(m > MomentPoly3::M)) {
-    if (__any(m > MomentPoly5::M))
-      bary_moments_poly<MomentPoly6>(d0, d1, yr, yi, jr, ji);
-    else if (__any(m > MomentPoly4::M))
-      bary_moments_poly<MomentPoly5>(d0, d1, yr, yi, jr, ji);
-    else
-      bary_moments_poly<MomentPoly4>(d0, d1, yr, yi, jr, ji);
-  } else if (__any(m > MomentPoly1::M)) {
-    if (__any(m > MomentPoly2::M))
-      bary_moments_poly<MomentPoly3>(d0, d1, yr, yi, jr, ji);
-    else
-      bary_moments_poly<MomentPoly2>(d0, d1, yr, yi, jr, ji);
-  } else {
-    if (__any(m > MomentPoly0::M))
-      bary_moments_poly<MomentPoly1>(d0, d1, yr, yi, jr, ji);
-    else
-      bary_moments_poly<MomentPoly0>(d0, d1, yr, yi, jr, ji);
-  }
-}
+// They come from the fitted symmetric polynomials (face_moments.h) for max |d_k| <= kSeriesMaxPhase and from the
+// edge form below beyond.
+static_assert(FaceFit64::M == kSeriesMaxPhase && FaceFit32M::M == kSeriesMaxPhase, "fitted range of the moments");
 
 // Edge form of the barycentric moments (|Q.(v - g)| beyond the series range):
 // the moment of corner k relative to exp(iQ.g), normalised by 2A, is
@@ -190,12 +108,14 @@ __device__ __forceinline__ void far_moments_f64(Fit64 t, const Face64& f, const 
   ji = Sr * inv;
 }
 
-// One face against a thread's P Q points, binary64: with z = conj(g) exp(iQ.g), adds Re(z Y_0), Re(z Y_1) and
-// Re(z J) (Y_2 = J - Y_0 - Y_1 is taken once per face in adj_block_sum) to S. Y_k = alpha + beta d_k + gamma d_k^2
-// only enters through Re(z .), so three real combinations of the six fitted functions serve all corners. The edge
+// One face against a thread's P Q points, binary64: with z = conj(g) exp(iQ.g), adds Re z(Y_0 - Y_2), Re z(Y_1 - Y_2)
+// and Re(z J) to S (adj_block_sum turns their sums into the corners' Re(z Y_k)). With Y_k = alpha + beta d_k + gamma
+// d_k^2, Y_0 - Y_2 = (d_0 - d_2)(beta - gamma d_1) and Y_1 - Y_2 = (d_1 - d_2)(beta - gamma d_0): three real
+// combinations of the six fitted functions serve all corners and alpha drops out. The edge
 // form beyond the fitted range; the choice is per lane. An empty record (N = 0, phases 0) gives finite weights that
-// the vertex gather multiplies by N = 0. Bound by binary64 issue, about 165 instructions per pair against some 300 of
-// the series in n (5 120 faces x 64 000 Q: kernel 3.41 -> 2.41 ms under the profiler); with P = 2 a coefficient is
+// the vertex gather multiplies by N = 0. Bound by binary64 issue, about 160 instructions per pair against some 300 of
+// the series in n (5 120 faces x 64 000 Q: kernel 3.41 -> 2.41 ms under the profiler, and fitting step 3.22 -> 3.08 ms
+// with the differences in place of the corners); with P = 2 a coefficient is
 // read once for two pairs (3 and 4 points: 9 % and 0.5 % slower fitting step, fewer wavefronts in flight).
 template <int P>
 __device__ __forceinline__ void adj_face_f64(const Face64& f, const double* G, const double (*Q)[3], const double* gr,
@@ -228,10 +148,9 @@ __device__ __forceinline__ void adj_face_f64(const Face64& f, const double* G, c
     const double a = zr[k] * A[k] - ei * B[k];           // Re(z J)
     const double b = er * br[k] - zi[k] * bi[k];         // Re(z beta)
     const double c = zr[k] * cr[k] - ei * ci[k];         // Re(z gamma)
-    const double al = (a - 2.0 * p * c) * (1.0 / 3.0);
     A[k] = a;
-    B[k] = al + d0[k] * (b + d0[k] * c);
-    bi[k] = al + d1[k] * (b + d1[k] * c);
+    B[k] = (d0[k] + s) * (b - c * d1[k]);
+    bi[k] = (d1[k] + s) * (b - c * d0[k]);
   }
   if (any) {
 #pragma unroll
@@ -239,9 +158,11 @@ __device__ __forceinline__ void adj_face_f64(const Face64& f, const double* G, c
       if (fmax(fabs(d0[k]), fmax(fabs(d1[k]), fabs(d0[k] + d1[k]))) > FaceFit64::M) {
         double yr[2], yi[2], jr, ji;
         far_moments_f64(t, f, G, Q[k], d0[k], d1[k], yr, yi, jr, ji);
-        B[k] = zr[k] * yr[0] - zi[k] * yi[0];
-        bi[k] = zr[k] * yr[1] - zi[k] * yi[1];
+        const double R0 = zr[k] * yr[0] - zi[k] * yi[0], R1 = zr[k] * yr[1] - zi[k] * yi[1];
         A[k] = zr[k] * jr - zi[k] * ji;
+        const double R2 = A[k] - R0 - R1;
+        B[k] = R0 - R2;
+        bi[k] = R1 - R2;
       }
   }
 #pragma unroll
@@ -329,38 +250,76 @@ __device__ __forceinline__ void edge_moments_fp32c(const Face32B& f, float Px, f
   }
 }
 
-__device__ __forceinline__ void adj_term_fp32c(const Face32B& f, float qx, float qy, float qz, float Q2,
-                                               const double* Qd, float gr, float gi, float* R) {
-  const float N0 = f.N[0], N1 = f.N[1], N2 = f.N[2];
-  const float Px = qy * N2 - qz * N1;
-  const float Py = qz * N0 - qx * N2;
-  const float Pz = qx * N1 - qy * N0;
-  const float P2 = Px * Px + Py * Py + Pz * Pz;
-  const double ph = Qd[0] * f.gt[0] + Qd[1] * f.gt[1] + Qd[2] * f.gt[2];
-  const float r = (float)(ph - rint(ph));
-  const float cf = cos_turns(r), sf = sin_turns(r);
-  const float zr = gr * cf + gi * sf;
-  const float zi = gr * sf - gi * cf;
-  const float q0 = qx * f.u0[0] + qy * f.u0[1] + qz * f.u0[2];  // delta_k = Q.u_k
-  const float q1 = qx * f.u1[0] + qy * f.u1[1] + qz * f.u1[2];
-  const float q2 = -q0 - q1;
-  const float m = fmaxf(fabsf(q0), fmaxf(fabsf(q1), fabsf(q2)));
-  // (an empty face has an all-zero record: m = 0, finite weights, times N = 0 later)
-  if (m <= (float)kSeriesMaxPhase) {
-    // barycentric moments in binary32 from the fitted polynomial of exp(ix) (every
-    // term is bounded for |delta| <= 3; no cancellation with the face's size in Q)
-    float yr[2], yi[2], jr, ji;
-    bary_moments_f32(q0, q1, m, yr, yi, jr, ji);
-    R[0] = zr * yr[0] - zi * yi[0];
-    R[1] = zr * yr[1] - zi * yi[1];
-    R[2] = (zr * jr - zi * ji) - R[0] - R[1];
-    return;
-  }
-  const float inv = rcp_f(fmaxf(P2, 1e-30f));
+// The edge form's moments of one pair in binary32: Y_0, Y_1 and J relative to exp(iQ.g).
+__device__ __forceinline__ void far_moments_fp32c(const Face32B& f, float qx, float qy, float qz, float d0, float d1,
+                                                  float* yr, float* yi, float& jr, float& ji) {
+  const float Px = qy * f.N[2] - qz * f.N[1];
+  const float Py = qz * f.N[0] - qx * f.N[2];
+  const float Pz = qx * f.N[1] - qy * f.N[0];
+  const float inv = rcp_f(fmaxf(Px * Px + Py * Py + Pz * Pz, 1e-30f));
   float Xr[3], Xi[3], Sr, Si;
-  edge_moments_fp32c(f, Px, Py, Pz, q0, q1, inv, Xr, Xi, Sr, Si);
+  edge_moments_fp32c(f, Px, Py, Pz, d0, d1, inv, Xr, Xi, Sr, Si);
+  for (int k = 0; k < 2; ++k) yr[k] = Xr[k] * inv, yi[k] = Xi[k] * inv;
+  jr = -Si * inv;
+  ji = Sr * inv;
+}
+
+// One face against a thread's P Q points in binary32, the sums of adj_face_f64. Bound by FP32 issue: per pair 12
+// operations for the phases and their symmetric functions, 32 for the six fitted functions, 17 for the products and
+// sums, 2 transcendentals and 3 binary64 multiply-adds (origin_turns); the one-variable recurrences it replaced took
+// some 15 more (5 120 faces x 262 144 Q: fitting step 3.21 -> 3.09 ms; 6 400 x 91 125 with grad_Q 3.67 -> 3.26 ms). An empty face has an all-zero record: finite
+// weights, times N = 0 in the vertex gather.
+template <int P>
+__device__ __forceinline__ void adj_face_fp32c(const Face32B& f, const float* qx, const float* qy, const float* qz,
+                                               const double (*Qd)[3], const float* gr, const float* gi, bool wide,
+                                               float* S) {
+  float d0[P], d1[P], zr[P], zi[P], a[P], D0[P], D1[P], r[P], cf[P], sf[P];
+  bool any = false;
 #pragma unroll
-  for (int k = 0; k < 3; ++k) R[k] = (zr * Xr[k] - zi * Xi[k]) * inv;
+  for (int k = 0; k < P; ++k) r[k] = wide ? origin_turns_plain(Qd[k], f.gt) : origin_turns(Qd[k], f.gt);
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    cf[k] = cos_turns(r[k]);
+    sf[k] = sin_turns(r[k]);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    zr[k] = gr[k] * cf[k] + gi[k] * sf[k];
+    zi[k] = gr[k] * sf[k] - gi[k] * cf[k];
+    d0[k] = qx[k] * f.u0[0] + qy[k] * f.u0[1] + qz[k] * f.u0[2];
+    d1[k] = qx[k] * f.u1[0] + qy[k] * f.u1[1] + qz[k] * f.u1[2];
+    const float s = d0[k] + d1[k];
+    const float p = d0[k] * s + d1[k] * d1[k], E = d0[k] * d1[k] * s, w = E * E;
+    any |= fmaxf(fabsf(d0[k]), fmaxf(fabsf(d1[k]), fabsf(s))) > (float)FaceFit32M::M;
+    const Moments32 m = face_moments32(p, w);
+    const float er = zr[k] * E, ei = zi[k] * E;
+    a[k] = zr[k] * m.A - ei * m.B;                 // Re(z J)
+    const float b = er * m.br - zi[k] * m.bi;      // Re(z beta)
+    const float c = zr[k] * m.gr - ei * m.gi;      // Re(z gamma)
+    D0[k] = (d0[k] + s) * (b - c * d1[k]);
+    D1[k] = (d1[k] + s) * (b - c * d0[k]);
+  }
+  if (__builtin_expect(any, 0)) {
+#pragma unroll
+    for (int k = 0; k < P; ++k)
+      if (fmaxf(fabsf(d0[k]), fmaxf(fabsf(d1[k]), fabsf(d0[k] + d1[k]))) > (float)FaceFit32M::M) {
+        float yr[2], yi[2], jr, ji;
+        far_moments_fp32c(f, qx[k], qy[k], qz[k], d0[k], d1[k], yr, yi, jr, ji);
+        const float R0 = zr[k] * yr[0] - zi[k] * yi[0], R1 = zr[k] * yr[1] - zi[k] * yi[1];
+        a[k] = zr[k] * jr - zi[k] * ji;
+        const float R2 = a[k] - R0 - R1;
+        D0[k] = R0 - R2;
+        D1[k] = R1 - R2;
+      }
+  }
+#pragma unroll
+  for (int k = 0; k < P; ++k) {
+    S[0] += D0[k];
+    S[1] += D1[k];
+    S[2] += a[k];
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -435,12 +394,13 @@ __device__ __forceinline__ void adj_tile_f64(const Face64* tile, const double (*
 // no cross-lane traffic happens per face.
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ void adj_tile_fp32c(const Face32B* tile, int nt, int64_t qb, int64_t qe,
-                                               const QRec32* __restrict__ rec, float (*acc)[kBlock]) {
+                                               const QRec32* __restrict__ rec, double R, float (*acc)[kBlock]) {
   constexpr int P = kQPTB;
   const int tid = threadIdx.x;
   for (int64_t q0 = qb; q0 < qe; q0 += (int64_t)kBlock * P) {
     double Qd[P][3];
-    float qx[P], qy[P], qz[P], Q2[P], hr[P], hi[P];
+    float qx[P], qy[P], qz[P], hr[P], hi[P];
+    bool wide = false;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int64_t qi = q0 + (int64_t)p * kBlock + tid;
@@ -457,19 +417,12 @@ __device__ __forceinline__ void adj_tile_fp32c(const Face32B* tile, int nt, int6
       qx[p] = (float)Qd[p][0];
       qy[p] = (float)Qd[p][1];
       qz[p] = (float)Qd[p][2];
-      Q2[p] = qx[p] * qx[p] + qy[p] * qy[p] + qz[p] * qz[p];
+      wide |= wide_phases32(Qd[p][0] * Qd[p][0] + Qd[p][1] * Qd[p][1] + Qd[p][2] * Qd[p][2], R);
     }
 #pragma unroll 1
     for (int j = 0; j < nt; ++j) {
       float S[3] = {0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int p = 0; p < P; ++p) {
-        float R[3];
-        adj_term_fp32c(tile[j], qx[p], qy[p], qz[p], Q2[p], Qd[p], hr[p], hi[p], R);
-        S[0] += R[0];
-        S[1] += R[1];
-        S[2] += R[2];
-      }
+      adj_face_fp32c<P>(tile[j], qx, qy, qz, Qd, hr, hi, wide, S);
       // private slots: a plain read-modify-write (an LDS atomic add is far slower)
 #pragma unroll
       for (int k = 0; k < 3; ++k) acc[3 * j + k][tid] += S[k];
@@ -478,10 +431,9 @@ __device__ __forceinline__ void adj_tile_fp32c(const Face32B* tile, int nt, int6
 }
 
 // Sum of the per-thread slots of adj_tile_fp32c / adj_tile_f64 for each of the nt faces, in binary64 and a fixed
-// order; wave w handles faces w, w + 4, ... and lane 0 writes the corner weights out[3 j + k]. kFaceSum: the third
-// slot holds the face integral's weight, corner 2 is that less the other two (binary64; in binary32 the subtraction
-// after the sum would leave corner 2 the rounding of a three times larger sum). Call after a barrier.
-template <bool kFaceSum, typename T>
+// order; wave w handles faces w, w + 4, ... and lane 0 writes the corner weights out[3 j + k]: from the sums D_0, D_1
+// of Re z(Y_0 - Y_2), Re z(Y_1 - Y_2) and a of Re(z J) = Re z(Y_0 + Y_1 + Y_2). Call after a barrier.
+template <typename T>
 __device__ __forceinline__ void adj_block_sum(T (*acc)[kBlock], int nt, double* out) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int j = wave; j < nt; j += kBlock / 64) {
@@ -494,9 +446,10 @@ __device__ __forceinline__ void adj_block_sum(T (*acc)[kBlock], int nt, double* 
       x[k] = wave_total(x[k]);
     }
     if (lane == 0) {
-      out[3 * j] = x[0];
-      out[3 * j + 1] = x[1];
-      out[3 * j + 2] = kFaceSum ? x[2] - x[0] - x[1] : x[2];
+      const double R2 = (x[2] - x[0] - x[1]) * (1.0 / 3.0);
+      out[3 * j] = R2 + x[0];
+      out[3 * j + 1] = R2 + x[1];
+      out[3 * j + 2] = R2;
     }
   }
 }

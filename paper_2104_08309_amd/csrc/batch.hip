@@ -265,7 +265,7 @@ __global__ __launch_bounds__(kBlock) void batch_bwd_fp64_kernel(const BatchItemB
     __syncthreads();
     adj_tile_f64(tile, gtile, nt, it.q0, it.q0 + it.nq, rec, info[it.mesh].R, acc);
     __syncthreads();
-    adj_block_sum<true>(acc, nt, partial + it.part * 3);
+    adj_block_sum(acc, nt, partial + it.part * 3);
     __syncthreads();
   }
 }
@@ -273,7 +273,8 @@ __global__ __launch_bounds__(kBlock) void batch_bwd_fp64_kernel(const BatchItemB
 __global__ __launch_bounds__(kBlock) void batch_bwd_fp32c_kernel(const BatchItemBwd* __restrict__ items,
                                                                 int64_t n_items, uint32_t* counter,
                                                                 const Face32B* __restrict__ f32b,
-                                                                const QRec32* __restrict__ rec, double* partial) {
+                                                                const QRec32* __restrict__ rec,
+                                                                const MeshInfo* __restrict__ info, double* partial) {
   __shared__ Face32B tile[kTileFB32];
   __shared__ float acc[kTileFB32 * 3][kBlock];
   __shared__ int slot;
@@ -287,9 +288,9 @@ __global__ __launch_bounds__(kBlock) void batch_bwd_fp32c_kernel(const BatchItem
       reinterpret_cast<uint4*>(tile)[i] = reinterpret_cast<const uint4*>(f32b + it.f0)[i];
     for (int v = 0; v < nt * 3; ++v) acc[v][tid] = 0.0f;
     __syncthreads();
-    adj_tile_fp32c(tile, nt, it.q0, it.q0 + it.nq, rec, acc);
+    adj_tile_fp32c(tile, nt, it.q0, it.q0 + it.nq, rec, info[it.mesh].R, acc);
     __syncthreads();
-    adj_block_sum<false>(acc, nt, partial + it.part * 3);
+    adj_block_sum(acc, nt, partial + it.part * 3);
     __syncthreads();
   }
 }
@@ -379,7 +380,7 @@ hipError_t launch_batch_bwd(int mode, const BatchItemBwd* items, int64_t n_items
   if (mode == PFT_FP64)
     batch_bwd_fp64_kernel<<<grid, kBlock, 0, s>>>(items, n_items, counter, f64, gram, rec64, info, partial);
   else
-    batch_bwd_fp32c_kernel<<<grid, kBlock, 0, s>>>(items, n_items, counter, f32b, rec, partial);
+    batch_bwd_fp32c_kernel<<<grid, kBlock, 0, s>>>(items, n_items, counter, f32b, rec, info, partial);
   return hipGetLastError();
 }
 

@@ -9,18 +9,17 @@
 //   dL/dv_k = sum_{m ∋ k} N_m R_{m,k},   R_{m,k} = Re sum_Q conj(g(Q)) B_{m,k}(Q) / |N_m|.
 //
 // Writing Bt_k = B_{m,k} / |N_m| = exp(iQ.g) Y_k, Y_k is evaluated either
-//  (series)    Y_k = sum_n i^n h_n(delta_a, delta_b, delta_c, delta_k) / (n+3)!,
-//              the barycentric moment of the simplex (node k doubled); the binary32
-//              form replaces 1/n! by the coefficients of a polynomial of exp(ix)
-//              fitted on the lanes' phase range and stops at its degree, or
+//  (fitted)    Y_k = sum_n i^n h_n(delta_a, delta_b, delta_c, delta_k) / (n+3)!,
+//              the barycentric moment of the simplex (node k doubled), as a quadratic in
+//              delta_k with symmetric coefficients fitted by polynomials (face_poly.h), or
 //  (edge form) from lambda_k = 1/3 + beta_k.(r - g), beta_k = N x d_{k+1} / |N|^2,
 //              and the centred face integral J_c = i |N| S / |P|^2 differentiated in Q:
 //              |P|^2 Y_k = (i/2) S + sum_l (d_{k+1}.d_l) sinc_l e_l
 //                          + (w_{k-1} sinc'_{k-1} e_{k-1} - w_k sinc'_k e_k) / 2
 //                          - (i/2) w_{k+1} sinc_{k+1} e_{k+1} - 2 S w_{k+1} / |P|^2,
 //              with w_l = P.d_l, e_l = exp(-i psi_{l+2}), S = sum_l w_l sinc_l e_l.
-// The series is used where |Q_perp| L is small (it has no cancellation there;
-// the edge form cancels like 1/(|Q_perp| L)^2).
+// The fitted form is used where |Q_perp| L is small (it has no cancellation
+// there; the edge form cancels like 1/(|Q_perp| L)^2).
 //
 // Layout: a block owns a tile of faces (records in LDS) and loops over a
 // range of Q (a Q-split), kQPTB Q per thread per pass; the grid is one-
@@ -69,7 +68,7 @@ __global__ __launch_bounds__(kBlock) void bwd3d_fp64_kernel(BwdArgs a, const dou
   const int64_t qe = min(a.nq, qb + a.q_per_split);
   adj_tile_f64(tile, gtile, nt, qb, qe, a.rec64, a.info[0].R, acc);
   __syncthreads();
-  adj_block_sum<true>(acc, nt, a.partial + (qs * a.nf + f0) * 3);
+  adj_block_sum(acc, nt, a.partial + (qs * a.nf + f0) * 3);
 }
 
 __global__ __launch_bounds__(kBlock) void bwd3d_fp32c_kernel(BwdArgs a) {
@@ -86,9 +85,9 @@ __global__ __launch_bounds__(kBlock) void bwd3d_fp32c_kernel(BwdArgs a) {
   __syncthreads();
   const int64_t qb = qs * a.q_per_split;
   const int64_t qe = min(a.nq, qb + a.q_per_split);
-  adj_tile_fp32c(tile, nt, qb, qe, a.rec, acc);
+  adj_tile_fp32c(tile, nt, qb, qe, a.rec, a.info[0].R, acc);
   __syncthreads();
-  adj_block_sum<false>(acc, nt, a.partial + (qs * a.nf + f0) * 3);
+  adj_block_sum(acc, nt, a.partial + (qs * a.nf + f0) * 3);
 }
 
 __global__ __launch_bounds__(256) void gram64_kernel(const Face64* f64, int64_t nf, double* gram) {

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp32c_kernel(DqArgs a) {
   double Qd[P][3];
   float qx[P], qy[P], qz[P];
   bool small[P], active[P];
-  bool any_small = false;
+  bool any_small = false, wide = false;
 #pragma unroll
   for (int k = 0; k < P; ++k) {
     const int64_t qi = qbase + (int64_t)k * kBlock;
@@ -100,8 +100,10 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp32c_kernel(DqArgs a) {
     qx[k] = (float)Qd[k][0];
     qy[k] = (float)Qd[k][1];
     qz[k] = (float)Qd[k][2];
-    small[k] = sqrt(Qd[k][0] * Qd[k][0] + Qd[k][1] * Qd[k][1] + Qd[k][2] * Qd[k][2]) * R < a.tau;
+    const double Q2 = Qd[k][0] * Qd[k][0] + Qd[k][1] * Qd[k][1] + Qd[k][2] * Qd[k][2];
+    small[k] = sqrt(Q2) * R < a.tau;
     any_small |= small[k];
+    wide |= wide_phases32(Q2, a.info[0].R);
   }
   int64_t f_begin, f_end;
   split_range(a, f_begin, f_end);
@@ -129,7 +131,7 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp32c_kernel(DqArgs a) {
     for (int j = 0; j < nt; ++j) {
       const Face32B f = tile[j];
 #pragma unroll
-      for (int k = 0; k < P; ++k) dq_term_fp32c(f, qx[k], qy[k], qz[k], Qd[k], Ar[k], Ai[k], Br[k], Bi[k]);
+      for (int k = 0; k < P; ++k) dq_term_fp32c(f, qx[k], qy[k], qz[k], Qd[k], wide, Ar[k], Ai[k], Br[k], Bi[k]);
     }
 #pragma unroll
     for (int k = 0; k < P; ++k) {

@@ -143,48 +143,46 @@ __device__ __forceinline__ void dq_term_f64(const Face64& f, const double* G, co
   Bi += cr * ji + ci * jr;
 }
 
-// FP32C surface term of face f (record of the FP32C adjoint), the same sums in binary32.
+// FP32C surface term of face f (record of the FP32C adjoint), the same sums in binary32 as
+//   sum_k (v_k - t) Y_k = g J + u_0 (Y_0 - Y_2) + u_1 (Y_1 - Y_2),
+// with the differences in the adjoint's form (d_0 - d_2)(beta - gamma d_1), (d_1 - d_2)(beta - gamma d_0). (An empty
+// face has an all-zero record: N = 0 makes its terms 0.)
 __device__ __forceinline__ void dq_term_fp32c(const Face32B& f, float qx, float qy, float qz, const double* Qd,
-                                              float* Ar, float* Ai, float& Br, float& Bi) {
-  const float N0 = f.N[0], N1 = f.N[1], N2 = f.N[2];
-  const float Px = qy * N2 - qz * N1;
-  const float Py = qz * N0 - qx * N2;
-  const float Pz = qx * N1 - qy * N0;
-  const float P2 = Px * Px + Py * Py + Pz * Pz;
-  const double ph = Qd[0] * f.gt[0] + Qd[1] * f.gt[1] + Qd[2] * f.gt[2];
-  const float r = (float)(ph - rint(ph));
+                                              bool wide, float* Ar, float* Ai, float& Br, float& Bi) {
+  const float r = wide ? origin_turns_plain(Qd, f.gt) : origin_turns(Qd, f.gt);
   const float cf = cos_turns(r), sf = sin_turns(r);
-  const float QN = qx * N0 + qy * N1 + qz * N2;
-  const float q0 = qx * f.u0[0] + qy * f.u0[1] + qz * f.u0[2];
-  const float q1 = qx * f.u1[0] + qy * f.u1[1] + qz * f.u1[2];
-  const float m = fmaxf(fabsf(q0), fmaxf(fabsf(q1), fabsf(q0 + q1)));
-  // (an empty face has an all-zero record: N = 0 makes its terms 0)
-  float yr[2], yi[2], jr, ji;
-  if (m <= (float)kSeriesMaxPhase) {
-    bary_moments_f32(q0, q1, m, yr, yi, jr, ji);
-  } else {
-    const float inv = rcp_f(fmaxf(P2, 1e-30f));
-    float Xr[3], Xi[3], Sr, Si;
-    edge_moments_fp32c(f, Px, Py, Pz, q0, q1, inv, Xr, Xi, Sr, Si);
-    yr[0] = Xr[0] * inv;
-    yi[0] = Xi[0] * inv;
-    yr[1] = Xr[1] * inv;
-    yi[1] = Xi[1] * inv;
-    jr = -Si * inv;
-    ji = Sr * inv;
+  const float QN = qx * f.N[0] + qy * f.N[1] + qz * f.N[2];
+  const float d0 = qx * f.u0[0] + qy * f.u0[1] + qz * f.u0[2];
+  const float d1 = qx * f.u1[0] + qy * f.u1[1] + qz * f.u1[2];
+  const float s = d0 + d1;
+  const float p = d0 * s + d1 * d1, E = d0 * d1 * s, w = E * E;
+  const Moments32 m = face_moments32(p, w);
+  float jr = m.A, ji = E * m.B;
+  const float br = E * m.br, gi = E * m.gi;
+  const float t0 = d0 + s, t1 = d1 + s;
+  float ur = t0 * (br - m.gr * d1), ui = t0 * (m.bi - gi * d1);   // Y_0 - Y_2
+  float vr = t1 * (br - m.gr * d0), vi = t1 * (m.bi - gi * d0);   // Y_1 - Y_2
+  if (__builtin_expect(fmaxf(fabsf(d0), fmaxf(fabsf(d1), fabsf(s))) > (float)FaceFit32M::M, 0)) {
+    float yr[2], yi[2];
+    far_moments_fp32c(f, qx, qy, qz, d0, d1, yr, yi, jr, ji);
+    const float y2r = jr - yr[0] - yr[1], y2i = ji - yi[0] - yi[1];
+    ur = yr[0] - y2r;
+    ui = yi[0] - y2i;
+    vr = yr[1] - y2r;
+    vi = yi[1] - y2i;
   }
+  // times c = (Q.N) exp(iQ.g)
   const float cr = QN * cf, ci = QN * sf;
+  const float Jr = cr * jr - ci * ji, Ji = cr * ji + ci * jr;
+  const float Ur = cr * ur - ci * ui, Ui = cr * ui + ci * ur;
+  const float Vr = cr * vr - ci * vi, Vi = cr * vi + ci * vr;
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
-    const float e0 = 2.0f * f.u0[c] + f.u1[c];
-    const float e1 = f.u0[c] + 2.0f * f.u1[c];
-    const float vr = f.c2[c] * jr + e0 * yr[0] + e1 * yr[1];
-    const float vi = f.c2[c] * ji + e0 * yi[0] + e1 * yi[1];
-    Ar[c] += cr * vr - ci * vi;
-    Ai[c] += cr * vi + ci * vr;
+    Ar[c] += f.g[c] * Jr + f.u0[c] * Ur + f.u1[c] * Vr;
+    Ai[c] += f.g[c] * Ji + f.u0[c] * Ui + f.u1[c] * Vi;
   }
-  Br += cr * jr - ci * ji;
-  Bi += cr * ji + ci * jr;
+  Br += Jr;
+  Bi += Ji;
 }
 
 }  // namespace pft

@@ -117,25 +117,6 @@ __device__ __forceinline__ void fwd_face_f64(const Face64& f, const double (*Q)[
 constexpr int kAnchor = PFT_ANCHOR;  // faces between binary64 origin phases in a chain (divides kTileF32)
 static_assert(kTileF32 % kAnchor == 0, "the anchor interval divides the face tile");
 
-// sum_a C::c[a] x^a in binary32 by fused multiply-adds whose addend is the instruction's literal. (Left to
-// itself the compiler keeps a loop's coefficients in scalar registers, and a scalar source halves the issue
-// rate of a vector instruction on this target: 99 460 faces x 64 000 Q, 5.80 ms against 5.66 ms.)
-template <class C, int A>
-__device__ __forceinline__ float horner_lit_from(float s, float x) {
-  if constexpr (A < 0) {
-    return s;
-  } else {
-    float r;
-    asm("v_fmaak_f32 %0, %1, %2, %3" : "=v"(r) : "v"(s), "v"(x), "n"(__builtin_bit_cast(int, C::c[A])));
-    return horner_lit_from<C, A - 1>(r, x);
-  }
-}
-template <class C>
-__device__ __forceinline__ float horner_lit(float x) {
-  constexpr int N = sizeof(C::c) / sizeof(C::c[0]);
-  return horner_lit_from<C, N - 2>(C::c[N - 1], x);
-}
-
 // Largest |p_k| in the range of FaceFit32.
 constexpr float kFitMax32 = (float)(FaceFit32::M / 12.566370614359172954);
 

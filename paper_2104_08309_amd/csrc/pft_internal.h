@@ -96,10 +96,9 @@ constexpr double kTauF64 = 0.05;     // forward and adjoint, FP64 mode
 constexpr double kTauF32 = 0.1;      // forward, FP32C mode (series in FP64)
 constexpr double kTauRel32 = 0.02;   // polygon forward, FP32C mode, relative test
 constexpr double kTauB32 = 1.5;      // (record field of the FP32C adjoint; empty-face flag)
-// The adjoint evaluates each face's barycentric moments by their series (binary64)
-// or by a polynomial of exp(ix) fitted on [-3, 3] (binary32, moment_poly.h) when the
-// largest centred vertex phase |Q.(v_k - g)| is at most this, by the
-// differentiated edge sums otherwise (there |Q_perp| L > 4.5).
+// The adjoint evaluates each face's barycentric moments by the fitted symmetric polynomials (face_poly.h) when the
+// largest centred vertex phase |Q.(v_k - g)| is at most this, by the differentiated edge sums otherwise (there
+// |Q_perp| L > 4.5).
 #ifndef PFT_SERIES_MAX_PHASE
 #define PFT_SERIES_MAX_PHASE 3.0
 #endif
@@ -189,7 +188,7 @@ struct alignas(16) Face32B {
   float G[6];     // d0.d0, d1.d1, d2.d2, d0.d1, d1.d2, d2.d0
   float thr;      // tau_b^2 |N|^2 / L^2 (-1 for an empty face, whose record is otherwise all zero)
   float kap;      // tau_relb^2 |N|^2
-  float c2[3];    // c - t (vertex c relative to the mesh centre; used by grad_Q F)
+  float g[3];     // centroid relative to the mesh centre t (used by grad_Q F)
 };
 static_assert(sizeof(Face32B) == 128, "Face32B layout");
 

@@ -2,9 +2,7 @@
 //
 // Each Q is evaluated independently, so the kernels may visit the Q list in any
 // order. Their cost per (Q, face) follows the worst lane of a wavefront: the
-// adjoint's series runs until its largest vertex phase |Q.(v - g)| has
-// converged, and the forward's near-degenerate branch (Q nearly along a face
-// normal) runs whenever one lane needs it. Wavefronts of nearby Q waste less
+// edge form beyond the fitted phase range runs whenever one lane needs it. Wavefronts of nearby Q waste less
 // work than wavefronts spanning a grid row or a random set. The Q points are
 // sorted by mesh, then by the Morton code of their coordinates quantised
 // inside the bounding box of all Q (10 bits per axis; 5 for a single mesh,
