@@ -348,14 +348,14 @@ __device__ __forceinline__ double block_total(double v, double* lds) {
 
 // ---------------------------------------------------------------------------
 // binary64 adjoint, one block's share: `nt` face records in LDS (with their
-// edge Gram matrices) against the reordered Q records [qb, qe), kQPTB Q per
+// edge Gram matrices) against the reordered Q records [qb, qe), P Q per
 // thread per pass. Each thread adds its weights for face j to its own
 // binary64 slots acc[3 j + k][thread] (zeroed by the caller); adj_block_sum
 // reduces the slots once the range is done.
 // ---------------------------------------------------------------------------
+template <int P>
 __device__ __forceinline__ void adj_tile_f64(const Face64* tile, const double (*gtile)[8], int nt, int64_t qb,
                                              int64_t qe, const QRec64* __restrict__ rec, double R, double (*acc)[kBlock]) {
-  constexpr int P = kQPTB64;
   const int tid = threadIdx.x;
   for (int64_t q0 = qb; q0 < qe; q0 += (int64_t)kBlock * P) {
     double Qd[P][3];
@@ -388,14 +388,14 @@ __device__ __forceinline__ void adj_tile_f64(const Face64* tile, const double (*
 
 // ---------------------------------------------------------------------------
 // FP32C adjoint, one block's share: `nt` face records in LDS against the
-// reordered Q records [qb, qe), kQPTB Q per thread per pass. Each thread adds
+// reordered Q records [qb, qe), P Q per thread per pass. Each thread adds
 // its weights for face j to its own binary32 slots acc[3 j + k][thread] (zeroed
 // by the caller); adj_block_sum32 reduces the slots once the range is done, so
 // no cross-lane traffic happens per face.
 // ---------------------------------------------------------------------------
+template <int P>
 __device__ __forceinline__ void adj_tile_fp32c(const Face32B* tile, int nt, int64_t qb, int64_t qe,
                                                const QRec32* __restrict__ rec, double R, float (*acc)[kBlock]) {
-  constexpr int P = kQPTB;
   const int tid = threadIdx.x;
   for (int64_t q0 = qb; q0 < qe; q0 += (int64_t)kBlock * P) {
     double Qd[P][3];

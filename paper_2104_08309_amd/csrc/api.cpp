@@ -286,6 +286,7 @@ int time_candidates(int n, F run, hipStream_t s, std::vector<float>& ms) {
 // least min_faces faces per split.
 void choose_face_splits(int64_t nq, int64_t nf, int64_t qtile, int64_t min_faces, int64_t target, int* splits,
                         int64_t* per) {
+  const int64_t unit = std::min<int64_t>(min_faces, kTileF);  // splits are multiples of a tile, or of a finer cut
   if (nf <= 0) {
     *splits = 1;
     *per = 0;
@@ -293,17 +294,21 @@ void choose_face_splits(int64_t nq, int64_t nf, int64_t qtile, int64_t min_faces
   }
   const int64_t qblocks = cdiv(nq, qtile);
   int64_t s = std::max<int64_t>(1, std::min(cdiv(target, qblocks), cdiv(nf, min_faces)));
-  int64_t p = cdiv(cdiv(nf, s), kTileF) * kTileF;
+  int64_t p = cdiv(cdiv(nf, s), unit) * unit;
   *per = p;
   *splits = (int)cdiv(nf, p);
 }
 
 // How a forward of nq Q and nf faces is cut: Q per thread, least faces per split and target blocks.
 // A call whose blocks of at least kMinFacesPerSplit faces per wavefront would leave most of the chip idle is
-// cut finer, down to one tile of kTileF faces per block and, if that does not give kSmallBlocks blocks either,
-// one Q per thread: such a call is bound by the latency of its longest wavefront, not by issue. 320 faces x
-// 4 096 Q (32 blocks before, 320 now): 67.5 -> 27.8 us a call.
+// cut finer, down to kSmallFaces faces per block and, if that does not give kSmallBlocks blocks either, one Q
+// per thread: such a call is bound by the latency of its longest wavefront, not by issue. 320 faces x 4 096 Q
+// (32 blocks before): 67.5 us a call; cut to 64 faces per block and one Q per thread (320 blocks) 27.8 us.
 constexpr int64_t kSmallBlocks = 1024;  // four blocks of four wavefronts per CU
+#ifndef PFT_SMALL_FACES
+#define PFT_SMALL_FACES 16
+#endif
+constexpr int64_t kSmallFaces = PFT_SMALL_FACES;
 struct FwdPlan {
   int qpt;
   int64_t qtile, min_faces, target;
@@ -311,7 +316,7 @@ struct FwdPlan {
 FwdPlan fwd_plan(int64_t nq, int64_t nf, bool c128) {
   FwdPlan p{c128 ? kQPT64 : fwd_qpt(nq), 0, kMinFacesPerSplit * kFwdSplitWaves, c128 ? kTargetBlocks : kTargetBlocksF32};
   if (cdiv(nq, fwd_qtile(p.qpt)) * cdiv(nf, p.min_faces) < kSmallBlocks) {
-    p.min_faces = kTileF;
+    p.min_faces = kSmallFaces;
     p.target = kSmallBlocks;
     if (cdiv(nq, fwd_qtile(p.qpt)) * cdiv(nf, p.min_faces) < kSmallBlocks) p.qpt = 1;
   }
@@ -337,19 +342,21 @@ int64_t plan_forward(int64_t nq, int64_t nf, bool c128, int64_t max_partials, Fw
   return (int64_t)splits * nq;
 }
 
-// Q-splits of the vertex adjoint (blocks of `tile` faces): about kTargetBlocks blocks, at least kBlock Q per
-// split; from kXcds splits up, a multiple of kXcds, so that each die takes whole Q-splits.
-void choose_q_splits(int64_t nq, int64_t nf, int tile, int* splits, int64_t* per) {
-  const int64_t fblocks = std::max<int64_t>(1, cdiv(nf, tile));
-  const int64_t smax = std::max<int64_t>(1, cdiv(nq, kBlock));
-  int64_t s = std::max<int64_t>(1, std::min(cdiv(kTargetBlocks, fblocks), smax));
-  if (s >= kXcds) {
-    s = cdiv(s, kXcds) * kXcds;
-    if (s > smax) s -= kXcds;
+// How the vertex adjoint is cut (sets b.small and b.qsplits): about kTargetBlocks blocks of kTileFB faces, each split
+// at least one pass of kBlock * (Q per thread) Q; from kXcds splits up a multiple of kXcds, so that each die takes
+// whole Q-splits. A call that gives fewer than kSmallBlocks such blocks takes the small instance (one Q per thread, two
+// faces per block: four to twelve times the blocks, each with a quarter of the serial faces).
+void plan_adjoint(int64_t nq, int64_t nf, bool c128, BwdArgs& b) {
+  int64_t tile = c128 ? kTileFB : kTileFB32, pass = (int64_t)kBlock * (c128 ? kQPTB64 : kQPTB);
+  b.small = cdiv(nf, tile) * cdiv(nq, pass) < kSmallBlocks;
+  if (b.small) {
+    tile = kTileFBSmall;
+    pass = kBlock;
   }
-  const int64_t p = std::max<int64_t>(1, cdiv(nq, s));
-  *per = p;
-  *splits = (int)std::max<int64_t>(1, cdiv(nq, p));
+  const int64_t fblocks = std::max<int64_t>(1, cdiv(nf, tile));
+  int64_t s = std::max<int64_t>(1, std::min(cdiv(kTargetBlocks, fblocks), cdiv(nq, pass)));
+  if (s >= kXcds) s = s / kXcds * kXcds;
+  b.qsplits = (int)s;
 }
 
 int num_cus() {
@@ -553,12 +560,6 @@ pft_status qrecs_from_perm(Arena& ar, int mode, const void* q, int qdtype, const
                            QRec32** rec, QRec64** rec64, hipStream_t s) {
   *rec = nullptr;
   *rec64 = nullptr;
-  if (!perm) {  // identity order
-    perm = ar.get<uint32_t>(nq);
-    if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-    hipError_t e = launch_iota_u32(perm, nq, s);
-    if (e != hipSuccess) return hip_fail(e, "Q order");
-  }
   hipError_t e;
   if (mode == PFT_FP64) {
     *rec64 = ar.get<QRec64>(nq);
@@ -603,6 +604,20 @@ pft_status gather_tail(Arena& ar, const int32_t* tris, int64_t nf, const int64_t
   e = launch_gather_vertices(keys_s, vals_s, ns, contrib, nv_total, grad, vdtype, s);
   if (e != hipSuccess) return hip_fail(e, "vertex gather");
   return PFT_OK;
+}
+
+// The adjoint's end for one mesh: split sums to vertex gradients (face_w: a weight per face, or NULL).
+pft_status adjoint_tail(Arena& ar, const int32_t* tris, int64_t nf, int64_t nv, const double* partial, int qsplits,
+                        const Face64* f64, const double* face_w, void* grad, int vdtype, hipStream_t s) {
+  if (nf <= kSmallGatherFaces && nv <= 2 * kSmallGatherFaces) {
+    hipError_t e = launch_gather_small(tris, nf, nv, partial, qsplits, f64, face_w, grad, vdtype, s);
+    return e == hipSuccess ? PFT_OK : hip_fail(e, "vertex gather");
+  }
+  double* contrib = ar.get<double>((size_t)nf * 9);
+  if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
+  hipError_t e = launch_bwd_face_contrib(partial, qsplits, f64, face_w, nf, contrib, s);
+  if (e != hipSuccess) return hip_fail(e, "adjoint reduce");
+  return gather_tail(ar, tris, nf, nullptr, nullptr, nv, contrib, grad, vdtype, s);
 }
 
 }  // namespace
@@ -804,10 +819,8 @@ pft_status forward3d_core(Arena& ar, const void* verts, int vdtype, int64_t nv, 
   const int64_t n_partial = plan_forward(nq, nf, c128, max_partials, a);
   double2* partial = ar.get<double2>((size_t)n_partial);
   if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-  hipError_t e = launch_mesh_info_single(verts, vdtype, 3, nv, info, s);
-  if (e == hipSuccess)
-    e = launch_face64(verts, vdtype, nv, tris, nf, info, c128 ? kTauF64 : kTauF32, f64, s, order, meta);
-  if (e == hipSuccess && !c128) e = launch_face32(f64, nf, f32, s);
+  hipError_t e = launch_mesh_records(verts, vdtype, nv, tris, nf, info, c128 ? kTauF64 : kTauF32,
+                                     MeshRecords{f64, f32, nullptr, nullptr}, s, order, meta);
   if (e != hipSuccess) return hip_fail(e, "3D prologue");
   uint32_t* perm = nullptr;
   if (q_order)
@@ -1281,16 +1294,11 @@ static pft_status backward3d_impl(const void* verts, pft_dtype vdtype, int64_t n
   Face64* f64 = ar.get<Face64>(nf);
   Face32B* f32 = c128 ? nullptr : ar.get<Face32B>(nf);
   double* gram = c128 ? ar.get<double>((size_t)nf * 8) : nullptr;
-  int qs;
-  int64_t qper;
-  choose_q_splits(nq, nf, c128 ? kTileFB : kTileFB32, &qs, &qper);
-  double* partial = ar.get<double>((size_t)qs * nf * 3);
-  double* contrib = ar.get<double>((size_t)nf * 9);
+  BwdArgs a;
+  plan_adjoint(nq, nf, c128, a);
+  double* partial = ar.get<double>((size_t)a.qsplits * nf * 3);
   if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-  hipError_t e = launch_mesh_info_single(verts, vdtype, 3, nv, info, s);
-  if (e == hipSuccess) e = launch_face64(verts, vdtype, nv, tris, nf, info, kTauF64, f64, s);
-  if (e == hipSuccess && !c128) e = launch_face32b(f64, nf, kTauB32, kTauRelB32, f32, s);
-  if (e == hipSuccess && c128) e = launch_gram64(f64, nf, gram, s);
+  hipError_t e = launch_mesh_records(verts, vdtype, nv, tris, nf, info, kTauF64, MeshRecords{f64, nullptr, f32, gram}, s);
   if (e != hipSuccess) return hip_fail(e, "adjoint prologue");
   QRec32* rec = nullptr;
   QRec64* rec64 = nullptr;
@@ -1302,7 +1310,6 @@ static pft_status backward3d_impl(const void* verts, pft_dtype vdtype, int64_t n
     st = build_qrecs(ar, mode, q, qdtype, grad_out, nq, info, nullptr, 1, &rec, &rec64, s);
   }
   if (st != PFT_OK) return st;
-  BwdArgs a;
   a.info = info;
   a.f64 = f64;
   a.f32 = f32;
@@ -1313,17 +1320,13 @@ static pft_status backward3d_impl(const void* verts, pft_dtype vdtype, int64_t n
   a.grad_out = grad_out;
   a.rec = rec;
   a.rec64 = rec64;
-  a.qsplits = qs;
-  a.q_per_split = qper;
   a.partial = partial;
   const char* nm = main_name(false, mode);
   prof_begin(nm, s);
   e = c128 ? launch_bwd3d_fp64(a, gram, s) : launch_bwd3d_fp32c(a, s);
   prof_end(nm, s);
   if (e != hipSuccess) return hip_fail(e, "adjoint");
-  e = launch_bwd_face_contrib(partial, qs, f64, nullptr, nf, contrib, s);
-  if (e != hipSuccess) return hip_fail(e, "adjoint reduce");
-  return gather_tail(ar, tris, nf, nullptr, nullptr, nv, contrib, grad_verts, vdtype, s);
+  return adjoint_tail(ar, tris, nf, nv, partial, a.qsplits, f64, nullptr, grad_verts, vdtype, s);
 }
 
 pft_status pft_backward_3d(const void* verts, pft_dtype vdtype, int64_t nv, const int32_t* tris, int64_t nf,
@@ -1376,12 +1379,16 @@ pft_status pft_intensity_loss_3d(const void* verts, pft_dtype vdtype, int64_t nv
   QRec64* rec64 = c128 ? ar.get<QRec64>(nq) : nullptr;
   double* loss_part = ar.get<double>(loss_blocks(nq));
   if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-  e = launch_mesh_info_single(verts, vdtype, 3, nv, info, s);
-  // binary64 records with the binary64 series threshold (the FP32C forward takes its own from Face32)
-  if (e == hipSuccess) e = launch_face64(verts, vdtype, nv, tris, nf, info, kTauF64, f64, s);
+  // the adjoint's records with the mesh, and the ordered forward's own
+  const bool want_grad = grad_verts != nullptr && nv > 0 && nf > 0;
+  Face32B* f32b = want_grad && !c128 ? ar.get<Face32B>(nf) : nullptr;
+  double* gram = want_grad && c128 ? ar.get<double>((size_t)nf * 8) : nullptr;
+  if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
+  e = launch_mesh_records(verts, vdtype, nv, tris, nf, info, kTauF64,
+                          MeshRecords{f64, ordered ? nullptr : f32, f32b, gram}, s);
   if (e == hipSuccess && ordered)
-    e = launch_face64(verts, vdtype, nv, tris, nf, info, kTauF64, f64o, s, face_order, face_meta);
-  if (e == hipSuccess && !c128) e = launch_face32(f64o, nf, f32, s);
+    e = launch_mesh_records(verts, vdtype, nv, tris, nf, info, kTauF64, MeshRecords{f64o, f32, nullptr, nullptr}, s,
+                            face_order, face_meta);
   if (e != hipSuccess) return hip_fail(e, "loss prologue");
   uint32_t* perm = nullptr;
   if ((st = build_qorder(ar, q, qdtype, nq, nullptr, 1, &perm, s)) != PFT_OK) return st;
@@ -1411,17 +1418,10 @@ pft_status pft_intensity_loss_3d(const void* verts, pft_dtype vdtype, int64_t nv
     e = zero_bytes(grad_verts, (size_t)nv * 3 * real_size(vdtype), s);
     return e == hipSuccess ? PFT_OK : hip_fail(e, "zero grad");
   }
-  Face32B* f32b = c128 ? nullptr : ar.get<Face32B>(nf);
-  double* gram = c128 ? ar.get<double>((size_t)nf * 8) : nullptr;
-  int qs;
-  int64_t qper;
-  choose_q_splits(nq, nf, c128 ? kTileFB : kTileFB32, &qs, &qper);
-  double* bpart = ar.get<double>((size_t)qs * nf * 3);
-  double* contrib = ar.get<double>((size_t)nf * 9);
-  if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-  e = c128 ? launch_gram64(f64, nf, gram, s) : launch_face32b(f64, nf, kTauB32, kTauRelB32, f32b, s);
-  if (e != hipSuccess) return hip_fail(e, "adjoint prologue");
   BwdArgs b;
+  plan_adjoint(nq, nf, c128, b);
+  double* bpart = ar.get<double>((size_t)b.qsplits * nf * 3);
+  if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
   b.info = info;
   b.f64 = f64;
   b.f32 = f32b;
@@ -1432,17 +1432,13 @@ pft_status pft_intensity_loss_3d(const void* verts, pft_dtype vdtype, int64_t nv
   b.grad_out = nullptr;
   b.rec = rec;
   b.rec64 = rec64;
-  b.qsplits = qs;
-  b.q_per_split = qper;
   b.partial = bpart;
   nm = main_name(false, mode);
   prof_begin(nm, s);
   e = c128 ? launch_bwd3d_fp64(b, gram, s) : launch_bwd3d_fp32c(b, s);
   prof_end(nm, s);
   if (e != hipSuccess) return hip_fail(e, "adjoint");
-  e = launch_bwd_face_contrib(bpart, qs, f64, nullptr, nf, contrib, s);
-  if (e != hipSuccess) return hip_fail(e, "adjoint reduce");
-  return gather_tail(ar, tris, nf, nullptr, nullptr, nv, contrib, grad_verts, vdtype, s);
+  return adjoint_tail(ar, tris, nf, nv, bpart, b.qsplits, f64, nullptr, grad_verts, vdtype, s);
 }
 
 pft_status pft_forward_3d_regions(const void* verts, pft_dtype vdtype, int64_t nv, const int32_t* tris, int64_t nf,
@@ -1474,12 +1470,10 @@ pft_status pft_forward_3d_regions(const void* verts, pft_dtype vdtype, int64_t n
   Face32* f32 = c128 ? nullptr : ar.get<Face32>(std::max<int64_t>(nf, 1));
   double2* partial = ar.get<double2>((size_t)std::max(plan.splits, 1) * nq);
   if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-  hipError_t e = launch_mesh_info_single(verts, vdtype, 3, nv, info, s);
   const bool ordered = face_order != nullptr && !c128 && nf > 0;
-  if (e == hipSuccess)
-    e = launch_face64(verts, vdtype, nv, tris, nf, info, c128 ? kTauF64 : kTauF32, f64, s,
-                      ordered ? face_order : nullptr, ordered ? face_meta : nullptr);
-  if (e == hipSuccess && !c128) e = launch_face32(f64, nf, f32, s);
+  hipError_t e = launch_mesh_records(verts, vdtype, nv, tris, nf, info, c128 ? kTauF64 : kTauF32,
+                                     MeshRecords{f64, f32, nullptr, nullptr}, s, ordered ? face_order : nullptr,
+                                     ordered ? face_meta : nullptr);
   if (e != hipSuccess) return hip_fail(e, "3D prologue");
   double* region_R = nullptr;
   double4* split_geo = nullptr;
@@ -1556,19 +1550,13 @@ pft_status pft_backward_3d_regions(const void* verts, pft_dtype vdtype, int64_t 
   Arena ar(s);
   MeshInfo* info = ar.get<MeshInfo>(1);
   Face64* f64 = ar.get<Face64>(nf);
+  // the adjoint's records for dL/dv and dL/dQ; dL/drho alone takes the forward's
+  Face32B* f32b = (want_v || want_q) && !c128 ? ar.get<Face32B>(nf) : nullptr;
+  double* gram = (want_v || want_q) && c128 ? ar.get<double>((size_t)nf * 8) : nullptr;
+  Face32* f32 = !want_q && want_r && !c128 ? ar.get<Face32>(nf) : nullptr;
   if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-  e = launch_mesh_info_single(verts, vdtype, 3, nv, info, s);
-  if (e == hipSuccess) e = launch_face64(verts, vdtype, nv, tris, nf, info, kTauF64, f64, s);
+  e = launch_mesh_records(verts, vdtype, nv, tris, nf, info, kTauF64, MeshRecords{f64, f32, f32b, gram}, s);
   if (e != hipSuccess) return hip_fail(e, "regions prologue");
-  Face32B* f32b = nullptr;
-  double* gram = nullptr;
-  if (want_v || want_q) {
-    f32b = c128 ? nullptr : ar.get<Face32B>(nf);
-    gram = c128 ? ar.get<double>((size_t)nf * 8) : nullptr;
-    if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-    e = c128 ? launch_gram64(f64, nf, gram, s) : launch_face32b(f64, nf, kTauB32, kTauRelB32, f32b, s);
-    if (e != hipSuccess) return hip_fail(e, "regions prologue");
-  }
   // one visiting order of Q for every part below
   uint32_t* perm = nullptr;
   if ((st = build_qorder(ar, q, qdtype, nq, nullptr, 1, &perm, s)) != PFT_OK) return st;
@@ -1578,11 +1566,9 @@ pft_status pft_backward_3d_regions(const void* verts, pft_dtype vdtype, int64_t 
     std::vector<int64_t> offv(region_offsets, region_offsets + nreg + 1);
     if ((st = upload(ar, offv, &d_off, s)) != PFT_OK) return st;
     double* face_w = ar.get<double>(nf);
-    int qs;
-    int64_t qper;
-    choose_q_splits(nq, nf, c128 ? kTileFB : kTileFB32, &qs, &qper);
-    double* partial = ar.get<double>((size_t)qs * nf * 3);
-    double* contrib = ar.get<double>((size_t)nf * 9);
+    BwdArgs b;
+    plan_adjoint(nq, nf, c128, b);
+    double* partial = ar.get<double>((size_t)b.qsplits * nf * 3);
     if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
     e = launch_face_weights(d_off, (int)nreg, rho, nf, face_w, s);
     if (e != hipSuccess) return hip_fail(e, "face weights");
@@ -1590,7 +1576,6 @@ pft_status pft_backward_3d_regions(const void* verts, pft_dtype vdtype, int64_t 
     QRec64* rec64 = nullptr;
     if ((st = qrecs_from_perm(ar, mode, q, qdtype, grad_out, nq, info, nullptr, 1, perm, &rec, &rec64, s)) != PFT_OK)
       return st;
-    BwdArgs b;
     b.info = info;
     b.f64 = f64;
     b.f32 = f32b;
@@ -1601,17 +1586,13 @@ pft_status pft_backward_3d_regions(const void* verts, pft_dtype vdtype, int64_t 
     b.grad_out = grad_out;
     b.rec = rec;
     b.rec64 = rec64;
-    b.qsplits = qs;
-    b.q_per_split = qper;
     b.partial = partial;
     const char* nm = main_name(false, mode);
     prof_begin(nm, s);
     e = c128 ? launch_bwd3d_fp64(b, gram, s) : launch_bwd3d_fp32c(b, s);
     prof_end(nm, s);
     if (e != hipSuccess) return hip_fail(e, "adjoint");
-    e = launch_bwd_face_contrib(partial, qs, f64, face_w, nf, contrib, s);
-    if (e != hipSuccess) return hip_fail(e, "adjoint reduce");
-    if ((st = gather_tail(ar, tris, nf, nullptr, nullptr, nv, contrib, grad_verts, vdtype, s)) != PFT_OK) return st;
+    if ((st = adjoint_tail(ar, tris, nf, nv, partial, b.qsplits, f64, face_w, grad_verts, vdtype, s)) != PFT_OK) return st;
   }
   if (!want_r && !want_q) return PFT_OK;
   const int64_t nblocks = finish_blocks(nq);
@@ -1667,13 +1648,8 @@ pft_status pft_backward_3d_regions(const void* verts, pft_dtype vdtype, int64_t 
     const FwdPlan cut = fwd_plan(nq, nf, c128);
     if ((st = plan_regions(ar, region_offsets, nreg, nq, cut.qtile, cut.min_faces, cut.target, plan, s)) != PFT_OK)
       return st;
-    Face32* f32 = c128 ? nullptr : ar.get<Face32>(nf);
     double2* partial = ar.get<double2>((size_t)std::max(plan.splits, 1) * nq);
     if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-    if (!c128) {
-      e = launch_face32(f64, nf, f32, s);
-      if (e != hipSuccess) return hip_fail(e, "regions prologue");
-    }
     FwdArgs a;
     a.f64 = f64;
     a.f32 = f32;
@@ -1802,7 +1778,7 @@ static pft_status batch_forward_impl(const pft_mesh_batch* b, pft_mode mode, voi
   if (!c128) {
     f32 = ar.get<Face32>(std::max<int64_t>(p.nf, 1));
     if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-    hipError_t e = launch_face32(p.f64, p.nf, f32, s);
+    hipError_t e = launch_face_records(MeshRecords{p.f64, f32, nullptr, nullptr}, p.nf, s);
     if (e != hipSuccess) return hip_fail(e, "batch prologue");
   }
   // work items: (mesh, Q-tile, face chunk), longest first, for given tile sizes; returns the number of
@@ -1980,15 +1956,12 @@ pft_status pft_batch_backward(const pft_mesh_batch* b, pft_mode mode, const void
   QRec32* rec = nullptr;
   double* gram = nullptr;
   hipError_t e = hipSuccess;
-  if (c128) {
+  if (c128)
     gram = ar.get<double>((size_t)p.nf * 8);
-    if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-    e = launch_gram64(p.f64, p.nf, gram, s);
-  } else {
+  else
     f32b = ar.get<Face32B>(p.nf);
-    if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-    e = launch_face32b(p.f64, p.nf, kTauB32, kTauRelB32, f32b, s);
-  }
+  if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
+  e = launch_face_records(MeshRecords{p.f64, nullptr, f32b, gram}, p.nf, s);
   if (e != hipSuccess) return hip_fail(e, "batch adjoint prologue");
   QRec64* rec64 = nullptr;
   if ((st = build_qrecs(ar, mode, b->q, b->qdtype, grad_out, nq_total, p.info, p.d_q_off, n, &rec, &rec64, s)) !=

@@ -215,11 +215,7 @@ __global__ __launch_bounds__(256) void batch_fwd_finish_kernel(const double2* pa
   const int64_t nqm = q_off[mesh + 1] - q_off[mesh];
   const int64_t j = qi - q_off[mesh];
   double xr = 0.0, xi = 0.0;
-  for (int c = 0; c < q_chunks[mesh]; ++c) {
-    const double2 v = load_stream(partial + q_part[mesh] + (int64_t)c * nqm + j);
-    xr += v.x;
-    xi += v.y;
-  }
+  add_partials(partial + q_part[mesh] + j, nqm, q_chunks[mesh], xr, xi);
   double Q[3];
   load_q3(q, qdtype, dst, Q);
   const MeshInfo mi = info[mesh];
@@ -263,7 +259,7 @@ __global__ __launch_bounds__(kBlock) void batch_bwd_fp64_kernel(const BatchItemB
     for (int i = tid; i < nt * 8; i += kBlock) gtile[i / 8][i % 8] = gram[(it.f0 + i / 8) * 8 + i % 8];
     for (int v = 0; v < nt * 3; ++v) acc[v][tid] = 0.0;
     __syncthreads();
-    adj_tile_f64(tile, gtile, nt, it.q0, it.q0 + it.nq, rec, info[it.mesh].R, acc);
+    adj_tile_f64<kQPTB64>(tile, gtile, nt, it.q0, it.q0 + it.nq, rec, info[it.mesh].R, acc);
     __syncthreads();
     adj_block_sum(acc, nt, partial + it.part * 3);
     __syncthreads();
@@ -288,7 +284,7 @@ __global__ __launch_bounds__(kBlock) void batch_bwd_fp32c_kernel(const BatchItem
       reinterpret_cast<uint4*>(tile)[i] = reinterpret_cast<const uint4*>(f32b + it.f0)[i];
     for (int v = 0; v < nt * 3; ++v) acc[v][tid] = 0.0f;
     __syncthreads();
-    adj_tile_fp32c(tile, nt, it.q0, it.q0 + it.nq, rec, info[it.mesh].R, acc);
+    adj_tile_fp32c<kQPTB>(tile, nt, it.q0, it.q0 + it.nq, rec, info[it.mesh].R, acc);
     __syncthreads();
     adj_block_sum(acc, nt, partial + it.part * 3);
     __syncthreads();

@@ -22,7 +22,7 @@
 // there; the edge form cancels like 1/(|Q_perp| L)^2).
 //
 // Layout: a block owns a tile of faces (records in LDS) and loops over a
-// range of Q (a Q-split), kQPTB Q per thread per pass; the grid is one-
+// range of Q (a Q-split), P Q per thread per pass; the grid is one-
 // dimensional over (face tile, Q-split) pairs (adj_block).
 // Each thread adds its weights to private slots in LDS (one per face and
 // corner; binary64 or binary32 by form), and a fixed-order binary64 block sum
@@ -50,65 +50,56 @@ __device__ __forceinline__ void adj_block(const BwdArgs& a, int64_t ftiles, int6
   }
 }
 
+// Q range of split qs: whole passes of kBlock * P Q, shared out evenly (a part pass costs as much as a full one, so
+// no split but the last ends with one: 262 144 Q in 32 splits of 8 192 ran 11 passes of 768, a third of the last empty).
+template <int P>
+__device__ __forceinline__ void adj_range(const BwdArgs& a, int64_t qs, int64_t& qb, int64_t& qe) {
+  constexpr int64_t kPass = (int64_t)kBlock * P;
+  const int64_t n = (a.nq + kPass - 1) / kPass;
+  qb = qs * n / a.qsplits * kPass;
+  qe = min(a.nq, (qs + 1) * n / a.qsplits * kPass);
+}
+
+// P Q per thread and pass, TF faces per block. The small instances (P = 1, TF = kTileFBSmall) serve calls of few faces
+// and Q, which are bound by the latency of a block's serial face loop.
+template <int P, int TF>
 __global__ __launch_bounds__(kBlock) void bwd3d_fp64_kernel(BwdArgs a, const double* gram) {
-  __shared__ Face64 tile[kTileFB];
-  __shared__ double gtile[kTileFB][8];
-  __shared__ double acc[kTileFB * 3][kBlock];
+  __shared__ Face64 tile[TF];
+  __shared__ double gtile[TF][8];
+  __shared__ double acc[TF * 3][kBlock];
   const int tid = threadIdx.x;
-  int64_t ft, qs;
-  adj_block(a, (a.nf + kTileFB - 1) / kTileFB, ft, qs);
-  const int64_t f0 = ft * kTileFB;
-  const int nt = (int)min((int64_t)kTileFB, a.nf - f0);
+  int64_t ft, qs, qb, qe;
+  adj_block(a, (a.nf + TF - 1) / TF, ft, qs);
+  const int64_t f0 = ft * TF;
+  const int nt = (int)min((int64_t)TF, a.nf - f0);
   for (int i = tid; i < nt * (int)(sizeof(Face64) / 16); i += kBlock)
     reinterpret_cast<uint4*>(tile)[i] = reinterpret_cast<const uint4*>(a.f64 + f0)[i];
   for (int i = tid; i < nt * 8; i += kBlock) gtile[i / 8][i % 8] = gram[(f0 + i / 8) * 8 + i % 8];
   for (int v = 0; v < nt * 3; ++v) acc[v][tid] = 0.0;
   __syncthreads();
-  const int64_t qb = qs * a.q_per_split;
-  const int64_t qe = min(a.nq, qb + a.q_per_split);
-  adj_tile_f64(tile, gtile, nt, qb, qe, a.rec64, a.info[0].R, acc);
+  adj_range<P>(a, qs, qb, qe);
+  adj_tile_f64<P>(tile, gtile, nt, qb, qe, a.rec64, a.info[0].R, acc);
   __syncthreads();
   adj_block_sum(acc, nt, a.partial + (qs * a.nf + f0) * 3);
 }
 
+template <int P, int TF>
 __global__ __launch_bounds__(kBlock) void bwd3d_fp32c_kernel(BwdArgs a) {
-  __shared__ Face32B tile[kTileFB32];
-  __shared__ float acc[kTileFB32 * 3][kBlock];
+  __shared__ Face32B tile[TF];
+  __shared__ float acc[TF * 3][kBlock];
   const int tid = threadIdx.x;
-  int64_t ft, qs;
-  adj_block(a, (a.nf + kTileFB32 - 1) / kTileFB32, ft, qs);
-  const int64_t f0 = ft * kTileFB32;
-  const int nt = (int)min((int64_t)kTileFB32, a.nf - f0);
+  int64_t ft, qs, qb, qe;
+  adj_block(a, (a.nf + TF - 1) / TF, ft, qs);
+  const int64_t f0 = ft * TF;
+  const int nt = (int)min((int64_t)TF, a.nf - f0);
   for (int i = tid; i < nt * (int)(sizeof(Face32B) / 16); i += kBlock)
     reinterpret_cast<uint4*>(tile)[i] = reinterpret_cast<const uint4*>(a.f32 + f0)[i];
   for (int v = 0; v < nt * 3; ++v) acc[v][tid] = 0.0f;
   __syncthreads();
-  const int64_t qb = qs * a.q_per_split;
-  const int64_t qe = min(a.nq, qb + a.q_per_split);
-  adj_tile_fp32c(tile, nt, qb, qe, a.rec, a.info[0].R, acc);
+  adj_range<P>(a, qs, qb, qe);
+  adj_tile_fp32c<P>(tile, nt, qb, qe, a.rec, a.info[0].R, acc);
   __syncthreads();
   adj_block_sum(acc, nt, a.partial + (qs * a.nf + f0) * 3);
-}
-
-__global__ __launch_bounds__(256) void gram64_kernel(const Face64* f64, int64_t nf, double* gram) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= nf) return;
-  const Face64 f = f64[m];
-  double d0[3], d1[3], d2[3];
-  for (int k = 0; k < 3; ++k) {
-    d0[k] = f.u1[k] - f.u0[k];
-    d1[k] = -f.u0[k] - 2.0 * f.u1[k];
-    d2[k] = 2.0 * f.u0[k] + f.u1[k];
-  }
-  auto dot = [](const double* x, const double* y) { return x[0] * y[0] + x[1] * y[1] + x[2] * y[2]; };
-  double* G = gram + m * 8;
-  G[0] = dot(d0, d0);
-  G[1] = dot(d1, d1);
-  G[2] = dot(d2, d2);
-  G[3] = dot(d0, d1);
-  G[4] = dot(d1, d2);
-  G[5] = dot(d2, d0);
-  G[6] = G[7] = 0.0;
 }
 
 // ---------------------------------------------------------------------------
@@ -173,30 +164,93 @@ __global__ __launch_bounds__(256) void gather_kernel(const uint32_t* keys, const
   }
 }
 
+// One wavefront per vertex; a block's corner vertex indices in LDS (-1 for a corner of an empty face).
+constexpr int kGatherBlock = 1024;
+__global__ __launch_bounds__(kGatherBlock) void gather_small_kernel(const int32_t* tris, int64_t nf, int64_t nv,
+                                                                    const double* partial, int qsplits,
+                                                                    const Face64* f64, const double* face_w,
+                                                                    void* grad, int vdtype) {
+  __shared__ int32_t corner[3 * kSmallGatherFaces];
+  for (int64_t m = threadIdx.x; m < nf; m += kGatherBlock) {
+    const int32_t a = tris[3 * m], b = tris[3 * m + 1], c = tris[3 * m + 2];
+    const bool ok = a >= 0 && b >= 0 && c >= 0 && a < nv && b < nv && c < nv;
+    corner[3 * m] = ok ? a : -1;
+    corner[3 * m + 1] = ok ? b : -1;
+    corner[3 * m + 2] = ok ? c : -1;
+  }
+  __syncthreads();
+  const int lane = threadIdx.x & 63;
+  const int64_t v = (int64_t)blockIdx.x * (kGatherBlock / 64) + (threadIdx.x >> 6);
+  if (v >= nv) return;
+  double g[3] = {0.0, 0.0, 0.0};
+  // up to 64 of the vertex's corners at a time, one per lane, in corner order
+  auto flush = [&](int n, int64_t i) {
+    double c[3] = {0.0, 0.0, 0.0};
+    if (lane < n) {
+      double R = 0.0;
+      for (int s = 0; s < qsplits; ++s) R += partial[(int64_t)s * nf * 3 + i];
+      if (face_w) R *= face_w[i / 3];  // density of the face's region
+      for (int k = 0; k < 3; ++k) c[k] = f64[i / 3].N[k] * R;
+    }
+    for (int k = 0; k < 3; ++k) g[k] += wave_total(c[k]);
+  };
+  int n = 0;
+  int64_t mine = 0;
+  for (int64_t i0 = 0; i0 < nf * 3; i0 += 64) {
+    const bool hit = i0 + lane < nf * 3 && corner[i0 + lane] == (int32_t)v;
+    for (uint64_t m = __ballot(hit); m != 0; m &= m - 1) {
+      if (lane == n) mine = i0 + __ffsll((unsigned long long)m) - 1;
+      if (++n == 64) {
+        flush(64, mine);
+        n = 0;
+      }
+    }
+  }
+  if (n > 0) flush(n, mine);
+  if (lane < 3) {
+    const double x = lane == 0 ? g[0] : (lane == 1 ? g[1] : g[2]);
+    if (vdtype == PFT_F64)
+      static_cast<double*>(grad)[v * 3 + lane] = x;
+    else
+      static_cast<float*>(grad)[v * 3 + lane] = (float)x;
+  }
+}
+
 inline unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-hipError_t launch_gram64(const Face64* f64, int64_t nf, double* gram, hipStream_t s) {
-  if (nf <= 0) return hipSuccess;
-  gram64_kernel<<<grid_for(nf), 256, 0, s>>>(f64, nf, gram);
-  return hipGetLastError();
-}
-
 hipError_t launch_bwd3d_fp64(const BwdArgs& a, const double* gram, hipStream_t s) {
-  const int64_t blocks = (a.nf + kTileFB - 1) / kTileFB * a.qsplits;
+  const int tf = a.small ? kTileFBSmall : kTileFB;
+  const int64_t blocks = (a.nf + tf - 1) / tf * a.qsplits;
   if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-  bwd3d_fp64_kernel<<<(unsigned)blocks, kBlock, 0, s>>>(a, gram);
+  if (a.small)
+    bwd3d_fp64_kernel<1, kTileFBSmall><<<(unsigned)blocks, kBlock, 0, s>>>(a, gram);
+  else
+    bwd3d_fp64_kernel<kQPTB64, kTileFB><<<(unsigned)blocks, kBlock, 0, s>>>(a, gram);
   return hipGetLastError();
 }
 
 hipError_t launch_bwd3d_fp32c(const BwdArgs& a, hipStream_t s) {
-  const int64_t blocks = (a.nf + kTileFB32 - 1) / kTileFB32 * a.qsplits;
+  const int tf = a.small ? kTileFBSmall : kTileFB32;
+  const int64_t blocks = (a.nf + tf - 1) / tf * a.qsplits;
   if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-  bwd3d_fp32c_kernel<<<(unsigned)blocks, kBlock, 0, s>>>(a);
+  if (a.small)
+    bwd3d_fp32c_kernel<1, kTileFBSmall><<<(unsigned)blocks, kBlock, 0, s>>>(a);
+  else
+    bwd3d_fp32c_kernel<kQPTB, kTileFB32><<<(unsigned)blocks, kBlock, 0, s>>>(a);
   return hipGetLastError();
 }
 
+hipError_t launch_gather_small(const int32_t* tris, int64_t nf, int64_t nv, const double* partial, int qsplits,
+                               const Face64* f64, const double* face_w, void* grad, int vdtype, hipStream_t s) {
+  if (nv <= 0) return hipSuccess;
+  if (nf > kSmallGatherFaces) return hipErrorInvalidValue;
+  constexpr int64_t per = kGatherBlock / 64;
+  gather_small_kernel<<<(unsigned)((nv + per - 1) / per), kGatherBlock, 0, s>>>(tris, nf, nv, partial, qsplits, f64,
+                                                                               face_w, grad, vdtype);
+  return hipGetLastError();
+}
 
 hipError_t launch_bwd_face_contrib(const double* partial, int qsplits, const Face64* f64, const double* face_w,
                                    int64_t nf, double* contrib, hipStream_t s) {

@@ -195,12 +195,10 @@ __global__ __launch_bounds__(kFinishBlock) void regions_finish_kernel(FwdArgs a,
   double Fr = 0.0, Fi = 0.0;
   for (int j = 0; j < r.nreg; ++j) {
     double xr = 0.0, xi = 0.0;
-    if (valid)
-      for (int s = r.region_split[j]; s < r.region_split[j + 1]; ++s) {
-        const double2 v = load_stream(a.partial + (int64_t)s * a.nq + qi);
-        xr += v.x;
-        xi += v.y;
-      }
+    if (valid) {
+      const int s0 = r.region_split[j];
+      add_partials(a.partial + (int64_t)s0 * a.nq + qi, a.nq, r.region_split[j + 1] - s0, xr, xi);
+    }
     if (!(qabs * (r.region_R ? r.region_R[j] : mi.R) < a.tau0)) {  // this region's small-|Q| test
       xr /= Q2;
       xi /= Q2;
@@ -243,14 +241,12 @@ __global__ __launch_bounds__(kFinishBlock) void dq_finish_kernel(DqArgs a, Regio
   double gq[3] = {0.0, 0.0, 0.0};
   for (int j = 0; j < r.nreg; ++j) {
     double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (valid)
-      for (int s = r.region_split[j]; s < r.region_split[j + 1]; ++s)
+    if (valid) {
+      const int s0 = r.region_split[j], n = r.region_split[j + 1] - s0;
 #pragma unroll
-        for (int c = 0; c < 4; ++c) {
-          const double2 x = load_stream(a.partial + ((int64_t)s * 4 + c) * a.nq + qi);
-          v[2 * c] += x.x;
-          v[2 * c + 1] += x.y;
-        }
+      for (int c = 0; c < 4; ++c)
+        add_partials(a.partial + ((int64_t)s0 * 4 + c) * a.nq + qi, 4 * a.nq, n, v[2 * c], v[2 * c + 1]);
+    }
     // centred F_c and grad F_c
     double fcr, fci, gcr[3], gci[3];
     if (qabs * (r.region_R ? r.region_R[j] : mi.R) < a.tau) {  // this region's small-|Q| test

@@ -68,14 +68,31 @@ __device__ __forceinline__ double2 load_stream(const double2* p) {
   return make_double2(__builtin_nontemporal_load(&p->x), __builtin_nontemporal_load(&p->y));
 }
 
-// Sum of the forward's binary64 partials (one per face split) of the visited Q number qi, in split order.
-__device__ __forceinline__ void fwd_partial_sum(const FwdArgs& a, int64_t qi, double& xr, double& xi) {
-  xr = xi = 0.0;
-  for (int s = 0; s < a.splits; ++s) {
-    const double2 v = load_stream(a.partial + (int64_t)s * a.nq + qi);
+// Adds n partial sums p[0], p[stride], .. to (xr, xi) in that order, eight loads in flight at a time (one after the
+// other, 18 splits took a finish kernel of 1 001 Q 10.2 us, 4.1 now).
+__device__ __forceinline__ void add_partials(const double2* p, int64_t stride, int n, double& xr, double& xi) {
+  int s = 0;
+  for (; s + 8 <= n; s += 8) {
+    double2 v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = load_stream(p + (s + k) * stride);
+#pragma unroll
+    for (int k = 0; k < 8; ++k) {
+      xr += v[k].x;
+      xi += v[k].y;
+    }
+  }
+  for (; s < n; ++s) {
+    const double2 v = load_stream(p + s * stride);
     xr += v.x;
     xi += v.y;
   }
+}
+
+// Sum of the forward's binary64 partials (one per face split) of the visited Q number qi, in split order.
+__device__ __forceinline__ void fwd_partial_sum(const FwdArgs& a, int64_t qi, double& xr, double& xi) {
+  xr = xi = 0.0;
+  add_partials(a.partial + qi, a.nq, a.splits, xr, xi);
 }
 
 // sin(2 pi x), cos(2 pi x) for x in turns (hardware transcendental unit; valid for |x| <= 256).

@@ -26,6 +26,7 @@ constexpr int kTileF = PFT_TILEF;  // faces staged in LDS per tile (binary64 for
 // than the 5 per SIMD the registers allow
 constexpr int kTileF32 = PFT_TILEF32;
 constexpr int kTileFB = 8;         // faces per block in the binary64 adjoint
+constexpr int kTileFBSmall = 2;    // the same in either form for calls that would leave most of the chip idle
 #ifndef PFT_QPT
 #define PFT_QPT 2
 #endif
@@ -95,7 +96,6 @@ constexpr int kTileE = 64;         // 2D edges staged in LDS per tile
 constexpr double kTauF64 = 0.05;     // forward and adjoint, FP64 mode
 constexpr double kTauF32 = 0.1;      // forward, FP32C mode (series in FP64)
 constexpr double kTauRel32 = 0.02;   // polygon forward, FP32C mode, relative test
-constexpr double kTauB32 = 1.5;      // (record field of the FP32C adjoint; empty-face flag)
 // The adjoint evaluates each face's barycentric moments by the fitted symmetric polynomials (face_poly.h) when the
 // largest centred vertex phase |Q.(v_k - g)| is at most this, by the differentiated edge sums otherwise (there
 // |Q_perp| L > 4.5).
@@ -103,7 +103,6 @@ constexpr double kTauB32 = 1.5;      // (record field of the FP32C adjoint; empt
 #define PFT_SERIES_MAX_PHASE 3.0
 #endif
 constexpr double kSeriesMaxPhase = PFT_SERIES_MAX_PHASE;
-constexpr double kTauRelB32 = 0.05;  // adjoint, FP32C mode, relative test
 // Whole-mesh series (fan of tetrahedra from the vertex mean) when |Q| R < tau0.
 constexpr double kTau0F64 = 0.01;
 constexpr double kTau0F32 = 0.2;
@@ -177,7 +176,7 @@ constexpr uint32_t kFaceLinked = 1u;
 constexpr unsigned kMetaLink = 4u;
 constexpr unsigned kMetaReflect = 8u;
 
-// FP32C adjoint face record.
+// FP32C adjoint face record (all zero for an empty face).
 struct alignas(16) Face32B {
   double gt[3];   // centroid / (2 pi)
   float N[3];
@@ -186,8 +185,7 @@ struct alignas(16) Face32B {
   float u0[3];    // a - g: vertex phase delta_0 = Q . u0
   float u1[3];    // b - g
   float G[6];     // d0.d0, d1.d1, d2.d2, d0.d1, d1.d2, d2.d0
-  float thr;      // tau_b^2 |N|^2 / L^2 (-1 for an empty face, whose record is otherwise all zero)
-  float kap;      // tau_relb^2 |N|^2
+  float pad[2];
   float g[3];     // centroid relative to the mesh centre t (used by grad_Q F)
 };
 static_assert(sizeof(Face32B) == 128, "Face32B layout");
@@ -223,13 +221,21 @@ hipError_t launch_mesh_info(const void* verts, int vdtype, const int64_t* d_vert
                             MeshInfo* info, hipStream_t s);
 hipError_t launch_mesh_info_single(const void* verts, int vdtype, int dim, int64_t nv, MeshInfo* info,
                                    hipStream_t s);
-// With order / meta (device, [nf]; NULL: the list order), record m is face order[m] with its
-// vertex list rotated by meta[m] & 3, and pad[2] holds the link meta[m] >> 2 (0, 1 or 2).
-hipError_t launch_face64(const void* verts, int vdtype, int64_t nv, const int32_t* tris, int64_t nf,
-                         MeshInfo* info, double tau, Face64* out, hipStream_t s,
-                         const int32_t* order = nullptr, const uint8_t* meta = nullptr);
-hipError_t launch_face32(const Face64* f64, int64_t nf, Face32* out, hipStream_t s);
-hipError_t launch_face32b(const Face64* f64, int64_t nf, double tau, double tau_rel, Face32B* out, hipStream_t s);
+// The face records of a mesh: f64 always, the others where not NULL (f32: FP32C forward, f32b: FP32C adjoint,
+// gram [nf][8]: binary64 adjoint).
+struct MeshRecords {
+  Face64* f64;
+  Face32* f32;
+  Face32B* f32b;
+  double* gram;
+};
+// Centre, radius and records of one mesh. With order / meta (device, [nf]; NULL: the list order), record m is face
+// order[m] with its vertex list rotated by meta[m] & 3, and pad[2] holds the link meta[m] >> 2 (0, 1 or 2).
+hipError_t launch_mesh_records(const void* verts, int vdtype, int64_t nv, const int32_t* tris, int64_t nf,
+                               MeshInfo* info, double tau, const MeshRecords& rec, hipStream_t s,
+                               const int32_t* order = nullptr, const uint8_t* meta = nullptr);
+// The records other than f64 from it.
+hipError_t launch_face_records(const MeshRecords& rec, int64_t nf, hipStream_t s);
 hipError_t launch_face64_batch(const void* verts, int vdtype, const int32_t* tris, const int64_t* d_vert_off,
                                const int64_t* d_tri_off, const int32_t* d_face_mesh, int64_t nf_total,
                                MeshInfo* info, double tau, Face64* out, hipStream_t s,
@@ -417,11 +423,10 @@ struct BwdArgs {
   const void* grad_out;
   const QRec32* rec;    // FP32C: reordered Q with their centred cotangents (launch_qrec32_gather)
   const QRec64* rec64;  // FP64: the same in binary64 (launch_qrec64_gather)
-  int qsplits;
-  int64_t q_per_split;
+  int qsplits;        // each a whole number of passes of kBlock * (Q per thread) Q
+  bool small;         // one Q per thread and kTileFBSmall faces per block
   double* partial;    // [qsplits][nf][3]
 };
-hipError_t launch_gram64(const Face64* f64, int64_t nf, double* gram /*[nf][8]*/, hipStream_t s);
 hipError_t launch_bwd3d_fp64(const BwdArgs& a, const double* gram, hipStream_t s);
 hipError_t launch_bwd3d_fp32c(const BwdArgs& a, hipStream_t s);
 
@@ -442,7 +447,7 @@ struct QOrderScratch {   // device temporaries of launch_qorder
 hipError_t qorder_sort_bytes(int64_t nq, int64_t n_meshes, size_t* bytes);
 hipError_t launch_qorder(const void* q, int qdtype, int64_t nq, const int64_t* d_q_off, int64_t n_meshes,
                          const QOrderScratch& w, hipStream_t s);
-// rec[i] = Q[perm[i]] with its centred cotangent g exp(-iQ.t), t the centre of the owning mesh.
+// rec[i] = Q[perm[i]] (perm NULL: Q[i]) with its centred cotangent g exp(-iQ.t), t the centre of the owning mesh.
 hipError_t launch_qrec32_gather(const void* q, int qdtype, const void* grad_out, int64_t nq, const uint32_t* perm,
                                 const MeshInfo* info, const int64_t* d_q_off, int64_t n_meshes, QRec32* rec,
                                 hipStream_t s);
@@ -459,6 +464,11 @@ hipError_t launch_incidence_keys(const int32_t* tris, int64_t nf, const int64_t*
                                  hipStream_t s);
 hipError_t sort_incidence(uint32_t* keys_in, uint32_t* vals_in, uint32_t* keys_out, uint32_t* vals_out, int64_t n,
                           int64_t nv_total, void* temp, size_t* temp_bytes, hipStream_t s);
+// The same for a mesh of at most kSmallGatherFaces faces in one launch: a wavefront per vertex looks its corners up
+// in the triangle list and adds their split sums (in corner order).
+constexpr int64_t kSmallGatherFaces = 2048;
+hipError_t launch_gather_small(const int32_t* tris, int64_t nf, int64_t nv, const double* partial, int qsplits,
+                               const Face64* f64, const double* face_w, void* grad, int vdtype, hipStream_t s);
 hipError_t launch_gather_vertices(const uint32_t* keys_sorted, const uint32_t* vals_sorted, int64_t nslots,
                                   const double* contrib, int64_t nv, void* grad, int vdtype, hipStream_t s);
 

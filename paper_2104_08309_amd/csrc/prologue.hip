@@ -38,14 +38,10 @@ __device__ __forceinline__ double info_wave_max(double v) {
   return v;
 }
 
-__global__ __launch_bounds__(kInfoBlock) void mesh_info_kernel(const void* verts, int vdtype, int dim,
-                                                              int64_t nv_single, const int64_t* vert_off,
-                                                              MeshInfo* info) {
+// t and (in thread 0) R of vertices [v0, v1); every thread of a kInfoBlock block calls it and gets t.
+__device__ inline double mesh_centre(const void* verts, int vdtype, int dim, int64_t v0, int64_t v1,
+                                     double (*red)[3], double* t) {
   constexpr int kWaves = kInfoBlock / 64;
-  __shared__ double red[kWaves][3];
-  const int64_t mesh = blockIdx.x;
-  const int64_t v0 = vert_off ? vert_off[mesh] : 0;
-  const int64_t v1 = vert_off ? vert_off[mesh + 1] : nv_single;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   double s[3] = {0.0, 0.0, 0.0};
   for (int64_t i = v0 + tid; i < v1; i += kInfoBlock) {
@@ -58,7 +54,6 @@ __global__ __launch_bounds__(kInfoBlock) void mesh_info_kernel(const void* verts
     for (int k = 0; k < 3; ++k) red[w][k] = s[k];
   __syncthreads();
   const int64_t n = v1 - v0;
-  double t[3];
   for (int k = 0; k < 3; ++k) {
     double a = 0.0;
     for (int u = 0; u < kWaves; ++u) a += red[u][k];
@@ -76,16 +71,21 @@ __global__ __launch_bounds__(kInfoBlock) void mesh_info_kernel(const void* verts
   r2 = info_wave_max(r2);
   if (lane == 0) red[w][0] = r2;
   __syncthreads();
-  if (tid == 0) {
-    double r = 0.0;
+  double r = 0.0;
+  if (tid == 0)
     for (int u = 0; u < kWaves; ++u) r = fmax(r, red[u][0]);
-    MeshInfo m;
-    for (int k = 0; k < 3; ++k) m.t[k] = t[k];
-    m.R = sqrt(r);
-    m.rho = 0.0;  // raised by the face prologue
-    m.pad = 0.0;
-    info[mesh] = m;
-  }
+  return sqrt(r);
+}
+
+__global__ __launch_bounds__(kInfoBlock) void mesh_info_kernel(const void* verts, int vdtype, int dim,
+                                                              int64_t nv_single, const int64_t* vert_off,
+                                                              MeshInfo* info) {
+  __shared__ double red[kInfoBlock / 64][3];
+  const int64_t mesh = blockIdx.x;
+  double t[3];
+  const double R = mesh_centre(verts, vdtype, dim, vert_off ? vert_off[mesh] : 0,
+                               vert_off ? vert_off[mesh + 1] : nv_single, red, t);
+  if (threadIdx.x == 0) info[mesh] = MeshInfo{{t[0], t[1], t[2]}, R, 0.0, 0.0};  // rho raised by the face prologue
 }
 
 __device__ inline void make_face64(const double* a, const double* b, const double* c, double tau, Face64& f) {
@@ -161,38 +161,44 @@ __device__ __forceinline__ int order_code(const uint8_t* meta, int64_t m) {
   return ((meta[m] & kMetaLink) ? 1 : 0) | ((meta[m] & kMetaReflect) ? 2 : 0);
 }
 
+// Record of the face at position m of the (optional) edge-sharing order, its vertex list rotated, for a mesh centred
+// on t; returns its largest squared vertex distance (0 for an empty face).
+__device__ inline double face64_at(const void* verts, int vdtype, int64_t nv, const int32_t* tris, int64_t nf,
+                                   const double* t, double tau, const int32_t* order, const uint8_t* meta, int64_t m,
+                                   Face64& f) {
+  const int64_t src = order ? (int64_t)order[m] : m;
+  const int rot = meta ? (meta[m] & 3) : 0;
+  const bool in_list = src >= 0 && src < nf && rot < 3;
+  const int32_t ia = in_list ? tris[3 * src + rot] : -1;
+  const int32_t ib = in_list ? tris[3 * src + (rot + 1) % 3] : -1;
+  const int32_t ic = in_list ? tris[3 * src + (rot + 2) % 3] : -1;
+  if (ia < 0 || ib < 0 || ic < 0 || ia >= nv || ib >= nv || ic >= nv) {
+    empty_face64(f);
+    return 0.0;
+  }
+  double a[3], b[3], c[3];
+  load_vertex(verts, vdtype, 3, ia, a);
+  load_vertex(verts, vdtype, 3, ib, b);
+  load_vertex(verts, vdtype, 3, ic, c);
+  for (int k = 0; k < 3; ++k) {
+    a[k] -= t[k];
+    b[k] -= t[k];
+    c[k] -= t[k];
+  }
+  make_face64(a, b, c, tau, f);
+  f.pad[2] = (double)order_code(meta, m);
+  return face_extent2(f);
+}
+
 __global__ __launch_bounds__(256) void face64_kernel(const void* verts, int vdtype, int64_t nv, const int32_t* tris,
                                                      int64_t nf, MeshInfo* info, double tau, Face64* out,
                                                      const int32_t* order, const uint8_t* meta) {
   const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   double ext2 = 0.0;
   if (m < nf) {
-    // the face at this position of the (optional) edge-sharing order, its vertex list rotated
-    const int64_t src = order ? (int64_t)order[m] : m;
-    const int rot = meta ? (meta[m] & 3) : 0;
-    const int code = order_code(meta, m);
+    const double t[3] = {info[0].t[0], info[0].t[1], info[0].t[2]};
     Face64 f;
-    const bool in_list = src >= 0 && src < nf && rot < 3;
-    const int32_t ia = in_list ? tris[3 * src + rot] : -1;
-    const int32_t ib = in_list ? tris[3 * src + (rot + 1) % 3] : -1;
-    const int32_t ic = in_list ? tris[3 * src + (rot + 2) % 3] : -1;
-    if (ia < 0 || ib < 0 || ic < 0 || ia >= nv || ib >= nv || ic >= nv) {
-      empty_face64(f);
-    } else {
-      double a[3], b[3], c[3];
-      load_vertex(verts, vdtype, 3, ia, a);
-      load_vertex(verts, vdtype, 3, ib, b);
-      load_vertex(verts, vdtype, 3, ic, c);
-      const MeshInfo mi = info[0];
-      for (int k = 0; k < 3; ++k) {
-        a[k] -= mi.t[k];
-        b[k] -= mi.t[k];
-        c[k] -= mi.t[k];
-      }
-      make_face64(a, b, c, tau, f);
-      f.pad[2] = (double)code;
-      ext2 = face_extent2(f);
-    }
+    ext2 = face64_at(verts, vdtype, nv, tris, nf, t, tau, order, meta, m, f);
     out[m] = f;
   }
   raise_rho(info, 0, ext2);
@@ -406,9 +412,7 @@ __global__ __launch_bounds__(256) void iota_u32_kernel(uint32_t* p, int64_t n) {
   if (i < n) p[i] = (uint32_t)i;
 }
 
-__global__ __launch_bounds__(256) void face32_kernel(const Face64* in, int64_t nf, Face32* out) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= nf) return;
+__device__ inline Face32 face32_at(const Face64* in, int64_t m) {
   const Face64 f = in[m];
   Face32 r;
   const bool ok = f.thr >= 0.0;
@@ -423,16 +427,11 @@ __global__ __launch_bounds__(256) void face32_kernel(const Face64* in, int64_t n
   }
   // linked only to a non-empty predecessor (an empty record carries no edge)
   r.flags = ok && (code & 1) && m > 0 && in[m - 1].thr >= 0.0 ? kFaceLinked : 0u;
-  out[m] = r;
+  return r;
 }
 
-__global__ __launch_bounds__(256) void face32b_kernel(const Face64* in, int64_t nf, double tau, double tau_rel,
-                                                      Face32B* out) {
-  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (m >= nf) return;
-  const Face64 f = in[m];
+__device__ inline Face32B face32b_at(const Face64& f) {
   Face32B r;
-  const double L2 = f.pad[0], N2 = f.pad[1];
   const bool ok = f.thr >= 0.0;
   double d0[3], d1[3], d2[3];
   for (int k = 0; k < 3; ++k) {
@@ -455,10 +454,71 @@ __global__ __launch_bounds__(256) void face32b_kernel(const Face64* in, int64_t 
   r.G[3] = ok ? (float)dot(d0, d1) : 0.0f;
   r.G[4] = ok ? (float)dot(d1, d2) : 0.0f;
   r.G[5] = ok ? (float)dot(d2, d0) : 0.0f;
-  r.thr = ok ? (float)(tau * tau * N2 / L2) : -1.0f;
-  r.kap = ok ? (float)(tau_rel * tau_rel * N2) : -1.0f;
+  r.pad[0] = r.pad[1] = 0.0f;
   for (int k = 0; k < 3; ++k) r.g[k] = ok ? (float)f.g[k] : 0.0f;
-  out[m] = r;
+  return r;
+}
+
+// Gram matrix of a face's edges, {d0.d0, d1.d1, d2.d2, d0.d1, d1.d2, d2.d0, 0, 0} (the binary64 edge form's).
+__device__ inline void gram64_at(const Face64& f, double* G) {
+  double d0[3], d1[3], d2[3];
+  for (int k = 0; k < 3; ++k) {
+    d0[k] = f.u1[k] - f.u0[k];
+    d1[k] = -f.u0[k] - 2.0 * f.u1[k];
+    d2[k] = 2.0 * f.u0[k] + f.u1[k];
+  }
+  auto dot = [](const double* x, const double* y) { return x[0] * y[0] + x[1] * y[1] + x[2] * y[2]; };
+  G[0] = dot(d0, d0);
+  G[1] = dot(d1, d1);
+  G[2] = dot(d2, d2);
+  G[3] = dot(d0, d1);
+  G[4] = dot(d1, d2);
+  G[5] = dot(d2, d0);
+  G[6] = G[7] = 0.0;
+}
+
+__global__ __launch_bounds__(256) void face32_kernel(const Face64* in, int64_t nf, Face32* out) {
+  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (m < nf) out[m] = face32_at(in, m);
+}
+
+__global__ __launch_bounds__(256) void face32b_kernel(const Face64* in, int64_t nf, Face32B* out) {
+  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (m < nf) out[m] = face32b_at(in[m]);
+}
+
+__global__ __launch_bounds__(256) void gram64_kernel(const Face64* f64, int64_t nf, double* gram) {
+  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (m < nf) gram64_at(f64[m], gram + m * 8);
+}
+
+// The whole prologue of a small mesh in one block: centre and radius, then the records asked for. Bound by the
+// latency of its dependent steps, which three to four launches of a few blocks each paid anew.
+__global__ __launch_bounds__(kInfoBlock) void mesh_records_small_kernel(const void* verts, int vdtype, int64_t nv,
+                                                                        const int32_t* tris, int64_t nf, double tau,
+                                                                        const int32_t* order, const uint8_t* meta,
+                                                                        MeshInfo* info, MeshRecords rec) {
+  __shared__ double red[kInfoBlock / 64][3];
+  double t[3];
+  const double R = mesh_centre(verts, vdtype, 3, 0, nv, red, t);
+  double ext2 = 0.0;
+  for (int64_t m = threadIdx.x; m < nf; m += kInfoBlock) {
+    Face64 f;
+    ext2 = fmax(ext2, face64_at(verts, vdtype, nv, tris, nf, t, tau, order, meta, m, f));
+    rec.f64[m] = f;
+    if (rec.f32b) rec.f32b[m] = face32b_at(f);
+    if (rec.gram) gram64_at(f, rec.gram + m * 8);
+  }
+  ext2 = info_wave_max(ext2);
+  __syncthreads();  // the records are visible to the block; thread 0 has read red
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6][0] = ext2;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int u = 0; u < kInfoBlock / 64; ++u) ext2 = fmax(ext2, red[u][0]);
+    info[0] = MeshInfo{{t[0], t[1], t[2]}, R, sqrt(ext2), 0.0};
+  }
+  if (rec.f32)
+    for (int64_t m = threadIdx.x; m < nf; m += kInfoBlock) rec.f32[m] = face32_at(rec.f64, m);
 }
 
 __global__ __launch_bounds__(256) void edges2d_kernel(const double* verts, int64_t nv, const int64_t* off,
@@ -516,12 +576,28 @@ hipError_t launch_mesh_info_single(const void* verts, int vdtype, int dim, int64
   return hipGetLastError();
 }
 
-hipError_t launch_face64(const void* verts, int vdtype, int64_t nv, const int32_t* tris, int64_t nf,
-                         MeshInfo* info, double tau, Face64* out, hipStream_t s, const int32_t* order,
-                         const uint8_t* meta) {
+hipError_t launch_face_records(const MeshRecords& rec, int64_t nf, hipStream_t s) {
   if (nf <= 0) return hipSuccess;
-  face64_kernel<<<grid_for(nf), 256, 0, s>>>(verts, vdtype, nv, tris, nf, info, tau, out, order, meta);
+  if (rec.f32) face32_kernel<<<grid_for(nf), 256, 0, s>>>(rec.f64, nf, rec.f32);
+  if (rec.f32b) face32b_kernel<<<grid_for(nf), 256, 0, s>>>(rec.f64, nf, rec.f32b);
+  if (rec.gram) gram64_kernel<<<grid_for(nf), 256, 0, s>>>(rec.f64, nf, rec.gram);
   return hipGetLastError();
+}
+
+hipError_t launch_mesh_records(const void* verts, int vdtype, int64_t nv, const int32_t* tris, int64_t nf,
+                               MeshInfo* info, double tau, const MeshRecords& rec, hipStream_t s,
+                               const int32_t* order, const uint8_t* meta) {
+  // one block for up to half its threads' faces: 320 faces 12.1 us in three launches, 10.1 in one (and two launches
+  // fewer on the host); 1 280 faces 13.5 us in three, 22 in one
+  if (nf <= kInfoBlock / 2 && nv <= kInfoBlock) {
+    mesh_records_small_kernel<<<1, kInfoBlock, 0, s>>>(verts, vdtype, nv, tris, nf, tau, order, meta, info, rec);
+    return hipGetLastError();
+  }
+  mesh_info_kernel<<<1, kInfoBlock, 0, s>>>(verts, vdtype, 3, nv, nullptr, info);
+  if (nf > 0)
+    face64_kernel<<<grid_for(nf), 256, 0, s>>>(verts, vdtype, nv, tris, nf, info, tau, rec.f64, order, meta);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? launch_face_records(rec, nf, s) : e;
 }
 
 hipError_t launch_poly_records(const void* verts, int vdtype, int64_t nv, const int64_t* face_off,
@@ -536,18 +612,6 @@ hipError_t launch_poly_records32(const FaceP64* f64, const VtxP64* v64, int64_t 
                                  VtxP32* v32, hipStream_t s) {
   if (nf <= 0) return hipSuccess;
   poly32_kernel<<<grid_for(nf), 256, 0, s>>>(f64, v64, nf, tau_rel, f32, v32);
-  return hipGetLastError();
-}
-
-hipError_t launch_face32(const Face64* f64, int64_t nf, Face32* out, hipStream_t s) {
-  if (nf <= 0) return hipSuccess;
-  face32_kernel<<<grid_for(nf), 256, 0, s>>>(f64, nf, out);
-  return hipGetLastError();
-}
-
-hipError_t launch_face32b(const Face64* f64, int64_t nf, double tau, double tau_rel, Face32B* out, hipStream_t s) {
-  if (nf <= 0) return hipSuccess;
-  face32b_kernel<<<grid_for(nf), 256, 0, s>>>(f64, nf, tau, tau_rel, out);
   return hipGetLastError();
 }
 

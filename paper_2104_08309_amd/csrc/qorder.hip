@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) void qrec32_kernel(const void* q, int qdtype, 
                                                      const int64_t* q_off, int64_t n_meshes, QRec32* rec) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nq) return;
-  const int64_t j = perm[i];
+  const int64_t j = perm ? (int64_t)perm[i] : i;
   double Q[3];
   load_q3(q, qdtype, j, Q);
   const float2 g = grad_out[j];
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256) void qrec64_kernel(const void* q, int qdtype, 
                                                      const int64_t* q_off, int64_t n_meshes, QRec64* rec) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= nq) return;
-  const int64_t j = perm[i];
+  const int64_t j = perm ? (int64_t)perm[i] : i;
   double Q[3];
   load_q3(q, qdtype, j, Q);
   const double2 g = grad_out[j];
