@@ -528,17 +528,13 @@ pft_status build_qorder(Arena& ar, const void* q, int qdtype, int64_t nq, const 
   if (nq < kQOrderMin || nq > INT32_MAX) return PFT_OK;
   QOrderScratch w;
   w.box_partial = ar.get<double>(256 * 6);
-  w.box = ar.get<double>(6);
-  w.keys = ar.get<uint64_t>(nq);
-  w.keys_sorted = ar.get<uint64_t>(nq);
+  w.keys = ar.get<uint32_t>(nq);
+  w.keys2 = ar.get<uint32_t>(nq);
   w.vals = ar.get<uint32_t>(nq);
+  w.counts = ar.get<uint32_t>((size_t)qorder_counts(nq));
   w.perm = ar.get<uint32_t>(nq);
   if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-  hipError_t e = qorder_sort_bytes(nq, n_meshes, &w.sort_bytes);
-  if (e != hipSuccess) return hip_fail(e, "Q sort size query");
-  w.sort_temp = ar.get<unsigned char>(w.sort_bytes);
-  if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
-  e = launch_qorder(q, qdtype, nq, d_q_off, n_meshes, w, s);
+  hipError_t e = launch_qorder(q, qdtype, nq, d_q_off, n_meshes, w, s);
   if (e != hipSuccess) return hip_fail(e, "Q order");
   *perm = w.perm;
   return PFT_OK;
@@ -1609,7 +1605,7 @@ pft_status pft_backward_3d_regions(const void* verts, pft_dtype vdtype, int64_t 
     // dL/dQ (and dL/drho from the same partials): the grad_Q kernel
     RegionPlan plan;
     if ((st = plan_regions(ar, region_offsets, nreg, nq, c128 ? kBlock : (int64_t)kBlock * kQPTDQ, kMinFacesPerSplit,
-                             kTargetBlocks, plan, s)) != PFT_OK) return st;
+                           kTargetBlocks, plan, s)) != PFT_OK) return st;
     double2* partial = ar.get<double2>((size_t)std::max(plan.splits, 1) * 4 * nq);
     if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
     DqArgs d;

@@ -436,15 +436,13 @@ hipError_t launch_bwd3d_fp32c(const BwdArgs& a, hipStream_t s);
 // caller's index of the i-th visited Q.
 struct QOrderScratch {   // device temporaries of launch_qorder
   double* box_partial;   // [256 * 6]
-  double* box;           // [6]
-  uint64_t* keys;        // [nq]
-  uint64_t* keys_sorted; // [nq]
+  uint32_t* keys;        // [nq]
+  uint32_t* keys2;       // [nq]
   uint32_t* vals;        // [nq]
+  uint32_t* counts;      // [qorder_counts(nq)]
   uint32_t* perm;        // [nq] result
-  void* sort_temp;       // [sort_bytes]
-  size_t sort_bytes;
 };
-hipError_t qorder_sort_bytes(int64_t nq, int64_t n_meshes, size_t* bytes);
+int64_t qorder_counts(int64_t nq);
 hipError_t launch_qorder(const void* q, int qdtype, int64_t nq, const int64_t* d_q_off, int64_t n_meshes,
                          const QOrderScratch& w, hipStream_t s);
 // rec[i] = Q[perm[i]] (perm NULL: Q[i]) with its centred cotangent g exp(-iQ.t), t the centre of the owning mesh.
