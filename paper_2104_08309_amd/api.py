@@ -8,6 +8,7 @@ library's HIP kernels; there is no CPU path.
 from __future__ import annotations
 
 import ctypes
+import itertools
 import weakref
 from typing import Optional, Sequence, Tuple
 
@@ -265,9 +266,11 @@ def forward_3d_poly(verts: torch.Tensor, faces: Sequence[Sequence[int]], q: torc
     if verts.dim() != 2 or verts.shape[1] != 3:
         raise ValueError(f"verts must have shape [nv, 3], got {tuple(verts.shape)}")
     off = np.zeros(len(faces) + 1, dtype=np.int64)
-    for i, f in enumerate(faces):
-        off[i + 1] = off[i] + len(f)
-    flat = np.fromiter((int(x) for f in faces for x in f), dtype=np.int32, count=int(off[-1]))
+    np.cumsum(np.fromiter(map(len, faces), dtype=np.int64, count=len(faces)), out=off[1:])
+    try:
+        flat = np.fromiter(itertools.chain.from_iterable(faces), dtype=np.int32, count=int(off[-1]))
+    except (TypeError, ValueError):  # entries that numpy does not convert by itself (0-dim tensors)
+        flat = np.fromiter((int(x) for f in faces for x in f), dtype=np.int32, count=int(off[-1]))
     fv = torch.from_numpy(flat).to(verts.device)
     q = _qlist(q, verts.device)
     m = mode_id(mode)

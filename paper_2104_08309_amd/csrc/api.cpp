@@ -914,6 +914,16 @@ pft_status plan_regions(Arena& ar, const int64_t* off, int64_t nreg, int64_t nq,
   return st;
 }
 
+// Whether a polygon mesh of nf faces and nref vertex references goes through its nref - 2 nf fan triangles. In FP32C a
+// fan triangle costs about 105 issue cycles per Q (170 to 210 beyond the fitted phase range), the polygon kernel 59 per
+// edge and 166 per face: at 150 per triangle the line lies between faces of five and six edges (lat-long sphere of 2 624
+// quads and triangles x 125 000 Q, profiled kernels: 0.76 ms through triangles, 1.20 ms through the polygon kernel; a 40-gon prism the
+// other way round). In binary64 a triangle (450) is cheaper than the edge form's library sine and division per vertex
+// at any size.
+bool poly_as_triangles(int64_t nf, int64_t nref, bool c128) {
+  return c128 || 150 * (nref - 2 * nf) <= 59 * nref + 166 * nf;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1157,6 +1167,45 @@ pft_status pft_forward_3d_poly(const void* verts, pft_dtype vdtype, int64_t nv, 
   if (nq == 0) return PFT_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
   ensure_pool();
+  const int64_t ntri = nref - 2 * nf;
+  if (poly_as_triangles(nf, nref, c128)) {
+    Arena ar(s);
+    MeshInfo* info = ar.get<MeshInfo>(1);
+    int64_t* d_off = ar.get<int64_t>(nf + 1);
+    Face64* f64 = ar.get<Face64>(std::max<int64_t>(ntri, 1));
+    Face32* f32 = c128 ? nullptr : ar.get<Face32>(std::max<int64_t>(ntri, 1));
+    FwdArgs a;
+    a.partial = ar.get<double2>((size_t)plan_forward(nq, ntri, c128, -1, a));
+    if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
+    hipError_t e = hipMemcpyAsync(d_off, face_offsets, sizeof(int64_t) * (nf + 1), hipMemcpyHostToDevice, s);
+    if (e == hipSuccess) e = launch_mesh_info_single(verts, vdtype, 3, nv, info, s);
+    if (e == hipSuccess)
+      e = launch_poly_fan_records(verts, vdtype, nv, d_off, face_verts, nf, ntri, info, c128 ? kTauF64 : kTauF32, f64,
+                                  f32, s);
+    if (e != hipSuccess) return hip_fail(e, "polygon prologue");
+    uint32_t* perm = nullptr;
+    if ((st = build_qorder(ar, q, qdtype, nq, nullptr, 1, &perm, s)) != PFT_OK) return st;
+    a.f64 = f64;
+    a.f32 = f32;
+    a.info = info;
+    a.nf = ntri;
+    a.q = q;
+    a.qdtype = qdtype;
+    a.nq = nq;
+    a.perm = perm;
+    a.split_face = nullptr;
+    a.out = out;
+    a.intensity = intensity;
+    a.tau0 = c128 ? kTau0F64 : kTau0F32;
+    a.share_edges = c128 ? 0 : 1;
+    const char* nm = c128 ? "fwdpoly_fp64" : "fwdpoly_fp32c";
+    prof_begin(nm, s);
+    e = c128 ? launch_fwd3d_fp64(a, s) : launch_fwd3d_fp32c(a, s);
+    prof_end(nm, s);
+    if (e != hipSuccess) return hip_fail(e, "polygon transform");
+    e = launch_fwd3d_finish(a, c128 ? 1 : 0, s);
+    return e == hipSuccess ? PFT_OK : hip_fail(e, "3D finish");
+  }
   // tiles of consecutive faces: at most kTileFP faces and kTileV vertex records each
   std::vector<PolyTile> tiles;
   for (int64_t f = 0; f < nf;) {
@@ -1174,9 +1223,9 @@ pft_status pft_forward_3d_poly(const void* verts, pft_dtype vdtype, int64_t nv, 
   int64_t* d_off = ar.get<int64_t>(nf + 1);
   FaceP64* f64 = ar.get<FaceP64>(std::max<int64_t>(nf, 1));
   VtxP64* v64 = ar.get<VtxP64>(std::max<int64_t>(nref, 1));
-  FaceP32* f32 = c128 ? nullptr : ar.get<FaceP32>(std::max<int64_t>(nf, 1));
-  VtxP32* v32 = c128 ? nullptr : ar.get<VtxP32>(std::max<int64_t>(nref, 1));
-  const int64_t qblocks = cdiv(nq, (int64_t)kBlock * (c128 ? 1 : kQPTPoly));
+  FaceP32* f32 = ar.get<FaceP32>(std::max<int64_t>(nf, 1));
+  VtxP32* v32 = ar.get<VtxP32>(std::max<int64_t>(nref, 1));
+  const int64_t qblocks = cdiv(nq, (int64_t)kBlock * kQPTPoly);
   const int64_t sp = std::max<int64_t>(1, std::min<int64_t>(cdiv(kTargetBlocks, qblocks), ntiles));
   const int64_t per = std::max<int64_t>(1, cdiv(ntiles, sp));
   const int splits = (int)std::max<int64_t>(1, cdiv(ntiles, per));
@@ -1187,8 +1236,8 @@ pft_status pft_forward_3d_poly(const void* verts, pft_dtype vdtype, int64_t nv, 
   hipError_t e = hipMemcpyAsync(d_off, face_offsets, sizeof(int64_t) * (nf + 1), hipMemcpyHostToDevice, s);
   if (e == hipSuccess) e = launch_mesh_info_single(verts, vdtype, 3, nv, info, s);
   if (e == hipSuccess)
-    e = launch_poly_records(verts, vdtype, nv, d_off, face_verts, nf, info, c128 ? kTauF64 : kTauF32, f64, v64, s);
-  if (e == hipSuccess && !c128) e = launch_poly_records32(f64, v64, nf, kTauRel32, f32, v32, s);
+    e = launch_poly_records(verts, vdtype, nv, d_off, face_verts, nf, info, kTauF32, f64, v64, s);
+  if (e == hipSuccess) e = launch_poly_records32(f64, v64, nf, kTauRel32, f32, v32, s);
   if (e != hipSuccess) return hip_fail(e, "polygon prologue");
   uint32_t* perm = nullptr;
   if ((st = build_qorder(ar, q, qdtype, nq, nullptr, 1, &perm, s)) != PFT_OK) return st;
@@ -1207,7 +1256,7 @@ pft_status pft_forward_3d_poly(const void* verts, pft_dtype vdtype, int64_t nv, 
   a.partial = partial;
   a.out = out;
   a.intensity = intensity;
-  a.tau0 = c128 ? kTau0F64 : kTau0F32;
+  a.tau0 = kTau0F32;
   PolyArgs pa;
   pa.f64 = f64;
   pa.v64 = v64;
@@ -1216,12 +1265,11 @@ pft_status pft_forward_3d_poly(const void* verts, pft_dtype vdtype, int64_t nv, 
   pa.tiles = d_tiles;
   pa.ntiles = ntiles;
   pa.tiles_per_split = per;
-  const char* nm = c128 ? "fwdpoly_fp64" : "fwdpoly_fp32c";
-  prof_begin(nm, s);
-  e = c128 ? launch_fwdpoly_fp64(a, pa, s) : launch_fwdpoly_fp32c(a, pa, s);
-  prof_end(nm, s);
+  prof_begin("fwdpoly_fp32c", s);
+  e = launch_fwdpoly_fp32c(a, pa, s);
+  prof_end("fwdpoly_fp32c", s);
   if (e != hipSuccess) return hip_fail(e, "polygon transform");
-  e = launch_fwd3d_finish(a, c128 ? 1 : 0, s);
+  e = launch_fwd3d_finish(a, 0, s);
   return e == hipSuccess ? PFT_OK : hip_fail(e, "3D finish");
 }
 

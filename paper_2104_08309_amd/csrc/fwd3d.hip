@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kFwdBlock, fwd_waves(QPT)) void fwd3d_fp32c_kernel(
   float qmax = 0.0f;
 #pragma unroll
   for (int k = 0; k < QPT; ++k) qmax = fmaxf(qmax, sqrtf(Q2[k]));
-  const bool check = __builtin_amdgcn_readfirstlane((int)fit_range_test_needed(wave_max(qmax), a.info[0].rho)) != 0;
+  const bool check = __builtin_amdgcn_readfirstlane((int)fit_range_test_needed(wave_max(qmax), fmax(a.info[0].rho, a.info[0].fan_rho))) != 0;
   float sr[QPT], si[QPT], cr[QPT], ci[QPT];
 #pragma unroll
   for (int k = 0; k < QPT; ++k) sr[k] = si[k] = cr[k] = ci[k] = 0.0f;

@@ -1,6 +1,7 @@
-// Forward 3D transform of a closed mesh of planar polygon faces: eq.
-// sum_elements_3d with nu_m edges per face, evaluated natively (nu edge terms
-// per face instead of 3 (nu - 2) for a triangulation).
+// FP32C forward 3D transform of a closed mesh of planar polygon faces of many
+// edges: eq. sum_elements_3d with nu_m edges per face, evaluated natively (nu
+// edge terms per face; faces of few edges, and the binary64 form, go through
+// their fan triangles' face integrals, fwd3d.hip).
 //
 // Per face, with u_k = r_k - g (g the vertex mean), N = sum_k u_k x u_{k+1}
 // = 2 A n, P = Q x N, psi_k = Q.u_k / 2:
@@ -15,87 +16,6 @@
 
 namespace pft {
 namespace {
-
-// ---------------------------------------------------------------------------
-// binary64
-// ---------------------------------------------------------------------------
-// fan-triangle series of a polygon face: sum_t 2A_t exp(iQ.g_t) series(delta_t), relative to exp(iQ.g)
-__device__ void poly_fan_series_f64(const FaceP64& F, const VtxP64* V, const double* Q, double& jr, double& ji) {
-  jr = ji = 0.0;
-  const double* a = V[0].u;
-  const double qa = Q[0] * a[0] + Q[1] * a[1] + Q[2] * a[2];
-  for (int l = 1; l + 1 < F.nv; ++l) {
-    const double* b = V[l].u;
-    const double* c = V[l + 1].u;
-    const double e1[3] = {b[0] - a[0], b[1] - a[1], b[2] - a[2]};
-    const double e2[3] = {c[0] - a[0], c[1] - a[1], c[2] - a[2]};
-    const double cr[3] = {e1[1] * e2[2] - e1[2] * e2[1], e1[2] * e2[0] - e1[0] * e2[2], e1[0] * e2[1] - e1[1] * e2[0]};
-    const double two_a = (cr[0] * F.N[0] + cr[1] * F.N[1] + cr[2] * F.N[2]) * F.invN;
-    const double qb = Q[0] * b[0] + Q[1] * b[1] + Q[2] * b[2];
-    const double qc = Q[0] * c[0] + Q[1] * c[1] + Q[2] * c[2];
-    const double qt = (qa + qb + qc) / 3.0;  // phase of the triangle's centroid relative to g
-    double sr, si;
-    face_series_f64(qa - qt, qb - qt, qc - qt, sr, si, 1e-17);
-    double st, ct;
-    sincos(qt, &st, &ct);
-    jr += two_a * (ct * sr - st * si);
-    ji += two_a * (ct * si + st * sr);
-  }
-}
-
-__device__ void poly_term_f64(const FaceP64& F, const VtxP64* V, const double* Q, double& Tr, double& Ti) {
-  const double QN = Q[0] * F.N[0] + Q[1] * F.N[1] + Q[2] * F.N[2];
-  const double Px = Q[1] * F.N[2] - Q[2] * F.N[1];
-  const double Py = Q[2] * F.N[0] - Q[0] * F.N[2];
-  const double Pz = Q[0] * F.N[1] - Q[1] * F.N[0];
-  const double P2 = Px * Px + Py * Py + Pz * Pz;
-  double sf, cf;
-  sincos(Q[0] * F.g[0] + Q[1] * F.g[1] + Q[2] * F.g[2], &sf, &cf);
-  double Sr = 0.0, Si = 0.0, co;
-  if (P2 < F.thr) {
-    // T = -i (Q.n) exp(iQ.g) J
-    double jr, ji;
-    poly_fan_series_f64(F, V, Q, jr, ji);
-    co = QN * F.invN;
-    Sr = ji;
-    Si = -jr;
-  } else {
-    const double* u0 = V[0].u;
-    const double psi0 = 0.5 * (Q[0] * u0[0] + Q[1] * u0[1] + Q[2] * u0[2]);
-    const double pi0 = Px * u0[0] + Py * u0[1] + Pz * u0[2];
-    double s0, c0;
-    sincos(psi0, &s0, &c0);
-    double psi_a = psi0, pi_a = pi0, s_a = s0, c_a = c0;
-    for (int k = 1; k <= F.nv; ++k) {
-      double psi_b, pi_b, s_b, c_b;
-      if (k < F.nv) {
-        const double* u = V[k].u;
-        psi_b = 0.5 * (Q[0] * u[0] + Q[1] * u[1] + Q[2] * u[2]);
-        pi_b = Px * u[0] + Py * u[1] + Pz * u[2];
-        sincos(psi_b, &s_b, &c_b);
-      } else {
-        psi_b = psi0;
-        pi_b = pi0;
-        s_b = s0;
-        c_b = c0;
-      }
-      // edge a -> b: w = P.d, sinc(psi_b - psi_a), exp(i (psi_a + psi_b))
-      const double w = pi_b - pi_a;
-      const double sg = sinc_f64(psi_b - psi_a, s_b * c_a - c_b * s_a);
-      const double er = c_a * c_b - s_a * s_b, ei = s_a * c_b + c_a * s_b;
-      Sr += w * sg * er;
-      Si += w * sg * ei;
-      psi_a = psi_b;
-      pi_a = pi_b;
-      s_a = s_b;
-      c_a = c_b;
-    }
-    co = QN / fmax(P2, 1e-300);
-  }
-  const double Ur = co * cf, Ui = co * sf;
-  Tr = Ur * Sr - Ui * Si;
-  Ti = Ur * Si + Ui * Sr;
-}
 
 // small |Q|: the fan of tetrahedra (t, a, b, c) over the face's fan triangles, as tet_term_f64
 __device__ void poly_tet_f64(const FaceP64& F, const VtxP64* V, const double* Q, double& xr, double& xi) {
@@ -130,39 +50,6 @@ __device__ __forceinline__ void stage_tile(const PolyTile& tl, const FR* fsrc, c
   const uint32_t* vs = reinterpret_cast<const uint32_t*>(vsrc + tl.v0);
   uint32_t* vd = reinterpret_cast<uint32_t*>(vdst);
   for (int i = threadIdx.x; i < nvb / 4; i += kBlock) vd[i] = vs[i];
-}
-
-__global__ __launch_bounds__(kBlock) void fwdpoly_fp64_kernel(FwdArgs a, PolyArgs p) {
-  __shared__ FaceP64 fh[kTileFP];
-  __shared__ VtxP64 vr[kTileV];
-  const int64_t qi = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const bool active = qi < a.nq;
-  double Q[3] = {0.0, 0.0, 0.0};
-  if (active) load_q3(a.q, a.qdtype, a.perm ? (int64_t)a.perm[qi] : qi, Q);
-  const double Q2 = Q[0] * Q[0] + Q[1] * Q[1] + Q[2] * Q[2];
-  const bool small = sqrt(Q2) * a.info[0].R < a.tau0;
-  const int64_t t_begin = (int64_t)blockIdx.y * p.tiles_per_split;
-  const int64_t t_end = min(p.ntiles, t_begin + p.tiles_per_split);
-  double xr = 0.0, xi = 0.0;
-  for (int64_t t = t_begin; t < t_end; ++t) {
-    const PolyTile tl = p.tiles[t];
-    __syncthreads();
-    stage_tile(tl, p.f64, p.v64, fh, vr);
-    __syncthreads();
-    for (int j = 0; j < tl.f1 - tl.f0; ++j) {
-      const FaceP64 F = fh[j];
-      const VtxP64* V = vr + (F.v0 - tl.v0);
-      if (!small) {
-        double Tr, Ti;
-        poly_term_f64(F, V, Q, Tr, Ti);
-        xr += Tr;
-        xi += Ti;
-      } else {
-        poly_tet_f64(F, V, Q, xr, xi);
-      }
-    }
-  }
-  if (active) store_stream(a.partial + (int64_t)blockIdx.y * a.nq + qi, make_double2(xr, xi));
 }
 
 // ---------------------------------------------------------------------------
@@ -332,12 +219,6 @@ __global__ __launch_bounds__(kBlock) void fwdpoly_fp32c_kernel(FwdArgs a, PolyAr
 }
 
 }  // namespace
-
-hipError_t launch_fwdpoly_fp64(const FwdArgs& a, const PolyArgs& p, hipStream_t s) {
-  dim3 grid((unsigned)((a.nq + kBlock - 1) / kBlock), (unsigned)a.splits);
-  fwdpoly_fp64_kernel<<<grid, kBlock, 0, s>>>(a, p);
-  return hipGetLastError();
-}
 
 hipError_t launch_fwdpoly_fp32c(const FwdArgs& a, const PolyArgs& p, hipStream_t s) {
   dim3 grid((unsigned)((a.nq + kBlock * kQPTPoly - 1) / (kBlock * kQPTPoly)), (unsigned)a.splits);

@@ -128,7 +128,7 @@ struct MeshInfo {
   double t[3];
   double R;
   double rho;
-  double pad;
+  double fan_rho;  // the same over the fan triangles of polygon faces (0 for a triangle mesh)
 };
 
 // FP32C phase range. The binary32 form takes every phase it evaluates relative
@@ -314,6 +314,12 @@ struct PolyArgs {
   int64_t tiles_per_split;
 };
 
+// prologue.hip: the fan triangles (v_0, v_l, v_{l+1}) of polygon faces as triangle records (triangle l - 1 of face m at
+// face_off[m] - 2 m + l - 1), chained across the fan's inner edges; a face with an out-of-range index or no area gives
+// empty ones. f32 NULL: not written.
+hipError_t launch_poly_fan_records(const void* verts, int vdtype, int64_t nv, const int64_t* face_off,
+                                   const int32_t* face_verts, int64_t nf, int64_t ntri, MeshInfo* info, double tau,
+                                   Face64* f64, Face32* f32, hipStream_t s);
 // prologue.hip: records of polygon faces (face_off: device CSR offsets into face_verts)
 hipError_t launch_poly_records(const void* verts, int vdtype, int64_t nv, const int64_t* face_off,
                                const int32_t* face_verts, int64_t nf, MeshInfo* info, double tau, FaceP64* f64,
@@ -407,8 +413,7 @@ hipError_t launch_dq3d_fp32c(const DqArgs& a, hipStream_t s);
 // the dL/drho partials when r.rho_part is set.
 hipError_t launch_dq_finish(const DqArgs& a, const RegionArgs& r, int go_c128, void* grad_q, int gq_dtype,
                             hipStream_t s);
-// fwdpoly.hip: the forward over polygon faces (FwdArgs's face fields unused; splits over tiles)
-hipError_t launch_fwdpoly_fp64(const FwdArgs& a, const PolyArgs& p, hipStream_t s);
+// fwdpoly.hip: the FP32C forward over polygon faces (FwdArgs's face fields unused; splits over tiles)
 hipError_t launch_fwdpoly_fp32c(const FwdArgs& a, const PolyArgs& p, hipStream_t s);
 
 // bwd3d.hip

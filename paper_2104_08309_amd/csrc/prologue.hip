@@ -281,6 +281,70 @@ __global__ __launch_bounds__(256) void poly64_kernel(const void* verts, int vdty
   raise_rho(info, 0, ext2);
 }
 
+// One thread per polygon face: its fan triangles' records (each in the traversal (v_l, v_0, v_{l+1}), so that the inner
+// edge it shares with the previous one is edge 0 and the one it passes on edge 1). rho keeps the face's own extent.
+__global__ __launch_bounds__(256) void poly_fan_kernel(const void* verts, int vdtype, int64_t nv,
+                                                       const int64_t* face_off, const int32_t* face_verts, int64_t nf,
+                                                       MeshInfo* info, double tau, Face64* out) {
+  const int64_t m = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  double ext2 = 0.0, fan2 = 0.0;
+  if (m < nf) {
+    const int64_t b = face_off[m], e = face_off[m + 1];
+    const int n = (int)(e - b);
+    bool ok = n >= 3;
+    for (int64_t k = b; k < e; ++k) ok = ok && face_verts[k] >= 0 && face_verts[k] < nv;
+    const double t[3] = {info[0].t[0], info[0].t[1], info[0].t[2]};
+    auto vertex = [&](int64_t k, double* r) {
+      load_vertex(verts, vdtype, 3, face_verts[k], r);
+      for (int c = 0; c < 3; ++c) r[c] -= t[c];
+    };
+    double g[3] = {0.0, 0.0, 0.0}, a[3] = {0.0, 0.0, 0.0}, N[3] = {0.0, 0.0, 0.0};
+    if (ok) {
+      for (int64_t k = b; k < e; ++k) {
+        double r[3];
+        vertex(k, r);
+        for (int c = 0; c < 3; ++c) g[c] += r[c] / (double)n;
+      }
+      vertex(b, a);
+      double u[3];  // previous vertex relative to the first
+      for (int64_t k = b; k < e; ++k) {
+        double r[3], d2 = 0.0;
+        vertex(k, r);
+        for (int c = 0; c < 3; ++c) d2 += (r[c] - g[c]) * (r[c] - g[c]);
+        ext2 = fmax(ext2, d2);
+        for (int c = 0; c < 3; ++c) r[c] -= a[c];
+        if (k > b) {
+          N[0] += u[1] * r[2] - u[2] * r[1];
+          N[1] += u[2] * r[0] - u[0] * r[2];
+          N[2] += u[0] * r[1] - u[1] * r[0];
+        }
+        for (int c = 0; c < 3; ++c) u[c] = r[c];
+      }
+      ok = N[0] * N[0] + N[1] * N[1] + N[2] * N[2] > 0.0;
+    }
+    if (!ok) ext2 = 0.0;
+    for (int l = 1; l + 1 < n; ++l) {
+      Face64 f;
+      if (ok) {
+        double v1[3], v2[3];
+        vertex(b + l, v1);
+        vertex(b + l + 1, v2);
+        make_face64(a, v1, v2, tau, f);
+        f.pad[2] = l > 1 ? 3.0 : 2.0;  // reversed traversal, linked to the previous triangle of the fan
+        fan2 = fmax(fan2, face_extent2(f));
+      } else {
+        empty_face64(f);
+      }
+      out[b - 2 * m + l - 1] = f;
+    }
+  }
+  raise_rho(info, 0, ext2);
+  for (int off = 32; off > 0; off >>= 1) fan2 = fmax(fan2, __shfl_xor(fan2, off));
+  if ((threadIdx.x & 63) == 0 && fan2 > 0.0)
+    atomicMax(reinterpret_cast<unsigned long long*>(&info[0].fan_rho),
+              (unsigned long long)__double_as_longlong(sqrt(fan2)));
+}
+
 // FP32C polygon records: orthonormal in-plane basis (e1 along the first edge of
 // non-zero length, e2 = n x e1) and the per-vertex coefficients.
 __global__ __launch_bounds__(256) void poly32_kernel(const FaceP64* fin, const VtxP64* vin, int64_t nf,
@@ -598,6 +662,15 @@ hipError_t launch_mesh_records(const void* verts, int vdtype, int64_t nv, const 
     face64_kernel<<<grid_for(nf), 256, 0, s>>>(verts, vdtype, nv, tris, nf, info, tau, rec.f64, order, meta);
   hipError_t e = hipGetLastError();
   return e == hipSuccess ? launch_face_records(rec, nf, s) : e;
+}
+
+hipError_t launch_poly_fan_records(const void* verts, int vdtype, int64_t nv, const int64_t* face_off,
+                                   const int32_t* face_verts, int64_t nf, int64_t ntri, MeshInfo* info, double tau,
+                                   Face64* f64, Face32* f32, hipStream_t s) {
+  if (nf <= 0) return hipSuccess;
+  poly_fan_kernel<<<grid_for(nf), 256, 0, s>>>(verts, vdtype, nv, face_off, face_verts, nf, info, tau, f64);
+  hipError_t e = hipGetLastError();
+  return e == hipSuccess ? launch_face_records(MeshRecords{f64, f32, nullptr, nullptr}, ntri, s) : e;
 }
 
 hipError_t launch_poly_records(const void* verts, int vdtype, int64_t nv, const int64_t* face_off,
