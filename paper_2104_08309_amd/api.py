@@ -171,6 +171,7 @@ def q_order(q: torch.Tensor) -> torch.Tensor:
 # like the face orders; below the sorting size the kernels keep the list order and nothing is cached.
 _Q_ORDER_CACHE: dict = {}
 _Q_ORDER_MIN = 8192
+_FEW_FACES, _FEW_FACES_LONG, _FEW_LONG_NQ = 16, 32, 1 << 18  # pft_forward_3d takes these in the list order of Q
 
 
 def _q_order_arg(q_order, q_key, q: torch.Tensor):
@@ -223,7 +224,10 @@ def forward_3d(verts: torch.Tensor, tris: torch.Tensor, q: torch.Tensor, mode: s
     out = torch.empty(q.shape[0], dtype=cdt, device=verts.device)
     inten = torch.empty(q.shape[0], dtype=rdt, device=verts.device) if intensity else None
     fo, fm = _order_arg(order, tris_key, tris, verts.shape[0], m)
-    qo = _q_order_arg(q_order, q_key, q)
+    # (the few-face FP32C kernel takes the Q in the list order: an order computed for it would be wasted)
+    few = m == PFT_FP32C and fo is None and \
+        tris.shape[0] <= (_FEW_FACES_LONG if q.shape[0] >= _FEW_LONG_NQ else _FEW_FACES)
+    qo = _q_order_arg(None if few and isinstance(q_order, str) and q_order == "auto" else q_order, q_key, q)
     with torch.cuda.device(verts.device):
         if fo is None and qo is None:
             check(_lib.load().pft_forward_3d(_ptr(verts), _real_dtype_id(verts, "verts"), verts.shape[0],

@@ -324,6 +324,14 @@ FwdPlan fwd_plan(int64_t nq, int64_t nf, bool c128) {
   return p;
 }
 
+// Whether an FP32C forward goes through the few-face kernel. Measured, split form -> few-face form (us a call, random
+// Q of |Q| about 9): 16 faces 17.5 -> 15.2 at 2 000 Q, 22.7 -> 17.2 at 2^16, 201 -> 108 at 2^21; 32 faces 22 -> 34 at
+// 30 000 Q (one wavefront walks them all while the chip idles), 49 -> 39 at 2^18, 251 -> 186 at 2^21; 64 faces 27 -> 57
+// at 30 000, 70 -> 71 at 2^18, 358 -> 356 at 2^21.
+bool few_faces(int64_t nq, int64_t nf, bool c128, bool chained) {
+  return !c128 && !chained && nf > 0 && nf <= (nq >= (1 << 18) ? 32 : 16);
+}
+
 // Face splits of a single-mesh forward (sets a.splits and a.faces_per_split; returns the double2 partial
 // entries they need), capped so that the partials fit in max_partials entries when that is > 0.
 int64_t plan_forward(int64_t nq, int64_t nf, bool c128, int64_t max_partials, FwdArgs& a) {
@@ -812,14 +820,17 @@ pft_status forward3d_core(Arena& ar, const void* verts, int vdtype, int64_t nv, 
   Face64* f64 = ar.get<Face64>(std::max<int64_t>(nf, 1));
   Face32* f32 = c128 ? nullptr : ar.get<Face32>(std::max<int64_t>(nf, 1));
   FwdArgs a;
+  const bool few = few_faces(nq, nf, c128, order != nullptr);
   const int64_t n_partial = plan_forward(nq, nf, c128, max_partials, a);
-  double2* partial = ar.get<double2>((size_t)n_partial);
+  double2* partial = few ? nullptr : ar.get<double2>((size_t)n_partial);
   if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
   hipError_t e = launch_mesh_records(verts, vdtype, nv, tris, nf, info, c128 ? kTauF64 : kTauF32,
                                      MeshRecords{f64, f32, nullptr, nullptr}, s, order, meta);
   if (e != hipSuccess) return hip_fail(e, "3D prologue");
   uint32_t* perm = nullptr;
-  if (q_order)
+  if (few)  // the list order
+    st = PFT_OK;
+  else if (q_order)
     st = caller_qorder(ar, q_order, nq, &perm, s);
   else if (sort_q)
     st = build_qorder(ar, q, qdtype, nq, nullptr, 1, &perm, s);
@@ -840,9 +851,10 @@ pft_status forward3d_core(Arena& ar, const void* verts, int vdtype, int64_t nv, 
   a.share_edges = (order != nullptr && !c128) ? 1 : 0;
   const char* nm = main_name(true, mode);
   if (profile) prof_begin(nm, s);
-  e = c128 ? launch_fwd3d_fp64(a, s) : launch_fwd3d_fp32c(a, s);
+  e = c128 ? launch_fwd3d_fp64(a, s) : few ? launch_fwd3d_few_fp32c(a, s) : launch_fwd3d_fp32c(a, s);
   if (profile) prof_end(nm, s);
   if (e != hipSuccess) return hip_fail(e, "3D transform");
+  if (few) return PFT_OK;
   e = launch_fwd3d_finish(a, c128 ? 1 : 0, s);
   if (e != hipSuccess) return hip_fail(e, "3D finish");
   return PFT_OK;

@@ -154,8 +154,9 @@ __device__ __forceinline__ float origin_turns_plain(const double* Q, const doubl
   const double ph = Q[0] * gt[0] + Q[1] * gt[1] + Q[2] * gt[2];
   return (float)(ph - rint(ph));
 }
+constexpr double kWidePhase32 = 3.2e6;                                // 2^19 turns = 3.29e6 rad
 __device__ __forceinline__ bool wide_phases32(double q2, double R) {  // |g| <= R; NaN counts as beyond
-  return __any(!(sqrt(q2) * R <= 3.2e6));                             // 2^19 turns = 3.29e6 rad
+  return __any(!(sqrt(q2) * R <= kWidePhase32));
 }
 
 // Whether an origin phase Q.g of a wavefront can exceed the range of sincos64: |g| <= R, the mesh's radius (q2

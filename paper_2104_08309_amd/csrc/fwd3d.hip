@@ -277,16 +277,9 @@ __global__ __launch_bounds__(kFwdBlock, fwd_waves(QPT)) void fwd3d_fp32c_kernel(
   }
 }
 
-// Sum the splits in order, apply exp(i Q.t) and 1/|Q|^2, write F and |F|^2 at
-// the caller's index of the visited Q.
-__global__ __launch_bounds__(256) void fwd3d_finish_kernel(FwdArgs a, int out_c128) {
-  const int64_t qi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (qi >= a.nq) return;
-  const int64_t dst = a.perm ? (int64_t)a.perm[qi] : qi;
-  double Q[3];
-  load_q3(a.q, a.qdtype, dst, Q);
-  double xr, xi;
-  fwd_partial_sum(a, qi, xr, xi);
+// F and |F|^2 of one Q from its centred sum x: exp(i Q.t), and 1/|Q|^2 unless the small-|Q| fan gave x.
+__device__ __forceinline__ void write_transform(const FwdArgs& a, int out_c128, int64_t dst, const double* Q, double xr,
+                                                double xi) {
   const MeshInfo mi = a.info[0];
   const double Q2 = Q[0] * Q[0] + Q[1] * Q[1] + Q[2] * Q[2];
   const bool small = sqrt(Q2) * mi.R < a.tau0;
@@ -295,7 +288,7 @@ __global__ __launch_bounds__(256) void fwd3d_finish_kernel(FwdArgs a, int out_c1
     xi /= Q2;
   }
   double st, ct;
-  sincos(Q[0] * mi.t[0] + Q[1] * mi.t[1] + Q[2] * mi.t[2], &st, &ct);
+  sincos_any64(fit64(), Q[0] * mi.t[0] + Q[1] * mi.t[1] + Q[2] * mi.t[2], &st, &ct);
   double Fr = ct * xr - st * xi;
   double Fi = ct * xi + st * xr;
   if (!out_c128 && fp32c_phase_out_of_range(sqrt(Q2), mi)) Fr = Fi = quiet_nan();  // beyond the FP32C phase range
@@ -306,6 +299,88 @@ __global__ __launch_bounds__(256) void fwd3d_finish_kernel(FwdArgs a, int out_c1
     if (a.out) static_cast<float2*>(a.out)[dst] = make_float2((float)Fr, (float)Fi);
     if (a.intensity) static_cast<float*>(a.intensity)[dst] = (float)(Fr * Fr + Fi * Fi);
   }
+}
+
+// x + t as its own operation, so that a sum of terms does not depend on where they were computed.
+__device__ __forceinline__ void add_term(double& x, double t) {
+#pragma clang fp contract(off)
+  x = x + t;
+}
+
+// The FP32C forward of a mesh of few faces (at most one LDS tile): each thread holds one Q in the list order, walks all
+// faces and writes F itself. No face splits, so no partial sums and no finish launch, and no Q order: at a dozen faces
+// the split form's wavefronts loaded, reduced and finished each Q for three faces each (12 faces x 2^21 Q of |Q| about
+// 9: 187 -> 88 us a call; x 128^3 grid: 127 -> 72; two Q a thread instead of one: 91). Bound by issue: of the faces'
+// polynomials and phases for small faces, of the edge terms' transcendentals for large ones.
+__global__ __launch_bounds__(kBlock, 8) void fwd3d_few_fp32c_kernel(FwdArgs a) {
+  __shared__ Face32 tile[kTileF32];
+  const int nt = (int)a.nf;
+  for (int i = threadIdx.x; i < nt * (int)(sizeof(Face32) / 16); i += kBlock)
+    reinterpret_cast<uint4*>(tile)[i] = reinterpret_cast<const uint4*>(a.f32)[i];
+  __syncthreads();
+  const double R = a.info[0].R;
+  const int64_t qi = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  QReg<1> ql;
+  ql.Q[0][0] = ql.Q[0][1] = ql.Q[0][2] = 0.0;
+  if (qi < a.nq) load_q3(a.q, a.qdtype, qi, ql.Q[0]);
+  const double* Q = ql.Q[0];
+  const float qx[1] = {(float)Q[0]}, qy[1] = {(float)Q[1]}, qz[1] = {(float)Q[2]};
+  const double qabs = sqrt(Q[0] * Q[0] + Q[1] * Q[1] + Q[2] * Q[2]);
+  const bool small = qi < a.nq && qabs * R < a.tau0;
+  ql.wide[0] = !(qabs * R <= kWidePhase32);
+  ql.any_wide = __any(ql.wide[0]) != 0;
+  float tr[1] = {0.0f}, ti[1] = {0.0f};
+  FwdCarry<1> carry;
+  carry.reset();
+  const double rho = fmax(a.info[0].rho, a.info[0].fan_rho);
+  if (__builtin_amdgcn_readfirstlane((int)fit_range_test_needed(wave_max((float)qabs), rho)))
+    fwd_tile_fp32c<1, false, true>(tile, nt, qx, qy, qz, ql, tr, ti, carry);
+  else
+    fwd_tile_fp32c<1, false, false>(tile, nt, qx, qy, qz, ql, tr, ti, carry);
+  double xr = (double)tr[0], xi = (double)ti[0];
+  // The small-|Q| fan, its terms added in face order either way: a few such Q share the wavefront, a face per lane
+  // (one after the other by their own lanes, the few in 2 000 random Q took 23 us at 12 faces); many take theirs side
+  // by side.
+  uint64_t todo = __ballot(small);
+  if (2 * __popcll(todo) <= nt) {
+    const int lane = threadIdx.x & 63;
+    for (; todo; todo &= todo - 1) {
+      const int src = __ffsll((unsigned long long)todo) - 1;
+      const double Qs[3] = {__shfl(Q[0], src), __shfl(Q[1], src), __shfl(Q[2], src)};
+      double tx = 0.0, ty = 0.0, sx = 0.0, sy = 0.0;
+      if (lane < nt) tet_term_f64(a.f64[lane], Qs, tx, ty, kZeroOrigin);
+      for (int j = 0; j < nt; ++j) {
+        add_term(sx, __shfl(tx, j));
+        add_term(sy, __shfl(ty, j));
+      }
+      if (lane == src) {
+        xr = sx;
+        xi = sy;
+      }
+    }
+  } else if (small) {
+    xr = xi = 0.0;
+    for (int j = 0; j < nt; ++j) {
+      double tx = 0.0, ty = 0.0;
+      tet_term_f64(a.f64[j], Q, tx, ty, kZeroOrigin);
+      add_term(xr, tx);
+      add_term(xi, ty);
+    }
+  }
+  if (qi < a.nq) write_transform(a, 0, qi, Q, xr, xi);
+}
+
+// Sum the splits in order, apply exp(i Q.t) and 1/|Q|^2, write F and |F|^2 at
+// the caller's index of the visited Q.
+__global__ __launch_bounds__(256) void fwd3d_finish_kernel(FwdArgs a, int out_c128) {
+  const int64_t qi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (qi >= a.nq) return;
+  const int64_t dst = a.perm ? (int64_t)a.perm[qi] : qi;
+  double Q[3];
+  load_q3(a.q, a.qdtype, dst, Q);
+  double xr, xi;
+  fwd_partial_sum(a, qi, xr, xi);
+  write_transform(a, out_c128, dst, Q, xr, xi);
 }
 
 }  // namespace
@@ -343,6 +418,15 @@ hipError_t launch_fwd3d_fp32c(const FwdArgs& a, hipStream_t s) {
   else
     return hipErrorInvalidValue;
 #undef PFT_FWD3D
+  return hipGetLastError();
+}
+
+hipError_t launch_fwd3d_few_fp32c(const FwdArgs& a, hipStream_t s) {
+  static_assert(kTileF32 <= 64, "a face per lane");
+  if (a.nf > kTileF32) return hipErrorInvalidValue;
+  const int64_t blocks = (a.nq + kBlock - 1) / kBlock;
+  if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+  fwd3d_few_fp32c_kernel<<<(unsigned)blocks, kBlock, 0, s>>>(a);
   return hipGetLastError();
 }
 

@@ -164,31 +164,11 @@ struct FwdCarry {
   __device__ __forceinline__ void reset() { prev = false; }
 };
 
-// The binary64 Q of a thread's NQ points held as binary32 pairs: Q = hi + lo with
-// hi = (float)Q (the binary32 Q of the edge arithmetic) and lo = (float)(Q - hi),
-// i.e. Q to 48 bits (relative error <= 2^-48), for the binary64 origin phase at
-// the anchors, in half the registers of a binary64 copy.
-template <int NQ>
-struct QLow {
-  float lo[NQ][3];
-  __device__ __forceinline__ void set(int k, const double* Q, float hx, float hy, float hz) {
-    lo[k][0] = (float)(Q[0] - (double)hx);
-    lo[k][1] = (float)(Q[1] - (double)hy);
-    lo[k][2] = (float)(Q[2] - (double)hz);
-  }
-  __device__ __forceinline__ double qd(float hi, int k, int j) const { return (double)hi + (double)lo[k][j]; }
-  // The same inside the face loop: the empty asm statement makes the pair opaque at the anchor, so the
-  // compiler forms the binary64 value there instead of hoisting nine binary64 registers out of the loop.
-  __device__ __forceinline__ double qd_here(float hi, int k, int j) const {
-    float h = hi, l = lo[k][j];
-    asm volatile("" : "+v"(h), "+v"(l));
-    return (double)h + (double)l;
-  }
-};
-
-// The same low parts kept in a wavefront's slice of LDS (64 * 3 * NQ floats, lane-major so a wavefront's
-// access is one conflict-free row) instead of nine registers: only the anchors, the chain starts and the
-// small-|Q| fan read them. Each lane reads only what it wrote itself.
+// Where a thread's origin phases come from. QLowLds: the Q as binary32 pairs Q = hi + lo with hi = (float)Q (the
+// binary32 Q of the edge arithmetic) and lo = (float)(Q - hi), i.e. Q to 48 bits (relative error <= 2^-48), the low
+// parts in a wavefront's slice of LDS (64 * 3 * NQ floats, lane-major so a wavefront's access is one conflict-free
+// row) instead of nine registers: only the anchors, the chain starts and the small-|Q| fan read them. Each lane reads
+// only what it wrote itself.
 template <int NQ>
 struct QLowLds {
   float* lo;  // this wavefront's slice
@@ -201,7 +181,24 @@ struct QLowLds {
   __device__ __forceinline__ double qd(float hi, int k, int j) const {
     return (double)hi + (double)lo[(k * 3 + j) * 64 + lane];
   }
-  __device__ __forceinline__ double qd_here(float hi, int k, int j) const { return qd(hi, k, j); }
+  __device__ __forceinline__ float turns(int k, float hx, float hy, float hz, const double* gt) const {
+    const double Q[3] = {qd(hx, k, 0), qd(hy, k, 1), qd(hz, k, 2)};
+    return origin_turns_plain(Q, gt);
+  }
+};
+
+// QReg: the binary64 Q themselves, for lists of few faces without a chain, where every pair forms its origin phase.
+// wide: beyond the fixed-point range (per Q, so a Q's value does not depend on its wavefront; any_wide uniform).
+template <int NQ>
+struct QReg {
+  double Q[NQ][3];
+  bool wide[NQ];
+  bool any_wide;
+  __device__ __forceinline__ float turns(int k, float, float, float, const double* gt) const {
+    float r = origin_turns(Q[k], gt);
+    if (__builtin_expect(any_wide, 0)) r = wide[k] ? origin_turns_plain(Q[k], gt) : r;
+    return r;
+  }
 };
 
 // Orders a wavefront's LDS accesses around a tile it stages for itself: its stores are complete before
@@ -291,9 +288,7 @@ __device__ __forceinline__ void fwd_face_fp32c(const Face32& f, const float* qx,
   } else {
 #pragma unroll
     for (int k = 0; k < NQ; ++k) {
-      const double ph =
-          ql.qd_here(qx[k], k, 0) * f.gt[0] + ql.qd_here(qy[k], k, 1) * f.gt[1] + ql.qd_here(qz[k], k, 2) * f.gt[2];
-      r[k] = (float)(ph - rint(ph));
+      r[k] = ql.turns(k, qx[k], qy[k], qz[k], f.gt);
       if (SHARE) c.t[k] = r[k] - p0[k];
     }
   }
