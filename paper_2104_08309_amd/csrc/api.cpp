@@ -782,6 +782,14 @@ pft_status pft_forward_2d(const double* verts, int64_t nv, const int64_t* contou
   if (nq == 0) return PFT_OK;
   hipStream_t s = static_cast<hipStream_t>(stream);
   ensure_pool();
+  // One contour of at most an LDS tile of edges: one launch, every block reading all vertices (64 edges x 128^2 Q: the
+  // prologue's two launches took 6 of 17 us; 4 to 256 edges x 100 to 2^18 Q are all faster).
+  if ((contour_offsets == nullptr || ncontours == 1) && nv >= 1 && nv <= kTileE) {
+    prof_begin("fwd2d_fp64", s);
+    const hipError_t e1 = launch_fwd2d_own(verts, nv, q, nq, kTau02D, out, s);
+    prof_end("fwd2d_fp64", s);
+    return e1 == hipSuccess ? PFT_OK : hip_fail(e1, "2D transform");
+  }
   Arena ar(s);
   MeshInfo* info = ar.get<MeshInfo>(1);
   Edge2D* edges = ar.get<Edge2D>(std::max<int64_t>(nv, 1));
@@ -795,7 +803,7 @@ pft_status pft_forward_2d(const double* verts, int64_t nv, const int64_t* contou
   e = launch_edges2d(verts, nv, d_off, ncontours, info, edges, s);
   if (e != hipSuccess) return hip_fail(e, "2D prologue");
   prof_begin("fwd2d_fp64", s);
-  e = launch_fwd2d(edges, nv, info, 0.0, q, nq, kTau02D, out, s);
+  e = launch_fwd2d(edges, nv, info, q, nq, kTau02D, out, s);
   prof_end("fwd2d_fp64", s);
   if (e != hipSuccess) return hip_fail(e, "2D transform");
   return PFT_OK;

@@ -88,7 +88,7 @@ constexpr int kTileFB32 = PFT_TILEFB32;  // faces per block in the FP32C adjoint
 #define PFT_QPT_DQ 2
 #endif
 constexpr int kQPTDQ = PFT_QPT_DQ;  // Q per thread in the FP32C grad_Q kernel
-constexpr int kTileE = 64;         // 2D edges staged in LDS per tile
+constexpr int kTileE = 256;        // 2D edges staged in LDS per tile
 
 // Series thresholds (dimensionless). A (Q, face) pair uses the face's simplex
 // series instead of the edge sum when |Q_perp| L_face < tau (absolute test) or
@@ -477,8 +477,10 @@ hipError_t launch_gather_vertices(const uint32_t* keys_sorted, const uint32_t* v
                                   const double* contrib, int64_t nv, void* grad, int vdtype, hipStream_t s);
 
 // fwd2d.hip
-hipError_t launch_fwd2d(const Edge2D* edges, int64_t ne, const MeshInfo* info, double area_hint, const double* q,
-                        int64_t nq, double tau0, double* out, hipStream_t s);
+hipError_t launch_fwd2d(const Edge2D* edges, int64_t ne, const MeshInfo* info, const double* q, int64_t nq, double tau0,
+                        double* out, hipStream_t s);
+hipError_t launch_fwd2d_own(const double* verts, int64_t nv, const double* q, int64_t nq, double tau0, double* out,
+                            hipStream_t s);  // one contour of 1 .. kTileE vertices, no prologue
 
 // batch.hip
 struct BatchItemFwd {   // one (mesh, Q-tile, face-chunk) work item
