@@ -69,7 +69,7 @@ __global__ __launch_bounds__(kBlock) void batch_fwd_fp64_kernel(const BatchGroup
     double Qd[3] = {0.0, 0.0, 0.0};
     if (active) load_q3(q, qdtype, perm ? (int64_t)perm[it.q0 + lane] : it.q0 + lane, Qd);
     const double Q2d = Qd[0] * Qd[0] + Qd[1] * Qd[1] + Qd[2] * Qd[2];
-    const bool small = sqrt(Q2d) * R < tau0;
+    const bool small = active && sqrt(Q2d) * R < tau0;
     const bool big = big_phases64(Q2d, R);
     double xr = 0.0, xi = 0.0;
     for (int64_t t0 = it.f0; t0 < f_end; t0 += kTileF) {
@@ -78,11 +78,14 @@ __global__ __launch_bounds__(kBlock) void batch_fwd_fp64_kernel(const BatchGroup
       for (int i = lane; i < nt * (int)(sizeof(Face64) / 16); i += kBlock)
         reinterpret_cast<uint4*>(tile)[i] = reinterpret_cast<const uint4*>(f64 + t0)[i];
       __syncthreads();
-      if (!small) {
-        for (int j = 0; j < nt; ++j) fwd_face_f64<1>(tile[j], &Qd, big, &xr, &xi);
-      } else {
-        for (int j = 0; j < nt; ++j) tet_term_f64(tile[j], Qd, xr, xi, kZeroOrigin);
-      }
+      for (int j = 0; j < nt; ++j) fwd_face_f64<1>(tile[j], &Qd, big, &xr, &xi);
+    }
+    if (__any(small)) {
+      double x[2] = {xr, xi};
+      fan_sum<2>(small, it.f0, f_end, Qd,
+                 [&](int64_t f, const double* q, double* t) { tet_term_f64(f64[f], q, t[0], t[1], kZeroOrigin); }, x);
+      xr = x[0];
+      xi = x[1];
     }
     if (active) store_stream(partial + it.part + lane, make_double2(xr, xi));
   }
@@ -138,7 +141,7 @@ __global__ __launch_bounds__(kBlock, QPT >= 3 ? kBatchFwdWaves : kBatchFwdWaves 
       ql.set(k, Qd, qx[k], qy[k], qz[k]);
       Q2[k] = qx[k] * qx[k] + qy[k] * qy[k] + qz[k] * qz[k];
       const double Q2d = Qd[0] * Qd[0] + Qd[1] * Qd[1] + Qd[2] * Qd[2];
-      small[k] = sqrt(Q2d) * R < tau0;
+      small[k] = active[k] && sqrt(Q2d) * R < tau0;
       any_small |= small[k];
     }
     float qmax = 0.0f;
@@ -173,13 +176,17 @@ __global__ __launch_bounds__(kBlock, QPT >= 3 ? kBatchFwdWaves : kBatchFwdWaves 
     double xr[QPT], xi[QPT];
 #pragma unroll
     for (int k = 0; k < QPT; ++k) xr[k] = xi[k] = 0.0;
-    if (any_small) {
+    if (__any(any_small)) {
 #pragma unroll
-      for (int k = 0; k < QPT; ++k)
-        if (small[k]) {
-          const double Qd[3] = {ql.qd(qx[k], k, 0), ql.qd(qy[k], k, 1), ql.qd(qz[k], k, 2)};
-          for (int64_t j = it.f0; j < f_end; ++j) tet_term_f64(f64[j], Qd, xr[k], xi[k], kZeroOrigin);
-        }
+      for (int k = 0; k < QPT; ++k) {
+        const double Qd[3] = {ql.qd(qx[k], k, 0), ql.qd(qy[k], k, 1), ql.qd(qz[k], k, 2)};
+        double x[2] = {0.0, 0.0};
+        fan_sum<2>(small[k], it.f0, f_end, Qd,
+                   [&](int64_t f, const double* q, double* t) { tet_term_f64(f64[f], q, t[0], t[1], kZeroOrigin); },
+                   x);
+        xr[k] = x[0];
+        xi[k] = x[1];
+      }
     }
     const int l = (int)__lane_id();  // anew, so no lane index is kept live across the face loop
 #pragma unroll

@@ -34,6 +34,25 @@ __device__ __forceinline__ double2* dq_slot(const DqArgs& a, int comp, int64_t q
   return a.partial + ((int64_t)blockIdx.y * 4 + comp) * a.nq + qi;
 }
 
+// The tetrahedron fan of the `small` lanes over a split, in place of their surface sums. The whole wavefront calls it.
+__device__ __forceinline__ void dq_fan(const DqArgs& a, bool small, int64_t f_begin, int64_t f_end, const double* Q,
+                                       const double* o, double* Ar, double* Ai, double& Br, double& Bi) {
+  double x[8] = {Ar[0], Ai[0], Ar[1], Ai[1], Ar[2], Ai[2], Br, Bi};
+  fan_sum<8>(small, f_begin, f_end, Q,
+             [&](int64_t f, const double* q, double* t) {
+               double Gr[3] = {0.0, 0.0, 0.0}, Gi[3] = {0.0, 0.0, 0.0}, Fr = 0.0, Fi = 0.0;
+               dq_tet_f64(a.f64[f], q, Gr, Gi, Fr, Fi, o);
+               for (int c = 0; c < 3; ++c) t[2 * c] = Gr[c], t[2 * c + 1] = Gi[c];
+               t[6] = Fr;
+               t[7] = Fi;
+             },
+             x);
+  for (int c = 0; c < 3; ++c) Ar[c] = x[2 * c], Ai[c] = x[2 * c + 1];
+  Br = x[6];
+  Bi = x[7];
+  if (small && a.split_geo) dq_apex(Q, o, Ar, Ai, Br, Bi);
+}
+
 // ---------------------------------------------------------------------------
 // binary64: one Q per thread; face records and their Gram matrices in LDS
 // ---------------------------------------------------------------------------
@@ -47,7 +66,7 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp64_kernel(DqArgs a) {
   const double4 geo = a.split_geo ? a.split_geo[blockIdx.y] : make_double4(0.0, 0.0, 0.0, a.info[0].R);
   const double o[3] = {geo.x, geo.y, geo.z};
   const double Q2 = Q[0] * Q[0] + Q[1] * Q[1] + Q[2] * Q[2];
-  const bool small = sqrt(Q2) * geo.w < a.tau, big = big_phases64(Q2, a.info[0].R);
+  const bool small = active && sqrt(Q2) * geo.w < a.tau, big = big_phases64(Q2, a.info[0].R);
   int64_t f_begin, f_end;
   split_range(a, f_begin, f_end);
   double Ar[3] = {0.0, 0.0, 0.0}, Ai[3] = {0.0, 0.0, 0.0}, Br = 0.0, Bi = 0.0;
@@ -62,13 +81,9 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp64_kernel(DqArgs a) {
       for (int i = threadIdx.x; i < nt * 8; i += kBlock) gtile[i / 8][i % 8] = gs[i];
     }
     __syncthreads();
-    if (!small) {
-      for (int j = 0; j < nt; ++j) dq_term_f64(tile[j], gtile[j], Q, big, Ar, Ai, Br, Bi);
-    } else {
-      for (int j = 0; j < nt; ++j) dq_tet_f64(tile[j], Q, Ar, Ai, Br, Bi, o);
-    }
+    for (int j = 0; j < nt; ++j) dq_term_f64(tile[j], gtile[j], Q, big, Ar, Ai, Br, Bi);
   }
-  if (small && a.split_geo) dq_apex(Q, o, Ar, Ai, Br, Bi);
+  if (__any(small)) dq_fan(a, small, f_begin, f_end, Q, o, Ar, Ai, Br, Bi);
   if (active) {
     for (int c = 0; c < 3; ++c) store_stream(dq_slot(a, c, qi), make_double2(Ar[c], Ai[c]));
     store_stream(dq_slot(a, 3, qi), make_double2(Br, Bi));
@@ -78,9 +93,10 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp64_kernel(DqArgs a) {
 // ---------------------------------------------------------------------------
 // FP32C: kQPTDQ Q per thread (strided by the block size), binary32 sums per
 // LDS tile, Kahan across tiles; small-|Q| lanes take the binary64 tetrahedron
-// fan over the split after the tile loop.
+// fan over the split after the tile loop. Three waves per SIMD, as the face loop needs (without the bound the
+// fan's registers leave two: regions of 91 125 Q, dq 1.59 -> 1.73 ms; with it, spills outside the loop).
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kBlock) void dq3d_fp32c_kernel(DqArgs a) {
+__global__ __launch_bounds__(kBlock, 3) void dq3d_fp32c_kernel(DqArgs a) {
   constexpr int P = kQPTDQ;
   __shared__ Face32B tile[kTileF];
   const int64_t qbase = (int64_t)blockIdx.x * (kBlock * P) + threadIdx.x;
@@ -101,7 +117,7 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp32c_kernel(DqArgs a) {
     qy[k] = (float)Qd[k][1];
     qz[k] = (float)Qd[k][2];
     const double Q2 = Qd[k][0] * Qd[k][0] + Qd[k][1] * Qd[k][1] + Qd[k][2] * Qd[k][2];
-    small[k] = sqrt(Q2) * R < a.tau;
+    small[k] = active[k] && sqrt(Q2) * R < a.tau;
     any_small |= small[k];
     wide |= wide_phases32(Q2, a.info[0].R);
   }
@@ -147,19 +163,19 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp32c_kernel(DqArgs a) {
 #pragma unroll
   for (int k = 0; k < P; ++k) {
     const int64_t qi = qbase + (int64_t)k * kBlock;
-    double v[8];
+    double Ar[3], Ai[3], Br, Bi;
 #pragma unroll
-    for (int c = 0; c < 8; ++c) v[c] = (double)sum[k][c] - (double)cmp[k][c];
-    if (any_small && small[k]) {
-      double Gr[3] = {0.0, 0.0, 0.0}, Gi[3] = {0.0, 0.0, 0.0}, Fr = 0.0, Fi = 0.0;
-      for (int64_t f = f_begin; f < f_end; ++f) dq_tet_f64(a.f64[f], Qd[k], Gr, Gi, Fr, Fi, o);
-      if (a.split_geo) dq_apex(Qd[k], o, Gr, Gi, Fr, Fi);
-      for (int c = 0; c < 3; ++c) v[2 * c] = Gr[c], v[2 * c + 1] = Gi[c];
-      v[6] = Fr;
-      v[7] = Fi;
+    for (int c = 0; c < 3; ++c) {
+      Ar[c] = (double)sum[k][2 * c] - (double)cmp[k][2 * c];
+      Ai[c] = (double)sum[k][2 * c + 1] - (double)cmp[k][2 * c + 1];
     }
-    if (active[k])
-      for (int c = 0; c < 4; ++c) store_stream(dq_slot(a, c, qi), make_double2(v[2 * c], v[2 * c + 1]));
+    Br = (double)sum[k][6] - (double)cmp[k][6];
+    Bi = (double)sum[k][7] - (double)cmp[k][7];
+    if (__any(any_small)) dq_fan(a, small[k], f_begin, f_end, Qd[k], o, Ar, Ai, Br, Bi);
+    if (active[k]) {
+      for (int c = 0; c < 3; ++c) store_stream(dq_slot(a, c, qi), make_double2(Ar[c], Ai[c]));
+      store_stream(dq_slot(a, 3, qi), make_double2(Br, Bi));
+    }
   }
 }
 

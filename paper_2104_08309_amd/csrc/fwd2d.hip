@@ -140,7 +140,7 @@ __global__ __launch_bounds__(kBlock) void fwd2d_kernel(const double* verts, cons
     t[1] = info[0].t[1];
     R = info[0].R;
   }
-  const bool small = sqrt(Q2) * R < tau0, wide = big_phases64(Q2, R);
+  const bool small = active && sqrt(Q2) * R < tau0, wide = big_phases64(Q2, R);
   double xr = 0.0, xi = 0.0;
   for (int64_t t0 = 0; t0 < ne; t0 += kTileE) {
     const int nt = (int)min((int64_t)kTileE, ne - t0);

@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kFwdBlock, kFwdWaves64) void fwd3d_fp64_kernel(FwdA
     Q[k][0] = Q[k][1] = Q[k][2] = 0.0;
     if (qi < a.nq) load_q3(a.q, a.qdtype, a.perm ? (int64_t)a.perm[qi] : qi, Q[k]);
     const double Q2 = Q[k][0] * Q[k][0] + Q[k][1] * Q[k][1] + Q[k][2] * Q[k][2];
-    small[k] = sqrt(Q2) * geo.w < a.tau0;
+    small[k] = qi < a.nq && sqrt(Q2) * geo.w < a.tau0;
     any_small |= small[k];
     big |= big_phases64(Q2, a.info[0].R);
     xr[k] = xi[k] = 0.0;
@@ -116,15 +116,17 @@ __global__ __launch_bounds__(kFwdBlock, kFwdWaves64) void fwd3d_fp64_kernel(FwdA
     wave_lds_fence();
     for (int j = 0; j < nt; ++j) fwd_face_f64<QPT>(tile[j], Q, big, xr, xi);
   }
-  if (any_small) {  // small-|Q| lanes: the tetrahedron fan about the apex instead
+  if (__any(any_small)) {  // small-|Q| lanes: the tetrahedron fan about the apex instead
     const double o[3] = {geo.x, geo.y, geo.z};
+    const auto term = [&](int64_t f, const double* q, double* t) { tet_term_f64(a.f64[f], q, t[0], t[1], o); };
 #pragma unroll
-    for (int k = 0; k < QPT; ++k)
-      if (small[k]) {
-        xr[k] = xi[k] = 0.0;
-        for (int64_t j = f_begin; j < f_end; ++j) tet_term_f64(a.f64[j], Q[k], xr[k], xi[k], o);
-        if (a.split_geo) apex_phase(Q[k], o, xr[k], xi[k]);
-      }
+    for (int k = 0; k < QPT; ++k) {
+      double x[2] = {xr[k], xi[k]};
+      fan_sum<2>(small[k], f_begin, f_end, Q[k], term, x);
+      if (small[k] && a.split_geo) apex_phase(Q[k], o, x[0], x[1]);
+      xr[k] = x[0];
+      xi[k] = x[1];
+    }
   }
   // this wavefront's partials into its own tile (it reads no more records)
   wave_lds_fence();
@@ -202,7 +204,7 @@ __global__ __launch_bounds__(kFwdBlock, fwd_waves(QPT)) void fwd3d_fp32c_kernel(
     ql.set(k, Qd, qx[k], qy[k], qz[k]);
     Q2[k] = qx[k] * qx[k] + qy[k] * qy[k] + qz[k] * qz[k];
     const double Q2d = Qd[0] * Qd[0] + Qd[1] * Qd[1] + Qd[2] * Qd[2];
-    small[k] = sqrt(Q2d) * R < a.tau0;
+    small[k] = qi < a.nq && sqrt(Q2d) * R < a.tau0;
     any_small |= small[k];
   }
   float qmax = 0.0f;
@@ -243,14 +245,17 @@ __global__ __launch_bounds__(kFwdBlock, fwd_waves(QPT)) void fwd3d_fp32c_kernel(
   double xr[QPT], xi[QPT];
 #pragma unroll
   for (int k = 0; k < QPT; ++k) xr[k] = xi[k] = 0.0;
-  if (any_small) {
+  if (__any(any_small)) {
+    const auto term = [&](int64_t f, const double* q, double* t) { tet_term_f64(a.f64[f], q, t[0], t[1], o); };
 #pragma unroll
-    for (int k = 0; k < QPT; ++k)
-      if (small[k]) {
-        const double Qd[3] = {ql.qd(qx[k], k, 0), ql.qd(qy[k], k, 1), ql.qd(qz[k], k, 2)};
-        for (int64_t j = f_begin; j < f_end; ++j) tet_term_f64(a.f64[j], Qd, xr[k], xi[k], o);
-        if (a.split_geo) apex_phase(Qd, o, xr[k], xi[k]);
-      }
+    for (int k = 0; k < QPT; ++k) {
+      const double Qd[3] = {ql.qd(qx[k], k, 0), ql.qd(qy[k], k, 1), ql.qd(qz[k], k, 2)};
+      double x[2] = {0.0, 0.0};
+      fan_sum<2>(small[k], f_begin, f_end, Qd, term, x);
+      if (small[k] && a.split_geo) apex_phase(Qd, o, x[0], x[1]);
+      xr[k] = x[0];
+      xi[k] = x[1];
+    }
   }
   // this wavefront's partials into its own tile (it reads no more records)
   wave_lds_fence();
@@ -301,12 +306,6 @@ __device__ __forceinline__ void write_transform(const FwdArgs& a, int out_c128, 
   }
 }
 
-// x + t as its own operation, so that a sum of terms does not depend on where they were computed.
-__device__ __forceinline__ void add_term(double& x, double t) {
-#pragma clang fp contract(off)
-  x = x + t;
-}
-
 // The FP32C forward of a mesh of few faces (at most one LDS tile): each thread holds one Q in the list order, walks all
 // faces and writes F itself. No face splits, so no partial sums and no finish launch, and no Q order: at a dozen faces
 // the split form's wavefronts loaded, reduced and finished each Q for three faces each (12 faces x 2^21 Q of |Q| about
@@ -337,37 +336,11 @@ __global__ __launch_bounds__(kBlock, 8) void fwd3d_few_fp32c_kernel(FwdArgs a) {
     fwd_tile_fp32c<1, false, true>(tile, nt, qx, qy, qz, ql, tr, ti, carry);
   else
     fwd_tile_fp32c<1, false, false>(tile, nt, qx, qy, qz, ql, tr, ti, carry);
-  double xr = (double)tr[0], xi = (double)ti[0];
-  // The small-|Q| fan, its terms added in face order either way: a few such Q share the wavefront, a face per lane
-  // (one after the other by their own lanes, the few in 2 000 random Q took 23 us at 12 faces); many take theirs side
-  // by side.
-  uint64_t todo = __ballot(small);
-  if (2 * __popcll(todo) <= nt) {
-    const int lane = threadIdx.x & 63;
-    for (; todo; todo &= todo - 1) {
-      const int src = __ffsll((unsigned long long)todo) - 1;
-      const double Qs[3] = {__shfl(Q[0], src), __shfl(Q[1], src), __shfl(Q[2], src)};
-      double tx = 0.0, ty = 0.0, sx = 0.0, sy = 0.0;
-      if (lane < nt) tet_term_f64(a.f64[lane], Qs, tx, ty, kZeroOrigin);
-      for (int j = 0; j < nt; ++j) {
-        add_term(sx, __shfl(tx, j));
-        add_term(sy, __shfl(ty, j));
-      }
-      if (lane == src) {
-        xr = sx;
-        xi = sy;
-      }
-    }
-  } else if (small) {
-    xr = xi = 0.0;
-    for (int j = 0; j < nt; ++j) {
-      double tx = 0.0, ty = 0.0;
-      tet_term_f64(a.f64[j], Q, tx, ty, kZeroOrigin);
-      add_term(xr, tx);
-      add_term(xi, ty);
-    }
-  }
-  if (qi < a.nq) write_transform(a, 0, qi, Q, xr, xi);
+  double x[2] = {(double)tr[0], (double)ti[0]};
+  if (__any(small))
+    fan_sum<2>(small, 0, nt, Q,
+               [&](int64_t f, const double* q, double* t) { tet_term_f64(a.f64[f], q, t[0], t[1], kZeroOrigin); }, x);
+  if (qi < a.nq) write_transform(a, 0, qi, Q, x[0], x[1]);
 }
 
 // Sum the splits in order, apply exp(i Q.t) and 1/|Q|^2, write F and |F|^2 at
@@ -422,7 +395,6 @@ hipError_t launch_fwd3d_fp32c(const FwdArgs& a, hipStream_t s) {
 }
 
 hipError_t launch_fwd3d_few_fp32c(const FwdArgs& a, hipStream_t s) {
-  static_assert(kTileF32 <= 64, "a face per lane");
   if (a.nf > kTileF32) return hipErrorInvalidValue;
   const int64_t blocks = (a.nq + kBlock - 1) / kBlock;
   if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;

@@ -175,7 +175,7 @@ __global__ __launch_bounds__(kBlock) void fwdpoly_fp32c_kernel(FwdArgs a, PolyAr
     qz[k] = (float)Qd[k][2];
     Q2[k] = qx[k] * qx[k] + qy[k] * qy[k] + qz[k] * qz[k];
     const double Q2d = Qd[k][0] * Qd[k][0] + Qd[k][1] * Qd[k][1] + Qd[k][2] * Qd[k][2];
-    small[k] = sqrt(Q2d) * R < a.tau0;
+    small[k] = active[k] && sqrt(Q2d) * R < a.tau0;
     any_small |= small[k];
   }
   const int64_t t_begin = (int64_t)blockIdx.y * p.tiles_per_split;

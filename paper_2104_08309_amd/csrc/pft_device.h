@@ -95,6 +95,64 @@ __device__ __forceinline__ void fwd_partial_sum(const FwdArgs& a, int64_t qi, do
   add_partials(a.partial + qi, a.nq, a.splits, xr, xi);
 }
 
+// x + t as its own operation, so that a sum of terms does not depend on where they were computed.
+__device__ __forceinline__ void add_term(double& x, double t) {
+#pragma clang fp contract(off)
+  x = x + t;
+}
+
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  const uint64_t b = (uint64_t)__double_as_longlong(v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), lane);
+  return __longlong_as_double((long long)((uint64_t)hi << 32 | lo));
+}
+
+// x[0 .. N) = the sum over faces [f0, f1) of term(face, Q, t) for the lanes that are `small` (the small-|Q| fans); the
+// others' x stays. Every lane of the wavefront calls it. The terms are added in face order either way, so a lane's sum
+// does not depend on its wavefront: up to kFanShared such lanes are served one after the other, a face per lane (a
+// lone one held its wavefront for 150 us over 512 faces, its fan's chain of divisions at one lane in 64); more of them
+// each walk the faces side by side.
+constexpr int kFanShared = 8;
+template <int N, class Term>
+__device__ __forceinline__ void fan_sum(bool small, int64_t f0, int64_t f1, const double* Q, const Term& term,
+                                        double* x) {
+  uint64_t todo = __ballot(small);
+  const int lane = (int)__lane_id(), count = __popcll(todo);
+  if (count <= kFanShared && 2 * count <= f1 - f0) {
+    for (; todo; todo &= todo - 1) {
+      const int src = __ffsll((unsigned long long)todo) - 1;
+      const double Qs[3] = {read_lane(Q[0], src), read_lane(Q[1], src), read_lane(Q[2], src)};
+      double sum[N];
+#pragma unroll
+      for (int n = 0; n < N; ++n) sum[n] = 0.0;
+      for (int64_t f = f0; f < f1; f += 64) {
+        double t[N];
+#pragma unroll
+        for (int n = 0; n < N; ++n) t[n] = 0.0;
+        if (f + lane < f1) term(f + lane, Qs, t);
+        const int m = (int)min((int64_t)64, f1 - f);
+        for (int j = 0; j < m; ++j)
+#pragma unroll
+          for (int n = 0; n < N; ++n) add_term(sum[n], read_lane(t[n], j));
+      }
+#pragma unroll
+      for (int n = 0; n < N; ++n) x[n] = lane == src ? sum[n] : x[n];
+    }
+  } else if (small) {
+#pragma unroll
+    for (int n = 0; n < N; ++n) x[n] = 0.0;
+    for (int64_t f = f0; f < f1; ++f) {
+      double t[N];
+#pragma unroll
+      for (int n = 0; n < N; ++n) t[n] = 0.0;
+      term(f, Q, t);
+#pragma unroll
+      for (int n = 0; n < N; ++n) add_term(x[n], t[n]);
+    }
+  }
+}
+
 // sin(2 pi x), cos(2 pi x) for x in turns (hardware transcendental unit; valid for |x| <= 256).
 __device__ __forceinline__ float sin_turns(float x) { return __builtin_amdgcn_sinf(x); }
 __device__ __forceinline__ float cos_turns(float x) { return __builtin_amdgcn_cosf(x); }
