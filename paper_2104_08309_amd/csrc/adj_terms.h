@@ -3,6 +3,8 @@
 // kernels. The formulas are stated at the top of bwd3d.hip.
 #pragma once
 
+#include <type_traits>
+
 #include "face_moments.h"
 #include "pft_device.h"
 
@@ -117,7 +119,11 @@ __device__ __forceinline__ void far_moments_f64(Fit64 t, const Face64& f, const 
 // the series in n (5 120 faces x 64 000 Q: kernel 3.41 -> 2.41 ms under the profiler, and fitting step 3.22 -> 3.08 ms
 // with the differences in place of the corners); with P = 2 a coefficient is
 // read once for two pairs (3 and 4 points: 9 % and 0.5 % slower fitting step, fewer wavefronts in flight).
-template <int P>
+// SHORT (uniform): every phase of the wavefront's Q is within FaceFit64S, two thirds of the coefficients and no range
+// test (20 480 faces x 16 384 Q with phases to 0.7, transform and adjoint: 3.17 -> 2.92 ms). The forward has no such
+// choice: a Q's value there must not depend on its wavefront, and forming both where a wavefront's Q lie on both sides
+// cost more than it saved (5 120 faces x 64 000 Q, phases to 2.1: 3.15 -> 3.23 ms).
+template <int P, bool SHORT>
 __device__ __forceinline__ void adj_face_f64(const Face64& f, const double* G, const double (*Q)[3], const double* gr,
                                              const double* gi, bool big, double* S) {
   const Fit64 t = fit64();
@@ -141,9 +147,10 @@ __device__ __forceinline__ void adj_face_f64(const Face64& f, const double* G, c
   for (int k = 0; k < P; ++k) {
     const double s = d0[k] + d1[k];
     const double p = d0[k] * s + d1[k] * d1[k], E = d0[k] * d1[k] * s, w = E * E;
-    any |= fmax(fabs(d0[k]), fmax(fabs(d1[k]), fabs(s))) > FaceFit64::M;
-    face_ab64(t, p, w, A[k], B[k]);
-    face_beta_gamma64(t, p, w, bi[k], br[k], cr[k], ci[k]);
+    if (!SHORT) any |= fmax(fabs(d0[k]), fmax(fabs(d1[k]), fabs(s))) > FaceFit64::M;
+    using F = std::conditional_t<SHORT, FaceFit64S, FaceFit64>;
+    face_ab64<F>(t, p, w, A[k], B[k]);
+    face_beta_gamma64<F>(t, p, w, bi[k], br[k], cr[k], ci[k]);
     const double er = zr[k] * E, ei = zi[k] * E;
     const double a = zr[k] * A[k] - ei * B[k];           // Re(z J)
     const double b = er * br[k] - zi[k] * bi[k];         // Re(z beta)
@@ -152,7 +159,7 @@ __device__ __forceinline__ void adj_face_f64(const Face64& f, const double* G, c
     B[k] = (d0[k] + s) * (b - c * d1[k]);
     bi[k] = (d1[k] + s) * (b - c * d0[k]);
   }
-  if (any) {
+  if (!SHORT && any) {
 #pragma unroll
     for (int k = 0; k < P; ++k)
       if (fmax(fabs(d0[k]), fmax(fabs(d1[k]), fabs(d0[k] + d1[k]))) > FaceFit64::M) {
@@ -355,12 +362,13 @@ __device__ __forceinline__ double block_total(double v, double* lds) {
 // ---------------------------------------------------------------------------
 template <int P>
 __device__ __forceinline__ void adj_tile_f64(const Face64* tile, const double (*gtile)[8], int nt, int64_t qb,
-                                             int64_t qe, const QRec64* __restrict__ rec, double R, double (*acc)[kBlock]) {
+                                             int64_t qe, const QRec64* __restrict__ rec, const MeshInfo& info,
+                                             double (*acc)[kBlock]) {
   const int tid = threadIdx.x;
   for (int64_t q0 = qb; q0 < qe; q0 += (int64_t)kBlock * P) {
     double Qd[P][3];
     double hr[P], hi[P];
-    bool big = false;
+    bool big = false, brief = true;
 #pragma unroll
     for (int p = 0; p < P; ++p) {
       const int64_t qi = q0 + (int64_t)p * kBlock + tid;
@@ -374,12 +382,18 @@ __device__ __forceinline__ void adj_tile_f64(const Face64* tile, const double (*
         hr[p] = r.hr;
         hi[p] = r.hi;
       }
-      big |= big_phases64(Qd[p][0] * Qd[p][0] + Qd[p][1] * Qd[p][1] + Qd[p][2] * Qd[p][2], R);
+      const double q2 = Qd[p][0] * Qd[p][0] + Qd[p][1] * Qd[p][1] + Qd[p][2] * Qd[p][2];
+      big |= big_phases64(q2, info.R);
+      brief &= short_phases64(q2, info.rho);
     }
+    brief = __all(brief) != 0;
 #pragma unroll 1
     for (int j = 0; j < nt; ++j) {
       double S[3] = {0.0, 0.0, 0.0};
-      adj_face_f64<P>(tile[j], gtile[j], Qd, hr, hi, big, S);
+      if (brief)
+        adj_face_f64<P, true>(tile[j], gtile[j], Qd, hr, hi, big, S);
+      else
+        adj_face_f64<P, false>(tile[j], gtile[j], Qd, hr, hi, big, S);
 #pragma unroll
       for (int k = 0; k < 3; ++k) acc[3 * j + k][tid] += S[k];
     }

@@ -266,7 +266,7 @@ __global__ __launch_bounds__(kBlock) void batch_bwd_fp64_kernel(const BatchItemB
     for (int i = tid; i < nt * 8; i += kBlock) gtile[i / 8][i % 8] = gram[(it.f0 + i / 8) * 8 + i % 8];
     for (int v = 0; v < nt * 3; ++v) acc[v][tid] = 0.0;
     __syncthreads();
-    adj_tile_f64<kQPTB64>(tile, gtile, nt, it.q0, it.q0 + it.nq, rec, info[it.mesh].R, acc);
+    adj_tile_f64<kQPTB64>(tile, gtile, nt, it.q0, it.q0 + it.nq, rec, info[it.mesh], acc);
     __syncthreads();
     adj_block_sum(acc, nt, partial + it.part * 3);
     __syncthreads();

@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kBlock) void bwd3d_fp64_kernel(BwdArgs a, const dou
   for (int v = 0; v < nt * 3; ++v) acc[v][tid] = 0.0;
   __syncthreads();
   adj_range<P>(a, qs, qb, qe);
-  adj_tile_f64<P>(tile, gtile, nt, qb, qe, a.rec64, a.info[0].R, acc);
+  adj_tile_f64<P>(tile, gtile, nt, qb, qe, a.rec64, a.info[0], acc);
   __syncthreads();
   adj_block_sum(acc, nt, a.partial + (qs * a.nf + f0) * 3);
 }

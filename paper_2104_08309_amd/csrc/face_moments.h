@@ -66,27 +66,54 @@ __device__ __forceinline__ void sincos_any64(Fit64 t, double x, double* s, doubl
     sincos64(t, x, s, c);
 }
 
-// A and B of J = A + i E B, and J itself, binary64, max |d_k| <= FaceFit64::M.
-__device__ __forceinline__ void face_ab64(Fit64 t, double p, double w, double& A, double& B) {
-  A = ((horner64<FaceFit64::A3>(t, p) * w + horner64<FaceFit64::A2>(t, p)) * w + horner64<FaceFit64::A1>(t, p)) * w +
-      horner64<FaceFit64::A0>(t, p);
-  B = (horner64<FaceFit64::B2>(t, p) * w + horner64<FaceFit64::B1>(t, p)) * w + horner64<FaceFit64::B0>(t, p);
+// C0 + C1 w (+ C2 w^2 + C3 w^3), each a polynomial in p, binary64.
+template <class C0, class... C>
+__device__ __forceinline__ double poly64(Fit64 t, double p, double w) {
+  if constexpr (sizeof...(C) == 0)
+    return horner64<C0>(t, p);
+  else
+    return poly64<C...>(t, p, w) * w + horner64<C0>(t, p);
 }
+
+// A and B of J = A + i E B, and J itself, binary64, max |d_k| <= F::M: FaceFit64, or FaceFit64S of two thirds of its
+// coefficients for half its range.
+template <class F>
+__device__ __forceinline__ void face_ab64(Fit64 t, double p, double w, double& A, double& B) {
+  if constexpr (F::M < FaceFit64::M) {
+    A = poly64<typename F::A0, typename F::A1, typename F::A2>(t, p, w);
+  } else {
+    A = poly64<typename F::A0, typename F::A1, typename F::A2, typename F::A3>(t, p, w);
+  }
+  B = poly64<typename F::B0, typename F::B1, typename F::B2>(t, p, w);
+}
+template <class F>
 __device__ __forceinline__ void face_integral_fit64(Fit64 t, double d0, double d1, double& jr, double& ji) {
   const double s = d0 + d1;
   const double E = d0 * d1 * s;
   double B;
-  face_ab64(t, d0 * s + d1 * d1, E * E, jr, B);
+  face_ab64<F>(t, d0 * s + d1 * d1, E * E, jr, B);
   ji = E * B;
 }
 
+// Whether every phase |d_k| <= |Q| rho (as in fit_range_test_needed) of a Q is within FaceFit64S.
+__device__ __forceinline__ bool short_phases64(double q2, double rho) {
+  return sqrt(q2) * rho <= 0.999 * FaceFit64S::M;
+}
+
 // beta and gamma's parts: beta = i bi + E br, gamma = gr + i E gi.
+template <class F>
 __device__ __forceinline__ void face_beta_gamma64(Fit64 t, double p, double w, double& bi, double& br, double& gr, double& gi) {
-  bi = ((horner64<FaceFit64::bi3>(t, p) * w + horner64<FaceFit64::bi2>(t, p)) * w + horner64<FaceFit64::bi1>(t, p)) * w +
-       horner64<FaceFit64::bi0>(t, p);
-  br = (horner64<FaceFit64::br2>(t, p) * w + horner64<FaceFit64::br1>(t, p)) * w + horner64<FaceFit64::br0>(t, p);
-  gr = (horner64<FaceFit64::gr2>(t, p) * w + horner64<FaceFit64::gr1>(t, p)) * w + horner64<FaceFit64::gr0>(t, p);
-  gi = (horner64<FaceFit64::gi2>(t, p) * w + horner64<FaceFit64::gi1>(t, p)) * w + horner64<FaceFit64::gi0>(t, p);
+  if constexpr (F::M < FaceFit64::M) {
+    bi = poly64<typename F::bi0, typename F::bi1, typename F::bi2>(t, p, w);
+    br = poly64<typename F::br0, typename F::br1>(t, p, w);
+    gr = poly64<typename F::gr0, typename F::gr1, typename F::gr2>(t, p, w);
+    gi = poly64<typename F::gi0, typename F::gi1>(t, p, w);
+  } else {
+    bi = poly64<typename F::bi0, typename F::bi1, typename F::bi2, typename F::bi3>(t, p, w);
+    br = poly64<typename F::br0, typename F::br1, typename F::br2>(t, p, w);
+    gr = poly64<typename F::gr0, typename F::gr1, typename F::gr2>(t, p, w);
+    gi = poly64<typename F::gi0, typename F::gi1, typename F::gi2>(t, p, w);
+  }
 }
 
 // J and the complex moments Y_0, Y_1 (Y_2 = J - Y_0 - Y_1), binary64, max |d_k| <= FaceFit64::M.
@@ -95,9 +122,9 @@ __device__ __forceinline__ void bary_moments_fit64(Fit64 t, double d0, double d1
   const double s = d0 + d1;
   const double p = d0 * s + d1 * d1, E = d0 * d1 * s, w = E * E;
   double B, bi, br, gr, gi;
-  face_ab64(t, p, w, jr, B);
+  face_ab64<FaceFit64>(t, p, w, jr, B);
   ji = E * B;
-  face_beta_gamma64(t, p, w, bi, br, gr, gi);
+  face_beta_gamma64<FaceFit64>(t, p, w, bi, br, gr, gi);
   br *= E;
   gi *= E;
   const double ar = (jr - 2.0 * p * gr) * (1.0 / 3.0), ai = (ji - 2.0 * p * gi) * (1.0 / 3.0);

@@ -53,7 +53,7 @@ __device__ __forceinline__ void fwd_face_f64(const Face64& f, const double (*Q)[
   for (int k = 0; k < NQ; ++k) {
     d0[k] = Q[k][0] * f.u0[0] + Q[k][1] * f.u0[1] + Q[k][2] * f.u0[2];
     d1[k] = Q[k][0] * f.u1[0] + Q[k][1] * f.u1[1] + Q[k][2] * f.u1[2];
-    face_integral_fit64(t, d0[k], d1[k], jr[k], ji[k]);
+    face_integral_fit64<FaceFit64>(t, d0[k], d1[k], jr[k], ji[k]);
     far[k] = fmax(fabs(d0[k]), fmax(fabs(d1[k]), fabs(d0[k] + d1[k]))) > FaceFit64::M;
     any |= far[k];
   }

@@ -19,9 +19,8 @@ needed), the largest error (times |E| for B, br, gi) minimised by Lawson's rewei
 80-bit arithmetic. Symmetric functions in two variables need about half the operations of the
 one-variable recurrences in n.
 
-Three sets: binary32 J in the scaled phases d / (4 pi) (half-phases in turns), binary32 moments and binary64 in
-radians. The binary64
-sine and cosine on [-pi/4, pi/4] (their arguments are reduced by multiples of pi/2) are fitted the same way:
+Four sets: binary32 J in the scaled phases d / (4 pi) (half-phases in turns), binary32 moments, binary64 and binary64
+for short phases in radians. The binary64 sine and cosine on [-pi/4, pi/4] (their arguments are reduced by multiples of pi/2) are fitted the same way:
 sin x = x + x^3 S(x^2), cos x = 1 - x^2 / 2 + x^4 C(x^2).
 Run from this directory (on a machine with an 80-bit long double): python gen_face_poly.py > face_poly.h
 """
@@ -34,10 +33,11 @@ LD = np.longdouble
 NMAX = 44
 
 # (terms in p for w^0, w^1, ...) of each function, and the phase range
-M32, M64 = 3.6, 3.0
+M32, M64, M64S = 3.6, 3.0, 1.5
 SHAPE32 = {"A": (6, 3), "B": (5, 2)}                     # the forward's J, phases to M32
 SHAPE32M = {"A": (6, 3), "B": (5, 2), "bi": (5, 2), "br": (4, 1), "gr": (5, 2), "gi": (3,)}  # moments, to M64
 SHAPE64 = {"A": (11, 8, 4, 1), "B": (9, 6, 3), "bi": (9, 7, 3, 1), "br": (8, 5, 2), "gr": (9, 6, 3), "gi": (8, 4, 1)}
+SHAPE64S = {"A": (8, 5, 2), "B": (7, 4, 1), "bi": (7, 4, 1), "br": (6, 3), "gr": (7, 4, 1), "gi": (6, 3)}  # to M64S
 ODD = ("B", "br", "gi")  # multiplied by E
 ROW64 = []  # every binary64 coefficient, in the order of the "at" offsets
 
@@ -235,7 +235,8 @@ def main():
             ("FaceFit32", M32, SHAPE32, LD(4) * LD("3.14159265358979323846264338"), "float",
              "binary32; the variables are phases / (4 pi): p, E, w of d / (4 pi)"),
             ("FaceFit32M", M64, SHAPE32M, 1, "float", "binary32 moments; phases in radians"),
-            ("FaceFit64", M64, SHAPE64, 1, "double", "binary64; phases in radians")):
+            ("FaceFit64", M64, SHAPE64, 1, "double", "binary64; phases in radians"),
+            ("FaceFit64S", M64S, SHAPE64S, 1, "double", "binary64, short phases in radians")):
         print(f"// {what}; M in radians.")
         print(f"struct {st} {{")
         print(f"  static constexpr double M = {M!r};")

@@ -44,7 +44,7 @@ def _series(d, nmax=60):
 
 
 @pytest.mark.parametrize("name,tol_j,tol_y", [("FaceFit32", 4e-8, None), ("FaceFit32M", 4e-8, 4e-8),
-                                              ("FaceFit64", 4e-16, 4e-16)])
+                                              ("FaceFit64", 4e-16, 4e-16), ("FaceFit64S", 4e-16, 4e-16)])
 def test_face_fit(name, tol_j, tol_y):
     """Tolerances: the fits' own errors (at most 2.5e-8 for J and 2.2e-8 for a moment's parts in binary32, rounded
     coefficients beside them; below 1e-16 in binary64, where a few roundings of values near 1/2 remain)."""
