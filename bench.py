@@ -29,17 +29,17 @@ sys.path.insert(0, ROOT)
 # Operation counts per (triangle, Q) pair (multiply or add = 1, FMA = 2; sin, cos, reciprocal = 1 each):
 #   forward  = 104 flop (algorithmic): one face term of the edge sum with all three edges evaluated
 #              (cross and dot products with Q, three edge sincs, two half-vertex phases, the
-#              face-origin phase, the complex products and the accumulation); the kernel's edge sharing
-#              and polynomial sinc do less work for the same result, which this count credits;
+#              face-origin phase, the complex products and the accumulation); the kernel's fitted
+#              face integral does less work for the same result, which this count credits;
 #   adjoint  = 165.8 flop: on this workload every pair takes the adjoint's small-phase branch (largest
 #              centred vertex phase 2.07 < 3), where a face's barycentric moments are sums of complete
 #              homogeneous symmetric polynomials of its vertex phases; the basis is the hardware count
 #              (SQ_INSTS_VALU_FLOPS_FP32, _TRANS and _FP64 on the 5120-face sphere x 64^3 grid) of the adjoint
 #              with those sums taken as their Taylor series to binary32 accuracy (stopped once m^n/n! < 1e-6).
-#              The kernel evaluates the same moments, at the same error, from fitted polynomials of exp(ix)
-#              of lower degree and executes fewer operations (its own count is reported beside the fraction
-#              as counted_flop_per_face_q), which this basis credits as the forward's 104 credits its edge
-#              sharing; the differentiated edge-sum branch, not run here, would count 200;
+#              The kernel evaluates the same moments from fitted symmetric polynomials and executes fewer
+#              operations (its own count is reported beside the fraction as counted_flop_per_face_q), which
+#              this basis credits as the forward's 104 credits its fitted face integral; the differentiated
+#              edge-sum branch, not run here, would count 200;
 #   grad_Q   = 246 flop: the adjoint's recomputed terms (66), edge derivatives (15)
 #              and edge products (25), two barycentric moments with their
 #              normalisation and the face integral (59), Q.N and its phase (7),
@@ -639,7 +639,7 @@ def main():
         "scaling": "weak",
         "vs_baseline": None,
         "dtype": "f32",
-        "dtype_note": "FP32-compensated: edge arithmetic in binary32, face phases, series branches and the "
+        "dtype_note": "FP32-compensated: face arithmetic in binary32, face phases, small-|Q| series and the "
                       "sums across tiles and splits in binary64",
         "data": "synthetic",
         "config": {"workload": "icosphere L4 (5120 tri, R=50), Q 64^3 grid over [-0.5,0.5)^3, fwd+bwd FP32C",

@@ -66,12 +66,12 @@ typedef enum {
 /* Arithmetic of the transform.
  * PFT_FP64  : every step in IEEE binary64; complex128 outputs.
  * PFT_FP32C : "FP32-compensated": the mesh is re-centred on its vertex mean and
- *             each face on its centroid in binary64; the per-(Q, face) edge
+ *             each face on its centroid in binary64; the per-(Q, face)
  *             arithmetic then runs in binary32 on small local coordinates,
  *             with the face's origin phase Q.g and the mesh phase Q.t taken in
- *             binary64, the near-degenerate branches (Q nearly along a face
- *             normal, |Q| R small) evaluated in binary64, and the sum over
- *             faces accumulated with compensation; complex64 outputs. */
+ *             binary64, the near-degenerate branch (|Q| R small) evaluated in
+ *             binary64, and the sum over faces accumulated with compensation;
+ *             complex64 outputs. */
 typedef enum { PFT_FP64 = 0, PFT_FP32C = 1 } pft_mode;
 
 /* FP32C phase range (radians). The binary32 form takes every phase it
@@ -174,8 +174,10 @@ pft_status pft_q_order(const void* q, pft_dtype qdtype, int64_t nq, uint32_t* or
  * edge-sharing order (pft_strip_order, copied to the device) and/or the Q
  * visited in a given order (pft_q_order). The sum over faces is unchanged
  * (eq. sum_elements_3d; only the rounding order differs); in the
- * FP32-compensated form the term sinc(Q.d/2) exp(iQ.m) of an edge shared with
- * the previous face is reused, so a face costs two edge terms instead of three.
+ * FP32-compensated form the midpoint phase of the edge shared with the previous
+ * face gives the face its origin phase, which then needs no binary64 product.
+ * A mesh of few faces (16; 32 from 2^18 Q) given without a face order is taken
+ * in the list order of its Q, whatever q_order says.
  *
  *  Arguments as pft_forward_3d, plus
  *  face_order  NULL (the list order) or [nf] int32 (DEVICE), a permutation
@@ -221,8 +223,9 @@ pft_status pft_forward_3d_noalloc(const void* verts, pft_dtype vdtype, int64_t n
 
 /*
  * pft_forward_3d_poly -- F(Q) of the volume enclosed by planar polygon faces
- * (3D section: eq. sum_elements_3d with nu_m edges per face, evaluated natively:
- * nu edge terms per face).
+ * (3D section: eq. sum_elements_3d with nu_m edges per face): faces of few edges,
+ * and all of them in binary64, through the integrals of their fan triangles, the
+ * others by nu edge terms.
  *
  *  verts        [nv][3] of vdtype (DEVICE).
  *  face_offsets HOST int64 [nf + 1], non-decreasing from 0; face i is
@@ -414,7 +417,7 @@ pft_status pft_batch_forward(const pft_mesh_batch* batch, pft_mode mode, void* o
 /*
  * pft_batch_forward_ordered -- pft_batch_forward with each mesh's faces in an
  * edge-sharing order (pft_strip_order of the mesh, offset by its first
- * triangle), so that the FP32C forward reuses shared edge terms as
+ * triangle), so that the FP32C forward carries the shared edges' phases as
  * pft_forward_3d_ordered does.
  *  face_order  [total_nf] int32 (DEVICE): position m (in mesh i's triangle
  *              range) holds a triangle of the same mesh; an entry out of

@@ -90,12 +90,14 @@ constexpr int kTileFB32 = PFT_TILEFB32;  // faces per block in the FP32C adjoint
 constexpr int kQPTDQ = PFT_QPT_DQ;  // Q per thread in the FP32C grad_Q kernel
 constexpr int kTileE = 256;        // 2D edges staged in LDS per tile
 
-// Series thresholds (dimensionless). A (Q, face) pair uses the face's simplex
-// series instead of the edge sum when |Q_perp| L_face < tau (absolute test) or
-// |Q_perp| < tau_rel |Q| (relative test, guards the rounding of Q x N in FP32).
-constexpr double kTauF64 = 0.05;     // forward and adjoint, FP64 mode
-constexpr double kTauF32 = 0.1;      // forward, FP32C mode (series in FP64)
-constexpr double kTauRel32 = 0.02;   // polygon forward, FP32C mode, relative test
+// Series thresholds (dimensionless) of the polygon kernel: a (Q, face) pair uses
+// the fan triangles' series instead of the edge sum when |Q_perp| L_face < tau
+// (absolute test) or |Q_perp| < tau_rel |Q| (relative test, guards the rounding
+// of Q x N in FP32). The triangle kernels have no such branch; their records keep
+// the threshold only as the mark of an empty face (negative).
+constexpr double kTauF64 = 0.05;
+constexpr double kTauF32 = 0.1;
+constexpr double kTauRel32 = 0.02;
 // The adjoint evaluates each face's barycentric moments by the fitted symmetric polynomials (face_poly.h) when the
 // largest centred vertex phase |Q.(v_k - g)| is at most this, by the differentiated edge sums otherwise (there
 // |Q_perp| L > 4.5).
