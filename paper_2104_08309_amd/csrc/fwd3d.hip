@@ -309,7 +309,7 @@ __device__ __forceinline__ void write_transform(const FwdArgs& a, int out_c128, 
 // The FP32C forward of a mesh of few faces (at most one LDS tile): each thread holds one Q in the list order, walks all
 // faces and writes F itself. No face splits, so no partial sums and no finish launch, and no Q order: at a dozen faces
 // the split form's wavefronts loaded, reduced and finished each Q for three faces each (12 faces x 2^21 Q of |Q| about
-// 9: 187 -> 88 us a call; x 128^3 grid: 127 -> 72; two Q a thread instead of one: 91). Bound by issue: of the faces'
+// 9: 187 -> 88 us a call; x 128^3 grid: 127 -> 69; two Q a thread instead of one: 91). Bound by issue: of the faces'
 // polynomials and phases for small faces, of the edge terms' transcendentals for large ones.
 __global__ __launch_bounds__(kBlock, 8) void fwd3d_few_fp32c_kernel(FwdArgs a) {
   __shared__ Face32 tile[kTileF32];

@@ -232,26 +232,37 @@ __device__ __forceinline__ void face_edge_term_fp32c(float r, float p0, float p1
                                                      float& Tr, float& Ti) {
   constexpr float kInv16Pi2 = 0.0063325739776461107152f;
   const float p[3] = {p0, p1, -s};
-  float c[3], cs[3], sn[3];
+  float c[3], cs[3], sn[3], t[3], x[3];
   bool wide = false;
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    const float t = r - p[k], x = p[(k + 1) % 3] - p[(k + 2) % 3];
-    cs[k] = cos_turns(t);
-    sn[k] = sin_turns(t);
-    c[k] = sinc2pi_poly(x);
-    wide |= fabsf(x) > kSincPolyMax;
+    t[k] = r - p[k];
+    x[k] = p[(k + 1) % 3] - p[(k + 2) % 3];
+    c[k] = sinc2pi_poly(x[k]);
+    wide |= fabsf(x[k]) > kSincPolyMax;
   }
+  // the transcendentals in one run, as in the fitted form (12 faces x 128^3 Q: 72.6 -> 69.4 us)
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    cs[k] = cos_turns(t[k]);
+    sn[k] = sin_turns(t[k]);
+  }
+  const float rP = rcp_f(P);
+  __builtin_amdgcn_sched_barrier(0);
   if (wide) {
+    float rx[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) rx[k] = rcp_f(x[k]);
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
       const int i = (k + 1) % 3, j = (k + 2) % 3;
-      const float x = p[i] - p[j];
-      c[k] = fabsf(x) > kSincPolyMax ? (sn[j] * cs[i] - sn[i] * cs[j]) * rcp_f(x) : c[k];
+      c[k] = fabsf(x[k]) > kSincPolyMax ? (sn[j] * cs[i] - sn[i] * cs[j]) * rx[k] : c[k];
     }
   }
   const float a0 = p[0] * c[0], a1 = p[1] * c[1], a2 = p[2] * c[2];
-  const float co = kInv16Pi2 * rcp_f(P);
+  const float co = kInv16Pi2 * rP;
   Tr = co * (a0 * cs[0] + a1 * cs[1] + a2 * cs[2]);
   Ti = co * (a0 * sn[0] + a1 * sn[1] + a2 * sn[2]);
 }
