@@ -96,13 +96,14 @@ __device__ __forceinline__ void edge_moments_f64(Fit64 t, const Face64& f, const
   }
 }
 
-// The edge form's moments of one pair: X_k / |P|^2 for k = 0, 1 and the face integral J = i S / |P|^2.
+// The edge form's moments of one pair: X_k / |P|^2 for k = 0, 1 and the face integral J = i S / |P|^2. A record of a
+// zero-area face (thr < 0) keeps its vertices, so its phases can lead here with P = 0: its moments are 0.
 __device__ __forceinline__ void far_moments_f64(Fit64 t, const Face64& f, const double* G, const double* Q, double d0,
                                                 double d1, double* yr, double* yi, double& jr, double& ji) {
   const double Px = Q[1] * f.N[2] - Q[2] * f.N[1];
   const double Py = Q[2] * f.N[0] - Q[0] * f.N[2];
   const double Pz = Q[0] * f.N[1] - Q[1] * f.N[0];
-  const double inv = 1.0 / (Px * Px + Py * Py + Pz * Pz);
+  const double inv = f.thr < 0.0 ? 0.0 : 1.0 / (Px * Px + Py * Py + Pz * Pz);
   double Xr[3], Xi[3], Sr, Si;
   edge_moments_f64(t, f, G, Px, Py, Pz, d0, d1, inv, Xr, Xi, Sr, Si);
   for (int k = 0; k < 2; ++k) yr[k] = Xr[k] * inv, yi[k] = Xi[k] * inv;
@@ -114,8 +115,8 @@ __device__ __forceinline__ void far_moments_f64(Fit64 t, const Face64& f, const 
 // and Re(z J) to S (adj_block_sum turns their sums into the corners' Re(z Y_k)). With Y_k = alpha + beta d_k + gamma
 // d_k^2, Y_0 - Y_2 = (d_0 - d_2)(beta - gamma d_1) and Y_1 - Y_2 = (d_1 - d_2)(beta - gamma d_0): three real
 // combinations of the six fitted functions serve all corners and alpha drops out. The edge
-// form beyond the fitted range; the choice is per lane. An empty record (N = 0, phases 0) gives finite weights that
-// the vertex gather multiplies by N = 0. Bound by binary64 issue, about 160 instructions per pair against some 300 of
+// form beyond the fitted range; the choice is per lane. A zero-area face (N = 0; its phases need not be 0) gives finite
+// weights that the vertex gather multiplies by N = 0. Bound by binary64 issue, about 160 instructions per pair against some 300 of
 // the series in n (5 120 faces x 64 000 Q: kernel 3.41 -> 2.41 ms under the profiler, and fitting step 3.22 -> 3.08 ms
 // with the differences in place of the corners); with P = 2 a coefficient is
 // read once for two pairs (3 and 4 points: 9 % and 0.5 % slower fitting step, fewer wavefronts in flight).

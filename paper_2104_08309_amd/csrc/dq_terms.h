@@ -110,8 +110,8 @@ PFT_HD __forceinline__ void dq_apex(const double* Q, const double* o, double* Gr
   Fr = fr;
 }
 
-// binary64 surface term of face f: A += c sum_k (v_k - t) Y_k, B += c J. (An empty record has N = 0 and phases 0: it
-// adds 0.)
+// binary64 surface term of face f: A += c sum_k (v_k - t) Y_k, B += c J. (A zero-area face has N = 0 and finite
+// moments: it adds 0.)
 __device__ __forceinline__ void dq_term_f64(const Face64& f, const double* G, const double* Q, bool big, double* Ar,
                                             double* Ai, double& Br, double& Bi) {
   const Fit64 t = fit64();

@@ -41,7 +41,7 @@ __device__ __forceinline__ void face_integral_far64(Fit64 t, double d0, double d
 
 // One face against a thread's NQ Q points, binary64: adds T = -i (Q.N) exp(iQ.g) J to xr, xi. J by the fitted
 // polynomials where the largest centred vertex phase is at most FaceFit64::M (no quotient, nothing cancels near the
-// face normal), by the edge terms beyond; the choice is per lane. An empty record (N = 0, phases 0) gives 0. big
+// face normal), by the edge terms beyond; the choice is per lane. A face without area (N = 0, finite J) gives 0. big
 // (wavefront-uniform): some origin phase may exceed kSinCosMax64.
 template <int NQ>
 __device__ __forceinline__ void fwd_face_f64(const Face64& f, const double (*Q)[3], bool big, double* xr, double* xi) {

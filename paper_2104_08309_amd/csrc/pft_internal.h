@@ -153,7 +153,7 @@ struct alignas(16) Face64 {
   double u0[3];   // a - g
   double u1[3];   // b - g          (c - g = -u0 - u1)
   double N[3];    // (b - a) x (c - a) = 2 A n
-  double thr;     // series when |Q x N|^2 < thr  (tau^2 |N|^2 / L^2; -1 for an empty face)
+  double thr;     // < 0 marks a face without area (N = 0, but its vertices stay) or with a bad index (all 0)
   double pad[3];
 };
 static_assert(sizeof(Face64) == 128, "Face64 layout");
