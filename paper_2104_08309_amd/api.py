@@ -260,6 +260,21 @@ def forward_3d_noalloc(verts: torch.Tensor, tris: torch.Tensor, q: torch.Tensor,
     return (out, inten) if intensity else out
 
 
+def _flat_faces(faces: Sequence[Sequence[int]]) -> Tuple[np.ndarray, np.ndarray]:
+    """(offsets int64 [nf + 1], vertex indices int32) of a list of faces; an index that int32 cannot hold raises."""
+    off = np.zeros(len(faces) + 1, dtype=np.int64)
+    np.cumsum(np.fromiter(map(len, faces), dtype=np.int64, count=len(faces)), out=off[1:])
+    # numpy's own conversion, several times as fast as int() on each entry; where it does not convert (0-dim tensors)
+    # or could have wrapped (0-dim arrays are cast, not checked) each entry goes through int()
+    try:
+        flat = np.fromiter(itertools.chain.from_iterable(faces), dtype=np.int64, count=int(off[-1]))
+        if flat.size == 0 or flat.view(np.uint64).max() <= np.iinfo(np.int32).max:
+            return off, flat.astype(np.int32)
+    except (TypeError, ValueError, OverflowError):
+        pass
+    return off, np.fromiter((int(x) for f in faces for x in f), dtype=np.int32, count=int(off[-1]))
+
+
 def forward_3d_poly(verts: torch.Tensor, faces: Sequence[Sequence[int]], q: torch.Tensor, mode: str = "fp32c",
                     intensity: bool = False):
     """F(Q) of a closed mesh of planar polygon faces (each a CCW list of vertex indices, 3 to 256).
@@ -269,12 +284,7 @@ def forward_3d_poly(verts: torch.Tensor, faces: Sequence[Sequence[int]], q: torc
     verts = _on_gpu(verts, "verts")
     if verts.dim() != 2 or verts.shape[1] != 3:
         raise ValueError(f"verts must have shape [nv, 3], got {tuple(verts.shape)}")
-    off = np.zeros(len(faces) + 1, dtype=np.int64)
-    np.cumsum(np.fromiter(map(len, faces), dtype=np.int64, count=len(faces)), out=off[1:])
-    try:
-        flat = np.fromiter(itertools.chain.from_iterable(faces), dtype=np.int32, count=int(off[-1]))
-    except (TypeError, ValueError):  # entries that numpy does not convert by itself (0-dim tensors)
-        flat = np.fromiter((int(x) for f in faces for x in f), dtype=np.int32, count=int(off[-1]))
+    off, flat = _flat_faces(faces)
     fv = torch.from_numpy(flat).to(verts.device)
     q = _qlist(q, verts.device)
     m = mode_id(mode)
