@@ -311,6 +311,9 @@ __device__ __forceinline__ void write_transform(const FwdArgs& a, int out_c128, 
 // the split form's wavefronts loaded, reduced and finished each Q for three faces each (12 faces x 2^21 Q of |Q| about
 // 9: 187 -> 88 us a call; x 128^3 grid: 127 -> 69; two Q a thread instead of one: 91). Bound by issue: of the faces'
 // polynomials and phases for small faces, of the edge terms' transcendentals for large ones.
+// The faces are summed in binary32 in as many runs as the split form has wavefronts, and the runs in binary64, as there
+// (one binary32 sum of 32 faces doubled the error of F at phases of some radians, 5.3e-8 -> 1.07e-7; the runs cost nothing
+// that can be measured: 12 faces x 128^3, 68.8 and 68.2 us a call).
 __global__ __launch_bounds__(kBlock, 8) void fwd3d_few_fp32c_kernel(FwdArgs a) {
   __shared__ Face32 tile[kTileF32];
   const int nt = (int)a.nf;
@@ -328,15 +331,22 @@ __global__ __launch_bounds__(kBlock, 8) void fwd3d_few_fp32c_kernel(FwdArgs a) {
   const bool small = qi < a.nq && qabs * R < a.tau0;
   ql.wide[0] = !(qabs * R <= kWidePhase32);
   ql.any_wide = __any(ql.wide[0]) != 0;
-  float tr[1] = {0.0f}, ti[1] = {0.0f};
   FwdCarry<1> carry;
   carry.reset();
   const double rho = fmax(a.info[0].rho, a.info[0].fan_rho);
-  if (__builtin_amdgcn_readfirstlane((int)fit_range_test_needed(wave_max((float)qabs), rho)))
-    fwd_tile_fp32c<1, false, true>(tile, nt, qx, qy, qz, ql, tr, ti, carry);
-  else
-    fwd_tile_fp32c<1, false, false>(tile, nt, qx, qy, qz, ql, tr, ti, carry);
-  double x[2] = {(double)tr[0], (double)ti[0]};
+  const bool check = __builtin_amdgcn_readfirstlane((int)fit_range_test_needed(wave_max((float)qabs), rho)) != 0;
+  double x[2] = {0.0, 0.0};
+  const int per = (nt + kFwdSplitWaves - 1) / kFwdSplitWaves;
+  for (int j = 0; j < nt; j += per) {
+    float tr[1] = {0.0f}, ti[1] = {0.0f};
+    const int n = min(per, nt - j);
+    if (check)
+      fwd_tile_fp32c<1, false, true>(tile + j, n, qx, qy, qz, ql, tr, ti, carry);
+    else
+      fwd_tile_fp32c<1, false, false>(tile + j, n, qx, qy, qz, ql, tr, ti, carry);
+    x[0] += (double)tr[0];
+    x[1] += (double)ti[0];
+  }
   if (__any(small))
     fan_sum<2>(small, 0, nt, Q,
                [&](int64_t f, const double* q, double* t) { tet_term_f64(a.f64[f], q, t[0], t[1], kZeroOrigin); }, x);
