@@ -536,6 +536,7 @@ pft_status build_qorder(Arena& ar, const void* q, int qdtype, int64_t nq, const 
   if (nq < kQOrderMin || nq > INT32_MAX) return PFT_OK;
   QOrderScratch w;
   w.box_partial = ar.get<double>(256 * 6);
+  w.span = ar.get<float2>((size_t)n_meshes * 3);
   w.keys = ar.get<uint32_t>(nq);
   w.keys2 = ar.get<uint32_t>(nq);
   w.vals = ar.get<uint32_t>(nq);

@@ -443,7 +443,8 @@ hipError_t launch_bwd3d_fp32c(const BwdArgs& a, hipStream_t s);
 // (d_q_off: CSR offsets of Q per mesh, or NULL for one mesh). perm[i] is the
 // caller's index of the i-th visited Q.
 struct QOrderScratch {   // device temporaries of launch_qorder
-  double* box_partial;   // [256 * 6]
+  double* box_partial;   // [256 * 6], of one list (d_q_off NULL)
+  float2* span;          // [n_meshes * 3]
   uint32_t* keys;        // [nq]
   uint32_t* keys2;       // [nq]
   uint32_t* vals;        // [nq]

@@ -4,10 +4,12 @@
 // order. Their cost per (Q, face) follows the worst lane of a wavefront: the
 // edge form beyond the fitted phase range runs whenever one lane needs it. Wavefronts of nearby Q waste less
 // work than wavefronts spanning a grid row or a random set. The Q points are
-// sorted by mesh, then by the Morton code of their coordinates quantised
-// inside the bounding box of all Q (5 bits per axis); the forward reads Q
-// through the permutation and writes F back to the caller's order, the FP32C
-// adjoint gathers Q with their centred cotangents into QRec32 records.
+// sorted by mesh, then by the Morton code of their cells (5 bits per axis). One
+// list: cells of the box of its Q, or of the span of most of them (list_span)
+// where a few outlying Q make the box four times as wide. Batch: cells of each
+// list's own span. The forward reads Q through the permutation and writes F back
+// to the caller's order, the adjoints gather Q with their centred cotangents into
+// QRec records.
 //
 // The sort is a stable radix sort by 8-bit digits, three launches a pass
 // (digit counts per tile, their scan, the scatter), two passes for one mesh.
@@ -22,11 +24,65 @@ namespace {
 
 constexpr int kBoxBlocks = 256;
 
-__global__ __launch_bounds__(256) void qbox_partial_kernel(const void* q, int qdtype, int64_t nq, double* partial) {
-  __shared__ double red[6][256];
+// The span along an axis of all but about 3 % of a list's Q: kSpanSample of them, one from each stretch of the list (at a
+// scrambled place in it, so that the period of a grid list does not show), less kSpanTrim at either end, widened to what
+// the whole sample of an even list would span. Its cost does not depend on the list's length. {lowest, width}; {0, 0}
+// for a list of one wavefront or less; not finite where that many Q are not. A block of kSpanSample threads calls it.
+// Cells of a common box put two thirds of the wavefronts of such lists back into the list order (12 lists of 24 000 Q,
+// short and long by turns, two in each at 30 times the range: binary64 adjoint 1.36 ms, 1.00 with spans; 48 lists of
+// 5 000 to 40 000 and one such Q each: FP32C adjoint 1.78 -> 1.45 ms; without such Q the same to 1 % either way).
+constexpr int kSpanSample = 256;
+constexpr int kSpanTrim = 4;
+__device__ __forceinline__ void list_span(const void* q, int qdtype, int64_t b, int64_t n, int axis, float2* out) {
+  __shared__ float x[kSpanSample], end[2];
   const int tid = threadIdx.x;
+  if (n <= 64) {
+    if (tid == 0) *out = make_float2(0.0f, 0.0f);
+    return;
+  }
+  uint32_t h = (uint32_t)tid * 2654435769u;
+  h = (h ^ (h >> 15)) * 2246822519u;
+  h ^= h >> 13;
+  double Q[3];
+  load_q3(q, qdtype, b + (tid * n + (int64_t)(((uint64_t)h * (uint64_t)n) >> 32)) / kSpanSample, Q);
+  const float v = (float)Q[axis];
+  x[tid] = v == v ? v : INFINITY;  // a NaN goes last
+  __syncthreads();
+  const float mine = x[tid];
+  int below = 0, upto = 0;  // of the sample: less than mine, at most mine
+  for (int i = 0; i < kSpanSample; ++i) {
+    const float u = x[i];
+    below += u < mine;
+    upto += u <= mine;
+  }
+  // the sample's values at the two places (the threads of equals of such a value write the same)
+  constexpr int kLo = kSpanTrim, kHi = kSpanSample - 1 - kSpanTrim;
+  if (below <= kLo && kLo < upto) end[0] = mine;
+  if (below <= kHi && kHi < upto) end[1] = mine;
+  __syncthreads();
+  if (tid != 0) return;
+  const float w = end[1] - end[0], wide = w * ((float)kSpanSample / (float)(kSpanSample - 2 * kSpanTrim));
+  *out = make_float2(end[0] - 0.5f * (wide - w), wide);
+}
+
+__global__ __launch_bounds__(kSpanSample) void batch_span_kernel(const void* q, int qdtype, const int64_t* q_off,
+                                                                 float2* span) {
+  const int64_t b = q_off[blockIdx.x];
+  list_span(q, qdtype, b, q_off[blockIdx.x + 1] - b, (int)blockIdx.y, span + (int64_t)blockIdx.x * 3 + blockIdx.y);
+}
+
+// One list: the partial boxes of its Q (blocks 0 .. gridDim.x - 4) and its span per axis (the last three blocks).
+__global__ __launch_bounds__(256) void qbox_partial_kernel(const void* q, int qdtype, int64_t nq, double* partial,
+                                                           float2* span) {
+  static_assert(kSpanSample == 256, "blocks of both kinds");
+  __shared__ double red[6][256];
+  const int tid = threadIdx.x, boxes = (int)gridDim.x - 3;
+  if ((int)blockIdx.x >= boxes) {
+    list_span(q, qdtype, 0, nq, (int)blockIdx.x - boxes, span + (blockIdx.x - boxes));
+    return;
+  }
   double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + tid; i < nq; i += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + tid; i < nq; i += (int64_t)boxes * blockDim.x) {
     double Q[3];
     load_q3(q, qdtype, i, Q);
     for (int k = 0; k < 3; ++k) {
@@ -82,46 +138,65 @@ __device__ __forceinline__ int64_t sort_first() {
   return (int64_t)blockIdx.x * kSortTile + (int64_t)(threadIdx.x >> 6) * (64 * kSortRounds);
 }
 
-// Keys of the tile's Q (mesh, then Morton code of `bits` bits per axis inside the box of all Q, whose partial boxes
-// every block reduces for itself) and the counts of their lowest digit.
+// Keys of the tile's Q (mesh, then Morton code of `bits` bits per axis) and the counts of their lowest digit. One list:
+// cells of the box of all Q, whose partial boxes every block reduces for itself, or of the list's span. BATCH: of each
+// list's span.
+template <bool BATCH>
 __global__ __launch_bounds__(kSortBlock) void qkey_kernel(const void* q, int qdtype, int64_t nq,
-                                                          const double* box_partial, int n_partial,
+                                                          const double* box_partial, int n_partial, const float2* span,
                                                           const int64_t* q_off, int64_t n_meshes, int bits,
                                                           uint32_t* keys, uint32_t* counts) {
-  __shared__ double red[6][kSortBlock];
   __shared__ uint32_t hist[kDigits];
   const int tid = threadIdx.x;
-  for (int k = 0; k < 6; ++k)
-    red[k][tid] = tid < n_partial ? box_partial[tid * 6 + k] : (k < 3 ? INFINITY : -INFINITY);
   hist[tid] = 0u;
-  __syncthreads();
-  for (int h = kSortBlock / 2; h > 0; h >>= 1) {
-    if (tid < h)
-      for (int k = 0; k < 3; ++k) {
-        red[k][tid] = fmin(red[k][tid], red[k][tid + h]);
-        red[3 + k][tid] = fmax(red[3 + k][tid], red[3 + k][tid + h]);
+  double lo[3], ext[3];
+  if constexpr (!BATCH) {
+    __shared__ double red[6][kSortBlock];
+    for (int k = 0; k < 6; ++k)
+      red[k][tid] = tid < n_partial ? box_partial[tid * 6 + k] : (k < 3 ? INFINITY : -INFINITY);
+    __syncthreads();
+    for (int h = kSortBlock / 2; h > 0; h >>= 1) {
+      if (tid < h)
+        for (int k = 0; k < 3; ++k) {
+          red[k][tid] = fmin(red[k][tid], red[k][tid + h]);
+          red[3 + k][tid] = fmax(red[3 + k][tid], red[3 + k][tid + h]);
+        }
+      __syncthreads();
+    }
+    for (int k = 0; k < 3; ++k) {
+      lo[k] = red[k][0];
+      ext[k] = red[3 + k][0] - lo[k];
+      if (ext[k] > 4.0 * (double)span[k].y) {
+        lo[k] = (double)span[k].x;
+        ext[k] = (double)span[k].y;
       }
+    }
+  } else {
     __syncthreads();
   }
   const double cells = (double)(1u << bits);
-  double lo[3], ext[3];
-  for (int k = 0; k < 3; ++k) {
-    lo[k] = red[k][0];
-    ext[k] = red[3 + k][0] - lo[k];
-  }
   const int64_t i0 = sort_first() + (tid & 63);
   for (int r = 0; r < kSortRounds; ++r) {
     const int64_t i = i0 + r * 64;
     if (i >= nq) break;
     double Q[3];
     load_q3(q, qdtype, i, Q);
+    int64_t mesh = 0;
+    if constexpr (BATCH) {
+      mesh = mesh_of(q_off, n_meshes, i);
+      for (int k = 0; k < 3; ++k) {
+        const float2 s = span[mesh * 3 + k];
+        lo[k] = (double)s.x;
+        ext[k] = (double)s.y;
+      }
+    }
     uint32_t code = 0;
     for (int k = 0; k < 3; ++k) {
       double u = ext[k] > 0.0 ? (Q[k] - lo[k]) / ext[k] * cells : 0.0;
       u = fmin(fmax(u, 0.0), cells - 1.0);  // NaN coordinates map to 0 (fmax returns the non-NaN operand)
       code |= (uint32_t)spread3((uint32_t)u) << k;
     }
-    const uint32_t key = (uint32_t)((uint64_t)mesh_of(q_off, n_meshes, i) << (3 * bits)) | code;
+    const uint32_t key = (uint32_t)((uint64_t)mesh << (3 * bits)) | code;
     keys[i] = key;
     atomicAdd(&hist[key & (kDigits - 1)], 1u);
   }
@@ -290,7 +365,10 @@ hipError_t launch_qorder(const void* q, int qdtype, int64_t nq, const int64_t* d
   const int nb = (int)std::min<int64_t>(kBoxBlocks, (nq + 255) / 256);
   static_assert(kDigits == kSortBlock, "a thread per digit");
   static_assert(kBoxBlocks <= kSortBlock, "a block reduces all partial boxes in one step");
-  qbox_partial_kernel<<<nb, 256, 0, s>>>(q, qdtype, nq, w.box_partial);
+  if (d_q_off)
+    batch_span_kernel<<<dim3((unsigned)n_meshes, 3), kSpanSample, 0, s>>>(q, qdtype, d_q_off, w.span);
+  else
+    qbox_partial_kernel<<<nb + 3, 256, 0, s>>>(q, qdtype, nq, w.box_partial, w.span);
   int mesh_bits = 0;
   while (mesh_bits < 32 && ((int64_t)1 << mesh_bits) < n_meshes) ++mesh_bits;
   const int bits = std::min(5, (32 - mesh_bits) / 3);  // Morton bits per axis
@@ -300,8 +378,12 @@ hipError_t launch_qorder(const void* q, int qdtype, int64_t nq, const int64_t* d
   uint32_t *from = w.keys, *to = w.keys2, *totals = w.counts + (int64_t)tiles * kDigits;
   for (int p = 0; p < passes; ++p) {
     const bool last = p + 1 == passes;
-    if (p == 0)
-      qkey_kernel<<<tiles, kSortBlock, 0, s>>>(q, qdtype, nq, w.box_partial, nb, d_q_off, n_meshes, bits, from, w.counts);
+    if (p == 0 && d_q_off)
+      qkey_kernel<true><<<tiles, kSortBlock, 0, s>>>(q, qdtype, nq, nullptr, 0, w.span, d_q_off, n_meshes, bits, from,
+                                                     w.counts);
+    else if (p == 0)
+      qkey_kernel<false><<<tiles, kSortBlock, 0, s>>>(q, qdtype, nq, w.box_partial, nb, w.span, nullptr, 1, bits, from,
+                                                      w.counts);
     else
       sort_count_kernel<<<tiles, kSortBlock, 0, s>>>(from, nq, 8 * p, w.counts);
     sort_scan_kernel<<<kDigits, kSortBlock, 0, s>>>(w.counts, tiles, totals);
