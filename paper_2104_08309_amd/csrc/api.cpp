@@ -1458,7 +1458,7 @@ pft_status pft_intensity_loss_3d(const void* verts, pft_dtype vdtype, int64_t nv
                           MeshRecords{f64, ordered ? nullptr : f32, f32b, gram}, s);
   if (e == hipSuccess && ordered)
     e = launch_mesh_records(verts, vdtype, nv, tris, nf, info, kTauF64, MeshRecords{f64o, f32, nullptr, nullptr}, s,
-                            face_order, face_meta);
+                            face_order, face_meta, true);
   if (e != hipSuccess) return hip_fail(e, "loss prologue");
   uint32_t* perm = nullptr;
   if ((st = build_qorder(ar, q, qdtype, nq, nullptr, 1, &perm, s)) != PFT_OK) return st;

@@ -233,9 +233,10 @@ struct MeshRecords {
 };
 // Centre, radius and records of one mesh. With order / meta (device, [nf]; NULL: the list order), record m is face
 // order[m] with its vertex list rotated by meta[m] & 3, and pad[2] holds the link meta[m] >> 2 (0, 1 or 2).
+// have_info: info is that of an earlier call for the same vertices; only the records are made.
 hipError_t launch_mesh_records(const void* verts, int vdtype, int64_t nv, const int32_t* tris, int64_t nf,
                                MeshInfo* info, double tau, const MeshRecords& rec, hipStream_t s,
-                               const int32_t* order = nullptr, const uint8_t* meta = nullptr);
+                               const int32_t* order = nullptr, const uint8_t* meta = nullptr, bool have_info = false);
 // The records other than f64 from it.
 hipError_t launch_face_records(const MeshRecords& rec, int64_t nf, hipStream_t s);
 hipError_t launch_face64_batch(const void* verts, int vdtype, const int32_t* tris, const int64_t* d_vert_off,

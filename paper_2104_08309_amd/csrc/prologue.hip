@@ -704,15 +704,17 @@ hipError_t launch_face_records(const MeshRecords& rec, int64_t nf, hipStream_t s
 
 hipError_t launch_mesh_records(const void* verts, int vdtype, int64_t nv, const int32_t* tris, int64_t nf,
                                MeshInfo* info, double tau, const MeshRecords& rec, hipStream_t s,
-                               const int32_t* order, const uint8_t* meta) {
+                               const int32_t* order, const uint8_t* meta, bool have_info) {
   // one block for up to half its threads' faces: 320 faces 12.1 us in three launches, 10.1 in one (and two launches
   // fewer on the host); 1 280 faces 13.5 us in three, 22 in one
-  if (nf <= kInfoBlock / 2 && nv <= kInfoBlock) {
+  if (!have_info && nf <= kInfoBlock / 2 && nv <= kInfoBlock) {
     mesh_records_small_kernel<<<1, kInfoBlock, 0, s>>>(verts, vdtype, nv, tris, nf, tau, order, meta, info, rec);
     return hipGetLastError();
   }
   const int64_t blocks = nv / kCentrePerBlock < kCentreBlocks ? nv / kCentrePerBlock : kCentreBlocks;
-  if (nv >= kCentreSplitVerts && nf * (int64_t)sizeof(Face64) >= kCentreBlocks * 3 * (int64_t)sizeof(double)) {
+  if (have_info) {
+    // centre and radius stay, rho is raised to the same value again
+  } else if (nv >= kCentreSplitVerts && nf * (int64_t)sizeof(Face64) >= kCentreBlocks * 3 * (int64_t)sizeof(double)) {
     double(*partial)[3] = reinterpret_cast<double(*)[3]>(rec.f64);  // the records come after
     centre_sum_kernel<<<(unsigned)blocks, kInfoBlock, 0, s>>>(verts, vdtype, nv, partial, info);
     centre_radius_kernel<<<(unsigned)blocks, kInfoBlock, 0, s>>>(verts, vdtype, nv, partial, info);
