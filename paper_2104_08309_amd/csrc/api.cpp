@@ -1326,11 +1326,16 @@ pft_status pft_orientation_average(const void* verts, pft_dtype vdtype, int64_t 
   if (ar.failed) return fail(PFT_ENOMEM, "temporary allocation failed");
   hipError_t e = launch_qdirs(qabs, nqa, dirs, ndir, Q, s);
   if (e != hipSuccess) return hip_fail(e, "orientation Q list");
-  // A list of many directions per magnitude is in order as it stands: a wavefront's Q share |Q|, which decides what its
-  // pairs cost. Sorting them costs the sort and mixes the magnitudes near 0, where the keys' cells are coarse (1 280
-  // faces, 200 x 512 Q: 292 us sorted, 192 as it stands, 298 and 257 with magnitudes and directions shuffled). With 128
-  // directions the shuffled list was slower unsorted (2 000 magnitudes: 391 and 441 us).
-  const bool sort_q = ndir < 256;
+  // A list of many directions per magnitude is in order as it stands: a wavefront's Q share |Q|, which decides most of
+  // what its pairs cost. Measured in us a call, sorted -> as it stands, 256 to 2 048 directions, 40 to 400 magnitudes of
+  // |Q| to 0.5, in order and shuffled, twelve meshes of 12 to 20 480 faces: FP32C is never slower as it stands (36 faces
+  // x 10 240 Q 68 -> 35, 1 280 x 102 400 314 -> 203, 528 x 819 200 605 -> 500, 20 480 x 204 800 3 800 -> 3 600). Binary64
+  // pays twice the fitted form's price for a far pair and so more for a wavefront of both kinds, wherever phases lie about
+  // its limit: 224 faces x 102 400 Q 197 -> 193, x 204 800 315 -> 330, x 819 200 846 -> 930 to 1 015; 528 x 819 200
+  // 1 757 -> 1 846. Elsewhere the sort is lost there too, but it is the smaller loss from about 1e8 pairs (1 280 x 102 400
+  // 544 -> 500, x 204 800 950 -> 906, x 819 200 3 467 -> 3 397). With 128 directions FP32C was slower as it stands (2 000
+  // magnitudes, shuffled: 391 and 441).
+  const bool sort_q = ndir < 256 || (c128 && (double)nf * (double)nq >= 1e8);
   st = forward3d_core(ar, verts, vdtype, nv, tris, nf, Q, PFT_F64, nq, mode, nullptr, I, s,
                       nf > 0 ? face_order : nullptr, nf > 0 ? face_meta : nullptr, nullptr, sort_q);
   if (st != PFT_OK) return st;
