@@ -303,7 +303,8 @@ void choose_face_splits(int64_t nq, int64_t nf, int64_t qtile, int64_t min_faces
 // A call whose blocks of at least kMinFacesPerSplit faces per wavefront would leave most of the chip idle is
 // cut finer, down to kSmallFaces faces per block and, if that does not give kSmallBlocks blocks either, one Q
 // per thread: such a call is bound by the latency of its longest wavefront, not by issue. 320 faces x 4 096 Q
-// (32 blocks before): 67.5 us a call; cut to 64 faces per block and one Q per thread (320 blocks) 27.8 us.
+// (32 blocks before): 67.5 us a call; with one Q per thread and 64, 32 or 16 faces per block 26 to 28 us, with 8 31 us
+// (more partial sums to add).
 constexpr int64_t kSmallBlocks = 1024;  // four blocks of four wavefronts per CU
 #ifndef PFT_SMALL_FACES
 #define PFT_SMALL_FACES 16

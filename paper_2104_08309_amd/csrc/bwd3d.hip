@@ -183,7 +183,7 @@ __global__ __launch_bounds__(kGatherBlock) void gather_small_kernel(const int32_
   const int64_t v = (int64_t)blockIdx.x * (kGatherBlock / 64) + (threadIdx.x >> 6);
   if (v >= nv) return;
   double g[3] = {0.0, 0.0, 0.0};
-  // up to 64 of the vertex's corners at a time, one per lane, in corner order
+  // up to 64 of the vertex's corners at a time, one per lane, added by a butterfly
   auto flush = [&](int n, int64_t i) {
     double c[3] = {0.0, 0.0, 0.0};
     if (lane < n) {

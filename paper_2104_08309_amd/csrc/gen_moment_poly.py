@@ -1,5 +1,7 @@
-"""Writes moment_poly.h: the polynomials of exp(ix) that the binary32 adjoint uses for a
-triangle's barycentric moments at small centred vertex phases.
+"""Writes moment_poly.h: polynomials of exp(ix) for a triangle's face integral and barycentric
+moments at small centred vertex phases in binary32. The polygon kernel uses FacePoly; the bucketed
+MomentPoly are kept as checked tables that no kernel uses (the adjoint's moments come from the
+symmetric fits of gen_face_poly.py).
 
 The face integral of exp(iQ.x) over a triangle, normalised by twice its area, and the
 moments of the barycentric coordinates are averages over the standard simplex of
@@ -17,8 +19,7 @@ the exact moments (the simplex has area 1/2, each moment weight integrates to 1/
 Taylor polynomial (a_n = 1/n!) needs about e M + log(1/eps) terms; Chebyshev
 interpolation of cos and sin on [-M, M] (at the Chebyshev points of the first kind,
 mapped to [-M, M]) needs fewer, its error being about 2 (M/2)^(N+1) / (N+1)! against
-M^(N+1) / (N+1)! for Taylor. One polynomial per phase bucket M; a wavefront uses the
-bucket of the largest m among its lanes.
+M^(N+1) / (N+1)! for Taylor. One polynomial per phase bucket M.
 
 Run from this directory: python gen_moment_poly.py > moment_poly.h
 """
@@ -93,6 +94,7 @@ def main():
     out.append("// moments: cj[n] = a_n n!/(n+2)! (face integral J), cy[n] = a_n n!/(n+3)! (moments Y_k).")
     out.append("// err = max |q(x) - exp(ix)| on [-M, M] with a_n rounded to binary32; J is then within err/2")
     out.append("// and Y_k within err/6 of the exact moments for every triangle with max |d_k| <= M.")
+    out.append("// The polygon kernel uses FacePoly; no kernel uses the MomentPoly.")
     out.append("#pragma once")
     out.append("")
     out.append("namespace pft {")

@@ -15,10 +15,13 @@
 //   T_m(Q) = |Q|^2 I_m = (Q.N)/|P|^2 exp(i Q.g) S_m,
 //   S_m = sum_l (P.d_l) sinc(eta_l) exp(-i psi_{l+2}),
 // and F(Q) = exp(i Q.t) sum_m T_m / |Q|^2 for a mesh re-centred on t.
-// Where |P| -> 0 (Q along the face normal) the edge form is 0/0; there the
-// face integral is evaluated by its simplex series
-//   T_m = -i (Q.N) exp(i Q.g) sum_n i^n h_n(delta_a, delta_b, delta_c)/(n+2)!,
-// delta_k = Q.u_k, h_n the complete homogeneous symmetric polynomial.
+// The same by the face's simplex series,
+//   T_m = -i (Q.N) exp(i Q.g) J,  J = sum_n i^n h_n(delta_a, delta_b, delta_c)/(n+2)!,
+// delta_k = Q.u_k, h_n the complete homogeneous symmetric polynomial, has no
+// quotient: the triangle kernels evaluate J from fitted polynomials of the delta
+// (face_moments.h) and the edge form beyond their range; the polygon kernel the
+// edge form, and the series of a face's fan triangles where |P| -> 0 (Q along the
+// face normal), where the edge form is 0/0.
 #pragma once
 
 #include "pft_internal.h"
@@ -30,8 +33,6 @@ namespace pft {
 
 constexpr float kTwoPiF = 6.28318530717958647692f;
 constexpr float kInv2PiF = 0.15915494309189533577f;
-constexpr double kTwoPi = 6.28318530717958647692;
-constexpr double kInv2PiD = 0.15915494309189533577;
 
 PFT_HD __forceinline__ void load_q3(const void* q, int qdtype, int64_t i, double* Q) {
   if (qdtype == PFT_F64) {
@@ -158,17 +159,11 @@ __device__ __forceinline__ float sin_turns(float x) { return __builtin_amdgcn_si
 __device__ __forceinline__ float cos_turns(float x) { return __builtin_amdgcn_cosf(x); }
 __device__ __forceinline__ float rcp_f(float x) { return __builtin_amdgcn_rcpf(x); }
 
-// sin(2 pi x) / x for x in turns, i.e. 2 pi sinc(2 pi x). At the removable point
-// x = 0 the product is 0 * inf = NaN, and the IEEE minimum with 2 pi (which
-// returns the non-NaN operand) yields the limit 2 pi; elsewhere the quotient is
-// at most 2 pi, so the minimum leaves it unchanged.
-__device__ __forceinline__ float sinc2pi_turns(float x) { return fminf(sin_turns(x) * rcp_f(x), kTwoPiF); }
-
-// The same function as a polynomial in y = x^2 for |x| <= kSincPolyMax = 1/2 turn: the minimax fit of
-// degree 5 in y (Remez exchange on the absolute error over y in [0, 1/4]; fit error 3.9e-7), with the
-// coefficients rounded to binary32. Evaluated by Horner's rule in binary32 the error stays below 1e-6,
-// i.e. 1.6e-7 of the value 2 pi at x = 0 -- the size of the hardware sine's own error divided by x -- with
-// no transcendental instruction and no removable point. Beyond 1/2 turn the caller uses sinc2pi_turns.
+// sin(2 pi x) / x for x in turns, i.e. 2 pi sinc(2 pi x), as a polynomial in y = x^2 for |x| <= kSincPolyMax = 1/2 turn:
+// the minimax fit of degree 5 in y (Remez exchange on the absolute error over y in [0, 1/4]; fit error 3.9e-7), with the
+// coefficients rounded to binary32. Evaluated by Horner's rule in binary32 the error stays below 1e-6, i.e. 1.6e-7 of the
+// value 2 pi at x = 0 -- the size of the hardware sine's own error divided by x -- with no transcendental instruction and
+// no removable point. Beyond 1/2 turn the callers take the quotient.
 constexpr float kSincPolyMax = 0.5f;
 __device__ __forceinline__ float sinc2pi_poly(float x) {
   const float y = x * x;

@@ -17,7 +17,7 @@ constexpr int kBlock = 256;        // threads per block for the Q-parallel kerne
 #ifndef PFT_TILEF
 #define PFT_TILEF 64
 #endif
-constexpr int kTileF = PFT_TILEF;  // faces staged in LDS per tile (binary64 forward and grad_Q)
+constexpr int kTileF = PFT_TILEF;  // faces staged in LDS per tile (grad_Q, binary64 batched forward)
 #ifndef PFT_TILEF32
 #define PFT_TILEF32 64
 #endif
@@ -154,7 +154,8 @@ struct alignas(16) Face64 {
   double u1[3];   // b - g          (c - g = -u0 - u1)
   double N[3];    // (b - a) x (c - a) = 2 A n
   double thr;     // < 0 marks a face without area (N = 0, but its vertices stay) or with a bad index (all 0)
-  double pad[3];
+  double code;    // edge-sharing order: 1 linked to the previous record, 2 traversal reversed
+  double pad[2];
 };
 static_assert(sizeof(Face64) == 128, "Face64 layout");
 
@@ -232,7 +233,7 @@ struct MeshRecords {
   double* gram;
 };
 // Centre, radius and records of one mesh. With order / meta (device, [nf]; NULL: the list order), record m is face
-// order[m] with its vertex list rotated by meta[m] & 3, and pad[2] holds the link meta[m] >> 2 (0, 1 or 2).
+// order[m] with its vertex list rotated by meta[m] & 3, and the records keep its link flags.
 // have_info: info is that of an earlier call for the same vertices; only the records are made.
 hipError_t launch_mesh_records(const void* verts, int vdtype, int64_t nv, const int32_t* tris, int64_t nf,
                                MeshInfo* info, double tau, const MeshRecords& rec, hipStream_t s,
@@ -282,7 +283,7 @@ struct alignas(16) VtxP64 {
 };
 static_assert(sizeof(VtxP64) == 32, "VtxP64 layout");
 
-struct alignas(16) FaceP32 {      // FP32C: in-plane basis as in Face32
+struct alignas(16) FaceP32 {      // FP32C: in an orthonormal in-plane basis
   double gt[3];                   // g / (2 pi): face origin phase in turns is Q . gt
   float N[3];                     // 2 A n
   float E1[3];                    // |N| e1 (e1 along the first non-degenerate edge)
@@ -473,7 +474,7 @@ hipError_t launch_incidence_keys(const int32_t* tris, int64_t nf, const int64_t*
 hipError_t sort_incidence(uint32_t* keys_in, uint32_t* vals_in, uint32_t* keys_out, uint32_t* vals_out, int64_t n,
                           int64_t nv_total, void* temp, size_t* temp_bytes, hipStream_t s);
 // The same for a mesh of at most kSmallGatherFaces faces in one launch: a wavefront per vertex looks its corners up
-// in the triangle list and adds their split sums (in corner order).
+// in the triangle list and adds their split sums (64 corners at a time, each lot by a fixed butterfly).
 constexpr int64_t kSmallGatherFaces = 2048;
 hipError_t launch_gather_small(const int32_t* tris, int64_t nf, int64_t nv, const double* partial, int qsplits,
                                const Face64* f64, const double* face_w, void* grad, int vdtype, hipStream_t s);

@@ -114,15 +114,14 @@ __device__ inline void make_face64(const double* a, const double* b, const doubl
     f.N[k] = N[k];
   }
   f.thr = (N2 > 0.0 && L2 > 0.0) ? tau * tau * N2 / L2 : -1.0;
-  f.pad[0] = L2;
-  f.pad[1] = N2;
-  f.pad[2] = 0.0;
+  f.code = 0.0;
+  f.pad[0] = f.pad[1] = 0.0;
 }
 
 __device__ inline void empty_face64(Face64& f) {
   for (int k = 0; k < 3; ++k) f.g[k] = f.u0[k] = f.u1[k] = f.N[k] = 0.0;
   f.thr = -1.0;
-  f.pad[0] = f.pad[1] = f.pad[2] = 0.0;
+  f.code = f.pad[0] = f.pad[1] = 0.0;
 }
 
 // Largest squared distance from a face record's centroid to its vertices (u0, u1, -u0 - u1).
@@ -207,7 +206,7 @@ __device__ inline void raise_rho(MeshInfo* info, int64_t mesh, double ext2) {
               (unsigned long long)__double_as_longlong(sqrt(ext2)));
 }
 
-// The edge-sharing flags of position m kept in Face64::pad[2] for the FP32C record
+// The edge-sharing flags of position m kept in Face64::code for the FP32C record
 // builder: 1 = linked to the previous position, 2 = traversal reversed. The Face64
 // record itself keeps the outward (rotated) vertex order.
 __device__ __forceinline__ int order_code(const uint8_t* meta, int64_t m) {
@@ -240,7 +239,7 @@ __device__ inline double face64_at(const void* verts, int vdtype, int64_t nv, co
     c[k] -= t[k];
   }
   make_face64(a, b, c, tau, f);
-  f.pad[2] = (double)order_code(meta, m);
+  f.code = (double)order_code(meta, m);
   return face_extent2(f);
 }
 
@@ -384,7 +383,7 @@ __global__ __launch_bounds__(256) void poly_fan_kernel(const void* verts, int vd
         vertex(b + l, v1);
         vertex(b + l + 1, v2);
         make_face64(a, v1, v2, tau, f);
-        f.pad[2] = l > 1 ? 3.0 : 2.0;  // reversed traversal, linked to the previous triangle of the fan
+        f.code = l > 1 ? 3.0 : 2.0;  // reversed traversal, linked to the previous triangle of the fan
         fan2 = fmax(fan2, face_extent2(f));
       } else {
         empty_face64(f);
@@ -506,7 +505,7 @@ __global__ __launch_bounds__(256) void face64_batch_kernel(const void* verts, in
         c[k] -= mi.t[k];
       }
       make_face64(a, b, c, tau, f);
-      f.pad[2] = (double)code;
+      f.code = (double)code;
       ext2 = face_extent2(f);
     }
     out[m] = f;
@@ -534,7 +533,7 @@ __device__ inline Face32 face32_at(const Face64* in, int64_t m) {
   const Face64 f = in[m];
   Face32 r;
   const bool ok = f.thr >= 0.0;
-  const int code = (int)f.pad[2];
+  const int code = (int)f.code;
   const bool refl = (code & 2) != 0;  // traversal (b, a, c) instead of (a, b, c)
   for (int k = 0; k < 3; ++k) {
     r.gt[k] = f.g[k] * kInv2Pi;
