@@ -13,10 +13,11 @@
 //
 // The sort is a stable radix sort by 8-bit digits, three launches a pass
 // (digit counts per tile, their scan, the scatter), two passes for one mesh.
-// It is bound by launches and their tails at these sizes: against the library
-// sort, whose merge-based path below 1e5 keys took 14 launches, ordering
-// 91 125 Q takes 35 us instead of 87, 1.4e6 Q of 64 meshes 128 us instead of
-// about 230 (which sorted 36-bit keys, 10 bits per axis).
+// It is bound by launches and their tails on short lists: against the library
+// sort, whose merge-based path below 1e5 keys took 14 launches, ordering 91 125 Q
+// takes 36 us instead of 75, 1.4e6 Q of 64 meshes about 125 instead of 230 (which
+// sorted 36-bit keys, 10 bits per axis). Long lists are bound by the scattered
+// writes: 4e6 random Q 104 us (202 with the tiles of short lists; library 137).
 #include "pft_device.h"
 
 namespace pft {
@@ -71,6 +72,26 @@ __global__ __launch_bounds__(kSpanSample) void batch_span_kernel(const void* q, 
   list_span(q, qdtype, b, q_off[blockIdx.x + 1] - b, (int)blockIdx.y, span + (int64_t)blockIdx.x * 3 + blockIdx.y);
 }
 
+// Box of every stride-th Q from `first` (each thread's own part of a list), kAhead of them in flight.
+template <class T>
+__device__ __forceinline__ void box_of(const T* q, int64_t nq, int64_t first, int64_t stride, double* lo, double* hi) {
+  constexpr int kAhead = 4;
+  for (int64_t i = first; i < nq; i += kAhead * stride) {
+    T Q[kAhead][3];
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u) {
+      const int64_t j = 3 * min(i + u * stride, nq - 1);
+      for (int k = 0; k < 3; ++k) Q[u][k] = q[j + k];
+    }
+#pragma unroll
+    for (int u = 0; u < kAhead; ++u)
+      for (int k = 0; k < 3; ++k) {
+        lo[k] = fmin(lo[k], (double)Q[u][k]);
+        hi[k] = fmax(hi[k], (double)Q[u][k]);
+      }
+  }
+}
+
 // One list: the partial boxes of its Q (blocks 0 .. gridDim.x - 4) and its span per axis (the last three blocks).
 __global__ __launch_bounds__(256) void qbox_partial_kernel(const void* q, int qdtype, int64_t nq, double* partial,
                                                            float2* span) {
@@ -82,14 +103,11 @@ __global__ __launch_bounds__(256) void qbox_partial_kernel(const void* q, int qd
     return;
   }
   double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + tid; i < nq; i += (int64_t)boxes * blockDim.x) {
-    double Q[3];
-    load_q3(q, qdtype, i, Q);
-    for (int k = 0; k < 3; ++k) {
-      lo[k] = fmin(lo[k], Q[k]);
-      hi[k] = fmax(hi[k], Q[k]);
-    }
-  }
+  const int64_t first = (int64_t)blockIdx.x * blockDim.x + tid, stride = (int64_t)boxes * blockDim.x;
+  if (qdtype == PFT_F64)
+    box_of(static_cast<const double*>(q), nq, first, stride, lo, hi);
+  else
+    box_of(static_cast<const float*>(q), nq, first, stride, lo, hi);
   for (int k = 0; k < 3; ++k) {
     red[k][tid] = lo[k];
     red[3 + k][tid] = hi[k];
@@ -126,22 +144,30 @@ __device__ __forceinline__ int64_t mesh_of(const int64_t* q_off, int64_t n_meshe
   return lo;
 }
 
-// Sort tiles: kSortTile items per block, each wavefront a contiguous quarter of it.
+// Sort tiles: 256 ROUNDS items per block, each wavefront a contiguous quarter of it. 4 rounds on short lists (16: 14 us a
+// scatter of 91 125, which are 23 blocks), 16 on long ones, whose scatter then has runs of a digit to write in one piece.
 constexpr int kSortBlock = 256;
-constexpr int kSortRounds = 4;                            // items per thread (16: 14 us a scatter of 91 125, 23 blocks)
-constexpr int kSortTile = kSortBlock * kSortRounds;
 constexpr int kSortWaves = kSortBlock / 64;
+constexpr int kSortRounds = 4, kSortRoundsLong = 16;
+constexpr int64_t kSortLong = 3 << 19;  // short and long tiles: 1e6 random Q 70 and 73 us, a grid of them 57 and 72; 1.5e6
+                                        // 95 and 81, 72 and 80; 2e6 119 and 87, 87 and 86
 constexpr int kDigits = 256;
+inline int sort_rounds(int64_t nq) { return nq >= kSortLong ? kSortRoundsLong : kSortRounds; }
+inline int64_t sort_tiles(int64_t nq) {
+  const int64_t tile = (int64_t)kSortBlock * sort_rounds(nq);
+  return (nq + tile - 1) / tile;
+}
 
 // First item of this wavefront's part of the block's tile.
+template <int ROUNDS>
 __device__ __forceinline__ int64_t sort_first() {
-  return (int64_t)blockIdx.x * kSortTile + (int64_t)(threadIdx.x >> 6) * (64 * kSortRounds);
+  return (int64_t)blockIdx.x * (kSortBlock * ROUNDS) + (int64_t)(threadIdx.x >> 6) * (64 * ROUNDS);
 }
 
 // Keys of the tile's Q (mesh, then Morton code of `bits` bits per axis) and the counts of their lowest digit. One list:
 // cells of the box of all Q, whose partial boxes every block reduces for itself, or of the list's span. BATCH: of each
 // list's span.
-template <bool BATCH>
+template <bool BATCH, int ROUNDS>
 __global__ __launch_bounds__(kSortBlock) void qkey_kernel(const void* q, int qdtype, int64_t nq,
                                                           const double* box_partial, int n_partial, const float2* span,
                                                           const int64_t* q_off, int64_t n_meshes, int bits,
@@ -175,8 +201,8 @@ __global__ __launch_bounds__(kSortBlock) void qkey_kernel(const void* q, int qdt
     __syncthreads();
   }
   const double cells = (double)(1u << bits);
-  const int64_t i0 = sort_first() + (tid & 63);
-  for (int r = 0; r < kSortRounds; ++r) {
+  const int64_t i0 = sort_first<ROUNDS>() + (tid & 63);
+  for (int r = 0; r < ROUNDS; ++r) {
     const int64_t i = i0 + r * 64;
     if (i >= nq) break;
     double Q[3];
@@ -205,13 +231,14 @@ __global__ __launch_bounds__(kSortBlock) void qkey_kernel(const void* q, int qdt
 }
 
 // Counts of the digit at `shift` per tile, digit-major.
+template <int ROUNDS>
 __global__ __launch_bounds__(kSortBlock) void sort_count_kernel(const uint32_t* keys, int64_t n, int shift,
                                                                 uint32_t* counts) {
   __shared__ uint32_t hist[kDigits];
   hist[threadIdx.x] = 0u;
   __syncthreads();
-  const int64_t i0 = sort_first() + (threadIdx.x & 63);
-  for (int r = 0; r < kSortRounds; ++r)
+  const int64_t i0 = sort_first<ROUNDS>() + (threadIdx.x & 63);
+  for (int r = 0; r < ROUNDS; ++r)
     if (i0 + r * 64 < n) atomicAdd(&hist[(keys[i0 + r * 64] >> shift) & (kDigits - 1)], 1u);
   __syncthreads();
   counts[(int64_t)threadIdx.x * gridDim.x + blockIdx.x] = hist[threadIdx.x];
@@ -254,20 +281,25 @@ __global__ __launch_bounds__(kSortBlock) void sort_scan_kernel(uint32_t* counts,
 }
 
 // One stable pass: every item to the place its digit's scanned count gives (vals NULL: an item's value is its index;
-// keys_out NULL: the last pass).
+// keys_out NULL: the last pass). STAGED (long lists): the tile is put in order in LDS first, so that a digit's items go
+// out side by side; written one by one, 4e6 random Q took 56 us a scatter.
+template <int ROUNDS, bool STAGED>
 __global__ __launch_bounds__(kSortBlock) void sort_scatter_kernel(const uint32_t* keys, const uint32_t* vals, int64_t n,
                                                                   int shift, const uint32_t* counts,
                                                                   const uint32_t* totals, uint32_t* keys_out,
                                                                   uint32_t* vals_out) {
+  constexpr int kStage = STAGED ? kSortBlock * ROUNDS : 1;
   __shared__ uint32_t part[kSortWaves];
   __shared__ uint32_t place[kSortWaves][kDigits];  // next place of each digit in each wavefront's part
+  __shared__ uint32_t base[STAGED ? kDigits : 1];  // place in the list less place in the tile, per digit
+  __shared__ uint32_t skey[kStage], sval[kStage];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   for (int u = 0; u < kSortWaves; ++u) place[u][tid] = 0u;
   __syncthreads();
-  const int64_t i0 = sort_first() + lane;
-  uint32_t key[kSortRounds];
+  const int64_t i0 = sort_first<ROUNDS>() + lane;
+  uint32_t key[ROUNDS];
 #pragma unroll
-  for (int r = 0; r < kSortRounds; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     const int64_t i = i0 + r * 64;
     key[r] = i < n ? keys[i] : 0u;
     if (i < n) atomicAdd(&place[w][(key[r] >> shift) & (kDigits - 1)], 1u);
@@ -276,6 +308,13 @@ __global__ __launch_bounds__(kSortBlock) void sort_scatter_kernel(const uint32_t
   {
     uint32_t total;
     uint32_t at = block_scan(totals[tid], part, total) + counts[(int64_t)tid * gridDim.x + blockIdx.x];
+    if constexpr (STAGED) {
+      uint32_t mine = 0u;
+      for (int u = 0; u < kSortWaves; ++u) mine += place[u][tid];
+      const uint32_t in_tile = block_scan(mine, part, total);
+      base[tid] = at - in_tile;
+      at = in_tile;
+    }
     for (int u = 0; u < kSortWaves; ++u) {
       const uint32_t c = place[u][tid];
       place[u][tid] = at;
@@ -284,7 +323,7 @@ __global__ __launch_bounds__(kSortBlock) void sort_scatter_kernel(const uint32_t
   }
   __syncthreads();
 #pragma unroll
-  for (int r = 0; r < kSortRounds; ++r) {
+  for (int r = 0; r < ROUNDS; ++r) {
     const int64_t i = i0 + r * 64;
     const bool valid = i < n;
     const uint32_t d = (key[r] >> shift) & (kDigits - 1);
@@ -306,8 +345,23 @@ __global__ __launch_bounds__(kSortBlock) void sort_scatter_kernel(const uint32_t
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (valid) {
-      if (keys_out) keys_out[at] = key[r];
-      vals_out[at] = vals ? vals[i] : (uint32_t)i;
+      const uint32_t v = vals ? vals[i] : (uint32_t)i;
+      if constexpr (STAGED) {
+        skey[at] = key[r];
+        sval[at] = v;
+      } else {
+        if (keys_out) keys_out[at] = key[r];
+        vals_out[at] = v;
+      }
+    }
+  }
+  if constexpr (STAGED) {
+    __syncthreads();
+    const int m = (int)min((int64_t)kStage, n - (int64_t)blockIdx.x * kStage);
+    for (int j = tid; j < m; j += kSortBlock) {
+      const uint32_t k = skey[j], at = base[(k >> shift) & (kDigits - 1)] + (uint32_t)j;
+      if (keys_out) keys_out[at] = k;
+      vals_out[at] = sval[j];
     }
   }
 }
@@ -357,7 +411,40 @@ inline unsigned grid_for(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-int64_t qorder_counts(int64_t nq) { return (nq + kSortTile - 1) / kSortTile * kDigits + kDigits; }
+int64_t qorder_counts(int64_t nq) { return sort_tiles(nq) * kDigits + kDigits; }
+
+namespace {
+template <int ROUNDS, bool STAGED>
+hipError_t sort_by_key(const void* q, int qdtype, int64_t nq, const int64_t* d_q_off, int64_t n_meshes, int boxes,
+                       const QOrderScratch& w, hipStream_t s) {
+  int mesh_bits = 0;
+  while (mesh_bits < 32 && ((int64_t)1 << mesh_bits) < n_meshes) ++mesh_bits;
+  const int bits = std::min(5, (32 - mesh_bits) / 3);  // Morton bits per axis
+  const int passes = std::max(1, (mesh_bits + 3 * bits + 7) / 8);
+  const unsigned tiles = (unsigned)sort_tiles(nq);
+  const uint32_t* vals = nullptr;
+  uint32_t *from = w.keys, *to = w.keys2, *totals = w.counts + (int64_t)tiles * kDigits;
+  for (int p = 0; p < passes; ++p) {
+    const bool last = p + 1 == passes;
+    if (p == 0 && d_q_off)
+      qkey_kernel<true, ROUNDS><<<tiles, kSortBlock, 0, s>>>(q, qdtype, nq, nullptr, 0, w.span, d_q_off, n_meshes, bits,
+                                                             from, w.counts);
+    else if (p == 0)
+      qkey_kernel<false, ROUNDS><<<tiles, kSortBlock, 0, s>>>(q, qdtype, nq, w.box_partial, boxes, w.span, nullptr, 1,
+                                                              bits, from, w.counts);
+    else
+      sort_count_kernel<ROUNDS><<<tiles, kSortBlock, 0, s>>>(from, nq, 8 * p, w.counts);
+    sort_scan_kernel<<<kDigits, kSortBlock, 0, s>>>(w.counts, tiles, totals);
+    // the values end in w.perm: passes before the last alternate so that they do
+    uint32_t* out = (passes - 1 - p) % 2 == 0 ? w.perm : w.vals;
+    sort_scatter_kernel<ROUNDS, STAGED><<<tiles, kSortBlock, 0, s>>>(from, vals, nq, 8 * p, w.counts, totals,
+                                                                     last ? nullptr : to, out);
+    vals = out;
+    std::swap(from, to);
+  }
+  return hipGetLastError();
+}
+}  // namespace
 
 hipError_t launch_qorder(const void* q, int qdtype, int64_t nq, const int64_t* d_q_off, int64_t n_meshes,
                          const QOrderScratch& w, hipStream_t s) {
@@ -369,32 +456,8 @@ hipError_t launch_qorder(const void* q, int qdtype, int64_t nq, const int64_t* d
     batch_span_kernel<<<dim3((unsigned)n_meshes, 3), kSpanSample, 0, s>>>(q, qdtype, d_q_off, w.span);
   else
     qbox_partial_kernel<<<nb + 3, 256, 0, s>>>(q, qdtype, nq, w.box_partial, w.span);
-  int mesh_bits = 0;
-  while (mesh_bits < 32 && ((int64_t)1 << mesh_bits) < n_meshes) ++mesh_bits;
-  const int bits = std::min(5, (32 - mesh_bits) / 3);  // Morton bits per axis
-  const int passes = std::max(1, (mesh_bits + 3 * bits + 7) / 8);
-  const unsigned tiles = (unsigned)((nq + kSortTile - 1) / kSortTile);
-  const uint32_t* vals = nullptr;
-  uint32_t *from = w.keys, *to = w.keys2, *totals = w.counts + (int64_t)tiles * kDigits;
-  for (int p = 0; p < passes; ++p) {
-    const bool last = p + 1 == passes;
-    if (p == 0 && d_q_off)
-      qkey_kernel<true><<<tiles, kSortBlock, 0, s>>>(q, qdtype, nq, nullptr, 0, w.span, d_q_off, n_meshes, bits, from,
-                                                     w.counts);
-    else if (p == 0)
-      qkey_kernel<false><<<tiles, kSortBlock, 0, s>>>(q, qdtype, nq, w.box_partial, nb, w.span, nullptr, 1, bits, from,
-                                                      w.counts);
-    else
-      sort_count_kernel<<<tiles, kSortBlock, 0, s>>>(from, nq, 8 * p, w.counts);
-    sort_scan_kernel<<<kDigits, kSortBlock, 0, s>>>(w.counts, tiles, totals);
-    // the values end in w.perm: passes before the last alternate so that they do
-    uint32_t* out = (passes - 1 - p) % 2 == 0 ? w.perm : w.vals;
-    sort_scatter_kernel<<<tiles, kSortBlock, 0, s>>>(from, vals, nq, 8 * p, w.counts, totals,
-                                                     last ? nullptr : to, out);
-    vals = out;
-    std::swap(from, to);
-  }
-  return hipGetLastError();
+  return sort_rounds(nq) == kSortRounds ? sort_by_key<kSortRounds, false>(q, qdtype, nq, d_q_off, n_meshes, nb, w, s)
+                                        : sort_by_key<kSortRoundsLong, true>(q, qdtype, nq, d_q_off, n_meshes, nb, w, s);
 }
 
 hipError_t launch_qrec32_gather(const void* q, int qdtype, const void* grad_out, int64_t nq, const uint32_t* perm,
