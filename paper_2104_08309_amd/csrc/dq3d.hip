@@ -195,6 +195,30 @@ __device__ __forceinline__ void store_complex(void* p, int c128, int64_t i, doub
     static_cast<float2*>(p)[i] = make_float2((float)re, (float)im);
 }
 
+// The regions' splits, radii and densities in order, each read through the scalar cache while the region before is worked
+// on (nothing writes them while the kernel runs).
+struct RegionCursor {
+  struct Entry {
+    int s0, s1;
+    double R, rho;
+  };
+  using Split = const __attribute__((address_space(4))) int32_t*;
+  using Real = const __attribute__((address_space(4))) double*;
+  Entry ahead;
+  __device__ __forceinline__ static Entry read(const RegionArgs& r, int j, int s0, double R) {
+    return Entry{s0, ((Split)r.region_split)[j + 1], r.region_R ? ((Real)r.region_R)[j] : R, ((Real)r.rho)[j]};
+  }
+  __device__ __forceinline__ RegionCursor(const RegionArgs& r, double R) {
+    if (r.nreg > 0) ahead = read(r, 0, ((Split)r.region_split)[0], R);
+  }
+  // Entry j (called with j = 0, 1, ..); R: the mesh's radius, where regions have none of their own.
+  __device__ __forceinline__ Entry next(const RegionArgs& r, int j, double R) {
+    const Entry e = ahead;
+    if (j + 1 < r.nreg) ahead = read(r, j + 1, e.s1, R);
+    return e;
+  }
+};
+
 __global__ __launch_bounds__(kFinishBlock) void regions_finish_kernel(FwdArgs a, RegionArgs r, int out_c128) {
   __shared__ double lds[kFinishBlock / 64];
   const int64_t qi = (int64_t)blockIdx.x * kFinishBlock + threadIdx.x;
@@ -209,22 +233,20 @@ __global__ __launch_bounds__(kFinishBlock) void regions_finish_kernel(FwdArgs a,
   sincos(Q[0] * mi.t[0] + Q[1] * mi.t[1] + Q[2] * mi.t[2], &st, &ct);
   const double2 g = (valid && r.grad_out) ? load_cot(r.grad_out, out_c128, dst) : make_double2(0.0, 0.0);
   double Fr = 0.0, Fi = 0.0;
+  RegionCursor reg(r, mi.R);
   for (int j = 0; j < r.nreg; ++j) {
+    const RegionCursor::Entry e = reg.next(r, j, mi.R);
     double xr = 0.0, xi = 0.0;
-    if (valid) {
-      const int s0 = r.region_split[j];
-      add_partials(a.partial + (int64_t)s0 * a.nq + qi, a.nq, r.region_split[j + 1] - s0, xr, xi);
-    }
-    if (!(qabs * (r.region_R ? r.region_R[j] : mi.R) < a.tau0)) {  // this region's small-|Q| test
+    if (valid) add_partials(a.partial + (int64_t)e.s0 * a.nq + qi, a.nq, e.s1 - e.s0, xr, xi);
+    if (!(qabs * e.R < a.tau0)) {  // this region's small-|Q| test
       xr /= Q2;
       xi /= Q2;
     }
     if (!out_c128 && fp32c_phase_out_of_range(qabs, mi)) xr = xi = quiet_nan();  // beyond the FP32C phase range
     const double fr = ct * xr - st * xi, fi = ct * xi + st * xr;
     if (valid && r.out_regions) store_complex(r.out_regions, out_c128, (int64_t)j * a.nq + dst, fr, fi);
-    const double rho = r.rho[j];
-    Fr += rho * fr;
-    Fi += rho * fi;
+    Fr += e.rho * fr;
+    Fi += e.rho * fi;
     if (r.rho_part) {
       const double t = block_total<kFinishBlock>(g.x * fr + g.y * fi, lds);  // Re(conj(g) F_j)
       if (threadIdx.x == 0) r.rho_part[(int64_t)blockIdx.x * r.nreg + j] = t;
@@ -237,6 +259,40 @@ __global__ __launch_bounds__(kFinishBlock) void regions_finish_kernel(FwdArgs a,
       static_cast<double*>(a.intensity)[dst] = Fr * Fr + Fi * Fi;
     else
       static_cast<float*>(a.intensity)[dst] = (float)(Fr * Fr + Fi * Fi);
+  }
+}
+
+// The four sums of split s (0 past the last).
+__device__ __forceinline__ void load_split(const DqArgs& a, int64_t qi, bool valid, int s, double2* x) {
+  if (s < a.splits && valid) {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = load_stream(a.partial + ((int64_t)s * 4 + c) * a.nq + qi);
+  } else {
+#pragma unroll
+    for (int c = 0; c < 4; ++c) x[c] = make_double2(0.0, 0.0);
+  }
+}
+
+// Adds the four sums of n splits, p[(4 s + c) nq], to v in split order, those of kAhead splits in flight at a time (40 regions
+// of 10 splits x 200 Q: 150 us a split at a time, 385 us a sum at a time and eight splits ahead, which leaves the last
+// splits of each sum one by one, 126 us so).
+__device__ __forceinline__ void add_partials4(const double2* p, int64_t nq, int n, double* v) {
+  constexpr int kAhead = 4;
+  for (int s = 0; s < n; s += kAhead) {
+    double2 x[kAhead][4];
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+      if (s + k < n)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) x[k][c] = load_stream(p + ((int64_t)(s + k) * 4 + c) * nq);
+#pragma unroll
+    for (int k = 0; k < kAhead; ++k)
+      if (s + k < n)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+          v[2 * c] += x[k][c].x;
+          v[2 * c + 1] += x[k][c].y;
+        }
   }
 }
 
@@ -255,17 +311,24 @@ __global__ __launch_bounds__(kFinishBlock) void dq_finish_kernel(DqArgs a, Regio
   sincos(Q[0] * mi.t[0] + Q[1] * mi.t[1] + Q[2] * mi.t[2], &st, &ct);
   const double2 g = valid ? load_cot(r.grad_out, go_c128, dst) : make_double2(0.0, 0.0);
   double gq[3] = {0.0, 0.0, 0.0};
+  RegionCursor reg(r, mi.R);
+  double2 ahead[4];  // the sums of the split after the region's last, on their way while the region is worked on
+  load_split(a, qi, valid, 0, ahead);
   for (int j = 0; j < r.nreg; ++j) {
+    const RegionCursor::Entry e = reg.next(r, j, mi.R);
     double v[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    if (valid) {
-      const int s0 = r.region_split[j], n = r.region_split[j + 1] - s0;
+    if (e.s1 > e.s0) {
 #pragma unroll
-      for (int c = 0; c < 4; ++c)
-        add_partials(a.partial + ((int64_t)s0 * 4 + c) * a.nq + qi, 4 * a.nq, n, v[2 * c], v[2 * c + 1]);
+      for (int c = 0; c < 4; ++c) {
+        v[2 * c] = ahead[c].x;
+        v[2 * c + 1] = ahead[c].y;
+      }
+      load_split(a, qi, valid, e.s1, ahead);
+      if (valid) add_partials4(a.partial + (int64_t)(e.s0 + 1) * 4 * a.nq + qi, a.nq, e.s1 - e.s0 - 1, v);
     }
     // centred F_c and grad F_c
     double fcr, fci, gcr[3], gci[3];
-    if (qabs * (r.region_R ? r.region_R[j] : mi.R) < a.tau) {  // this region's small-|Q| test
+    if (qabs * e.R < a.tau) {  // this region's small-|Q| test
       fcr = v[6];
       fci = v[7];
       for (int c = 0; c < 3; ++c) gcr[c] = v[2 * c], gci[c] = v[2 * c + 1];
@@ -283,12 +346,11 @@ __global__ __launch_bounds__(kFinishBlock) void dq_finish_kernel(DqArgs a, Regio
       fcr = fci = quiet_nan();
       for (int c = 0; c < 3; ++c) gcr[c] = gci[c] = quiet_nan();
     }
-    const double rho = r.rho[j];
     for (int c = 0; c < 3; ++c) {
       // grad F = exp(iQ.t) (grad F_c + i t F_c)
       const double ur = gcr[c] - mi.t[c] * fci, ui = gci[c] + mi.t[c] * fcr;
       const double wr = ct * ur - st * ui, wi = ct * ui + st * ur;
-      gq[c] += rho * (g.x * wr + g.y * wi);
+      gq[c] += e.rho * (g.x * wr + g.y * wi);
     }
     if (r.rho_part) {
       const double fr = ct * fcr - st * fci, fi = ct * fci + st * fcr;
