@@ -939,9 +939,11 @@ pft_status plan_regions(Arena& ar, const int64_t* off, int64_t nreg, int64_t nq,
 // Whether a polygon mesh of nf faces and nref vertex references goes through its nref - 2 nf fan triangles. In FP32C a
 // fan triangle costs about 105 issue cycles per Q (170 to 210 beyond the fitted phase range), the polygon kernel 59 per
 // edge and 166 per face: at 150 per triangle the line lies between faces of five and six edges (lat-long sphere of 2 624
-// quads and triangles x 125 000 Q, profiled kernels: 0.76 ms through triangles, 1.20 ms through the polygon kernel; a 40-gon prism the
-// other way round). In binary64 a triangle (450) is cheaper than the edge form's library sine and division per vertex
-// at any size.
+// quads and triangles x 125 000 Q, profiled kernels: 0.76 ms through triangles, 1.20 ms through the polygon kernel; a 40-gon
+// prism the other way round). In binary64 always: against a native loop over edges with the library's sine and a division
+// each, prisms over nu-gons of radius 40 x 200 000 Q take, native -> triangles, nu = 12 207 -> 168 us, 40 411 -> 352, 60
+// 487 -> 492, 100 657 -> 763 and 250 1 420 -> 1 680 with |Q| to 0.5, but 250 1 640 -> 1 070 with |Q| to 0.05 (and 644 -> 382
+// at 1 000 Q), and the error is a tenth to a third of the native form's (120-gon stars 8e-15 -> 2e-15).
 bool poly_as_triangles(int64_t nf, int64_t nref, bool c128) {
   return c128 || 150 * (nref - 2 * nf) <= 59 * nref + 166 * nf;
 }

@@ -78,7 +78,7 @@ __global__ __launch_bounds__(kBlock) void batch_fwd_fp64_kernel(const BatchGroup
       for (int i = lane; i < nt * (int)(sizeof(Face64) / 16); i += kBlock)
         reinterpret_cast<uint4*>(tile)[i] = reinterpret_cast<const uint4*>(f64 + t0)[i];
       __syncthreads();
-      for (int j = 0; j < nt; ++j) fwd_face_f64<1>(tile[j], &Qd, big, &xr, &xi);
+      for (int j = 0; j < nt; ++j) fwd_face_f64<1, true>(tile[j], &Qd, big, &xr, &xi);
     }
     if (__any(small)) {
       double x[2] = {xr, xi};

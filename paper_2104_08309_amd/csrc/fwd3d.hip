@@ -94,6 +94,7 @@ __global__ __launch_bounds__(kFwdBlock, kFwdWaves64) void fwd3d_fp64_kernel(FwdA
   double Q[QPT][3], xr[QPT], xi[QPT];
   bool small[QPT];
   bool any_small = false, big = false;
+  float qmax = 0.0f;
 #pragma unroll
   for (int k = 0; k < QPT; ++k) {
     const int64_t qi = (int64_t)qtile * kQT + k * 64 + lane;
@@ -103,8 +104,11 @@ __global__ __launch_bounds__(kFwdBlock, kFwdWaves64) void fwd3d_fp64_kernel(FwdA
     small[k] = qi < a.nq && sqrt(Q2) * geo.w < a.tau0;
     any_small |= small[k];
     big |= big_phases64(Q2, a.info[0].R);
+    qmax = fmaxf(qmax, (float)sqrt(Q2));
     xr[k] = xi[k] = 0.0;
   }
+  const bool check = __builtin_amdgcn_readfirstlane((int)fit_range_test_needed64(
+                         wave_max(qmax), fmax(a.info[0].rho, a.info[0].fan_rho))) != 0;
   for (int64_t t0 = f_begin; t0 < f_end; t0 += kTileF64) {
     const int nt = (int)min((int64_t)kTileF64, f_end - t0);
     wave_lds_fence();
@@ -114,7 +118,10 @@ __global__ __launch_bounds__(kFwdBlock, kFwdWaves64) void fwd3d_fp64_kernel(FwdA
       for (int i = lane; i < nt * (int)(sizeof(Face64) / 16); i += 64) dst[i] = src[i];
     }
     wave_lds_fence();
-    for (int j = 0; j < nt; ++j) fwd_face_f64<QPT>(tile[j], Q, big, xr, xi);
+    if (check)
+      for (int j = 0; j < nt; ++j) fwd_face_f64<QPT, true>(tile[j], Q, big, xr, xi);
+    else
+      for (int j = 0; j < nt; ++j) fwd_face_f64<QPT, false>(tile[j], Q, big, xr, xi);
   }
   if (__any(any_small)) {  // small-|Q| lanes: the tetrahedron fan about the apex instead
     const double o[3] = {geo.x, geo.y, geo.z};
