@@ -35,7 +35,8 @@ constexpr int kBoxBlocks = 256;
 constexpr int kSpanSample = 256;
 constexpr int kSpanTrim = 4;
 __device__ __forceinline__ void list_span(const void* q, int qdtype, int64_t b, int64_t n, int axis, float2* out) {
-  __shared__ float x[kSpanSample], end[2];
+  __shared__ alignas(16) float x[kSpanSample];
+  __shared__ float end[2];
   const int tid = threadIdx.x;
   if (n <= 64) {
     if (tid == 0) *out = make_float2(0.0f, 0.0f);
@@ -51,10 +52,11 @@ __device__ __forceinline__ void list_span(const void* q, int qdtype, int64_t b, 
   __syncthreads();
   const float mine = x[tid];
   int below = 0, upto = 0;  // of the sample: less than mine, at most mine
-  for (int i = 0; i < kSpanSample; ++i) {
-    const float u = x[i];
-    below += u < mine;
-    upto += u <= mine;
+#pragma unroll 8
+  for (int i = 0; i < kSpanSample / 4; ++i) {
+    const float4 u = reinterpret_cast<const float4*>(x)[i];
+    below += (u.x < mine) + (u.y < mine) + (u.z < mine) + (u.w < mine);
+    upto += (u.x <= mine) + (u.y <= mine) + (u.z <= mine) + (u.w <= mine);
   }
   // the sample's values at the two places (the threads of equals of such a value write the same)
   constexpr int kLo = kSpanTrim, kHi = kSpanSample - 1 - kSpanTrim;
