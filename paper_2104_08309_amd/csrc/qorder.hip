@@ -180,6 +180,7 @@ __global__ __launch_bounds__(kSortBlock) void qkey_kernel(const void* q, int qdt
   double lo[3], ext[3];
   if constexpr (!BATCH) {
     __shared__ double red[6][kSortBlock];
+    const float2 own[3] = {span[0], span[1], span[2]};
     for (int k = 0; k < 6; ++k)
       red[k][tid] = tid < n_partial ? box_partial[tid * 6 + k] : (k < 3 ? INFINITY : -INFINITY);
     __syncthreads();
@@ -194,9 +195,9 @@ __global__ __launch_bounds__(kSortBlock) void qkey_kernel(const void* q, int qdt
     for (int k = 0; k < 3; ++k) {
       lo[k] = red[k][0];
       ext[k] = red[3 + k][0] - lo[k];
-      if (ext[k] > 4.0 * (double)span[k].y) {
-        lo[k] = (double)span[k].x;
-        ext[k] = (double)span[k].y;
+      if (ext[k] > 4.0 * (double)own[k].y) {
+        lo[k] = (double)own[k].x;
+        ext[k] = (double)own[k].y;
       }
     }
   } else {
