@@ -71,6 +71,8 @@ __global__ __launch_bounds__(kBlock) void batch_fwd_fp64_kernel(const BatchGroup
     const double Q2d = Qd[0] * Qd[0] + Qd[1] * Qd[1] + Qd[2] * Qd[2];
     const bool small = active && sqrt(Q2d) * R < tau0;
     const bool big = big_phases64(Q2d, R);
+    // a wavefront of small Q alone: the fan in the loop and no surface sums (few Q: the lane-per-face fan below)
+    const bool surface = __any(active && !small), fans = !surface && __popcll(__ballot(small)) > kFanShared;
     double xr = 0.0, xi = 0.0;
     for (int64_t t0 = it.f0; t0 < f_end; t0 += kTileF) {
       const int nt = (int)min((int64_t)kTileF, f_end - t0);
@@ -78,9 +80,17 @@ __global__ __launch_bounds__(kBlock) void batch_fwd_fp64_kernel(const BatchGroup
       for (int i = lane; i < nt * (int)(sizeof(Face64) / 16); i += kBlock)
         reinterpret_cast<uint4*>(tile)[i] = reinterpret_cast<const uint4*>(f64 + t0)[i];
       __syncthreads();
-      for (int j = 0; j < nt; ++j) fwd_face_f64<1, true>(tile[j], &Qd, big, &xr, &xi);
+      if (fans) {
+        for (int j = 0; j < nt; ++j) {
+          double t[2] = {0.0, 0.0};
+          tet_term_f64(tile[j], Qd, t[0], t[1], kZeroOrigin);
+          add_term(xr, t[0]);
+          add_term(xi, t[1]);
+        }
+      } else if (surface)
+        for (int j = 0; j < nt; ++j) fwd_face_f64<1, true>(tile[j], &Qd, big, &xr, &xi);
     }
-    if (__any(small)) {
+    if (__any(small) && !fans) {
       double x[2] = {xr, xi};
       fan_sum<2>(small, it.f0, f_end, Qd,
                  [&](int64_t f, const double* q, double* t) { tet_term_f64(f64[f], q, t[0], t[1], kZeroOrigin); }, x);

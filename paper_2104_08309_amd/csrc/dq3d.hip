@@ -67,6 +67,7 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp64_kernel(DqArgs a) {
   const double o[3] = {geo.x, geo.y, geo.z};
   const double Q2 = Q[0] * Q[0] + Q[1] * Q[1] + Q[2] * Q[2];
   const bool small = active && sqrt(Q2) * geo.w < a.tau, big = big_phases64(Q2, a.info[0].R);
+  const bool surface = __any(active && !small);  // no surface sums for a wavefront whose Q are all small
   int64_t f_begin, f_end;
   split_range(a, f_begin, f_end);
   double Ar[3] = {0.0, 0.0, 0.0}, Ai[3] = {0.0, 0.0, 0.0}, Br = 0.0, Bi = 0.0;
@@ -81,7 +82,8 @@ __global__ __launch_bounds__(kBlock) void dq3d_fp64_kernel(DqArgs a) {
       for (int i = threadIdx.x; i < nt * 8; i += kBlock) gtile[i / 8][i % 8] = gs[i];
     }
     __syncthreads();
-    for (int j = 0; j < nt; ++j) dq_term_f64(tile[j], gtile[j], Q, big, Ar, Ai, Br, Bi);
+    if (surface)
+      for (int j = 0; j < nt; ++j) dq_term_f64(tile[j], gtile[j], Q, big, Ar, Ai, Br, Bi);
   }
   if (__any(small)) dq_fan(a, small, f_begin, f_end, Q, o, Ar, Ai, Br, Bi);
   if (active) {

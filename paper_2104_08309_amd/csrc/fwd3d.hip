@@ -93,7 +93,7 @@ __global__ __launch_bounds__(kFwdBlock, kFwdWaves64) void fwd3d_fp64_kernel(FwdA
   }
   double Q[QPT][3], xr[QPT], xi[QPT];
   bool small[QPT];
-  bool any_small = false, big = false;
+  bool any_small = false, surface = false, big = false;
   float qmax = 0.0f;
 #pragma unroll
   for (int k = 0; k < QPT; ++k) {
@@ -103,13 +103,18 @@ __global__ __launch_bounds__(kFwdBlock, kFwdWaves64) void fwd3d_fp64_kernel(FwdA
     const double Q2 = Q[k][0] * Q[k][0] + Q[k][1] * Q[k][1] + Q[k][2] * Q[k][2];
     small[k] = qi < a.nq && sqrt(Q2) * geo.w < a.tau0;
     any_small |= small[k];
+    surface |= qi < a.nq && !small[k];
     big |= big_phases64(Q2, a.info[0].R);
     qmax = fmaxf(qmax, (float)sqrt(Q2));
     xr[k] = xi[k] = 0.0;
   }
   const bool check = __builtin_amdgcn_readfirstlane((int)fit_range_test_needed64(
                          wave_max(qmax), fmax(a.info[0].rho, a.info[0].fan_rho))) != 0;
-  for (int64_t t0 = f_begin; t0 < f_end; t0 += kTileF64) {
+  // A wavefront of small Q alone takes the fan in the loop, QPT Q to a face's record and vertices, and no surface
+  // sums (few Q: the lane-per-face fan below).
+  const bool fans = !__any(surface) && __popcll(__ballot(small[0])) > kFanShared;
+  const double o[3] = {geo.x, geo.y, geo.z};
+  for (int64_t t0 = f_begin; t0 < f_end && (fans || __any(surface)); t0 += kTileF64) {
     const int nt = (int)min((int64_t)kTileF64, f_end - t0);
     wave_lds_fence();
     {
@@ -118,18 +123,26 @@ __global__ __launch_bounds__(kFwdBlock, kFwdWaves64) void fwd3d_fp64_kernel(FwdA
       for (int i = lane; i < nt * (int)(sizeof(Face64) / 16); i += 64) dst[i] = src[i];
     }
     wave_lds_fence();
-    if (check)
+    if (fans) {
+      for (int j = 0; j < nt; ++j)
+#pragma unroll
+        for (int k = 0; k < QPT; ++k) {
+          double t[2] = {0.0, 0.0};
+          tet_term_f64(tile[j], Q[k], t[0], t[1], o);
+          add_term(xr[k], t[0]);
+          add_term(xi[k], t[1]);
+        }
+    } else if (check)
       for (int j = 0; j < nt; ++j) fwd_face_f64<QPT, true>(tile[j], Q, big, xr, xi);
     else
       for (int j = 0; j < nt; ++j) fwd_face_f64<QPT, false>(tile[j], Q, big, xr, xi);
   }
   if (__any(any_small)) {  // small-|Q| lanes: the tetrahedron fan about the apex instead
-    const double o[3] = {geo.x, geo.y, geo.z};
     const auto term = [&](int64_t f, const double* q, double* t) { tet_term_f64(a.f64[f], q, t[0], t[1], o); };
 #pragma unroll
     for (int k = 0; k < QPT; ++k) {
       double x[2] = {xr[k], xi[k]};
-      fan_sum<2>(small[k], f_begin, f_end, Q[k], term, x);
+      if (!fans) fan_sum<2>(small[k], f_begin, f_end, Q[k], term, x);
       if (small[k] && a.split_geo) apex_phase(Q[k], o, x[0], x[1]);
       xr[k] = x[0];
       xi[k] = x[1];
