@@ -320,8 +320,7 @@ __global__ __launch_bounds__(256) void batch_bwd_reduce_kernel(const double* par
   const int32_t mesh = face_mesh[m];
   const int64_t nfm = tri_off[mesh + 1] - tri_off[mesh];
   const int64_t fl = m - tri_off[mesh];
-  double R = 0.0;
-  for (int c = 0; c < face_nchunks[mesh]; ++c) R += partial[(face_base[mesh] + (int64_t)c * nfm + fl) * 3 + k];
+  const double R = strided_sum(partial + (face_base[mesh] + fl) * 3 + k, nfm * 3, face_nchunks[mesh]);
   const Face64& f = f64[m];
   contrib[i * 3 + 0] = f.N[0] * R;
   contrib[i * 3 + 1] = f.N[1] * R;

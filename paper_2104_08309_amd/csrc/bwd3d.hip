@@ -110,8 +110,7 @@ __global__ __launch_bounds__(256) void face_contrib_kernel(const double* partial
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;  // corner slot 3m + k
   if (i >= nf * 3) return;
   const int64_t m = i / 3;
-  double R = 0.0;
-  for (int s = 0; s < qsplits; ++s) R += partial[(int64_t)s * nf * 3 + i];
+  double R = strided_sum(partial + i, nf * 3, qsplits);
   if (face_w) R *= face_w[m];  // density of the face's region
   const Face64& f = f64[m];
   contrib[i * 3 + 0] = f.N[0] * R;
@@ -187,8 +186,7 @@ __global__ __launch_bounds__(kGatherBlock) void gather_small_kernel(const int32_
   auto flush = [&](int n, int64_t i) {
     double c[3] = {0.0, 0.0, 0.0};
     if (lane < n) {
-      double R = 0.0;
-      for (int s = 0; s < qsplits; ++s) R += partial[(int64_t)s * nf * 3 + i];
+      double R = strided_sum(partial + i, nf * 3, qsplits);
       if (face_w) R *= face_w[i / 3];  // density of the face's region
       for (int k = 0; k < 3; ++k) c[k] = f64[i / 3].N[k] * R;
     }
